@@ -885,6 +885,20 @@ __global__ __launch_bounds__(256, 2) void gemm32v_kernel(Gemm32 g) {
       }
 }
 
+// Output tiles of row panel i that reach the lower triangle, and the tiles of a product
+// (all of them, or only those).
+__host__ __device__ __forceinline__ int64_t lower_tiles(int64_t i, int64_t tiles_n, int64_t bm, int64_t bn) {
+  const int64_t w = (i * bm + bm - 1) / bn + 1;
+  return w < tiles_n ? w : tiles_n;
+}
+__host__ __device__ __forceinline__ int64_t direct64_tiles(int64_t M, int64_t N, int64_t bm, int64_t bn, bool lower) {
+  const int64_t tn = (N + bn - 1) / bn, tm = (M + bm - 1) / bm;
+  if (!lower) return tm * tn;
+  int64_t t = 0;
+  for (int64_t i = 0; i < tm; ++i) t += lower_tiles(i, tn, bm, bn);
+  return t;
+}
+
 // FP64 products with the operands moved from global memory straight into LDS, as
 // gemm32d_kernel does for FP32: global_load_lds_dwordx4 (two doubles per lane),
 // three LDS stages, loads issued two K steps ahead, one barrier per step, the loop
@@ -898,31 +912,51 @@ __global__ __launch_bounds__(256, 2) void gemm32v_kernel(Gemm32 g) {
 // multiple of 8, even leading dimensions, 16-byte aligned bases and an even width
 // for an MN-major operand; whole 16-byte pieces past M or N are read from the
 // matrix's edge (their products reach only outputs that are not stored).
-template <int TM, int TN, bool TA, bool TB>
+template <int TM, int TN, bool TA, bool TB, bool KS>
 __global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
   constexpr int BK8 = 8;
   constexpr int BM = 32 * TM, BN = 32 * TN;
   constexpr int ASZ = BM * BK8, BSZ = BN * BK8;              // doubles per stage
   constexpr int NA = ASZ / 2 / 256, NB = BSZ / 2 / 256;      // 16-byte pieces per thread per stage
-  constexpr int NPER = NA + NB;
+  constexpr int NPER = NA + NB + (KS ? 1 : 0);
   static_assert(NA >= 1 && NB >= 1 && NPER < 16, "stage split");
   __shared__ __attribute__((aligned(16))) double A0[ASZ], A1[ASZ], A2[ASZ];
   __shared__ __attribute__((aligned(16))) double B0[BSZ], B1[BSZ], B2[BSZ];
+  // row scale of a step: every wave keeps its own copy (one 1 KB run, the 8 values
+  // of the step repeated), so the loads in flight are the same for all waves
+  constexpr int SSZ = KS ? 4 * 128 : 2;
+  __shared__ __attribute__((aligned(16))) double S0[SSZ], S1[SSZ], S2[SSZ];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int l16 = lane & 15, lq = lane >> 4;
   const int64_t tiles_n = (g.N + BN - 1) / BN, tiles_m = (g.M + BM - 1) / BM;
-  const int64_t ntile = tiles_n * tiles_m * g.splitk;
+  const int64_t tiles = direct64_tiles(g.M, g.N, BM, BN, g.lower_only);
+  const int64_t ntile = tiles * g.splitk;
   const int64_t per = ((ntile + 7) / 8);
   const int64_t T = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   if (T >= ntile) return;
-  constexpr int64_t GROUP = 8;
-  const int bz = (int)(T / (tiles_n * tiles_m));
-  const int64_t T2 = T % (tiles_n * tiles_m);
-  const int64_t grp = T2 / (GROUP * tiles_n), r2 = T2 % (GROUP * tiles_n);
-  const int64_t gh = (tiles_m - grp * GROUP < GROUP) ? tiles_m - grp * GROUP : GROUP;
-  const int64_t m0 = (grp * GROUP + r2 % gh) * BM, n0 = (r2 / gh) * BN;
-  if (g.lower_only && n0 > m0 + BM - 1) return;
+  const int bz = (int)(T / tiles);
+  const int64_t T2 = T % tiles;
+  int64_t m0, n0;
+  if (g.lower_only) {
+    // only the tiles that reach the lower triangle, row panel by row panel: all of a K
+    // split's tiles read the same rows of both operands
+    int64_t i = 0, first = 0;
+    while (true) {
+      const int64_t w = lower_tiles(i, tiles_n, BM, BN);
+      if (T2 < first + w) break;
+      first += w;
+      ++i;
+    }
+    m0 = i * BM;
+    n0 = (T2 - first) * BN;
+  } else {
+    constexpr int64_t GROUP = 8;
+    const int64_t grp = T2 / (GROUP * tiles_n), r2 = T2 % (GROUP * tiles_n);
+    const int64_t gh = (tiles_m - grp * GROUP < GROUP) ? tiles_m - grp * GROUP : GROUP;
+    m0 = (grp * GROUP + r2 % gh) * BM;
+    n0 = (r2 / gh) * BN;
+  }
 
   int64_t kbeg = 0, kend = g.K;
   if (g.splitk > 1) {
@@ -959,7 +993,7 @@ __global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
       return g.B + (k0 + k) * ldb + gc;
     }
   };
-  auto issue = [&](int64_t t, double* as, double* bs) {
+  auto issue = [&](int64_t t, double* as, double* bs, double* ss) {
     const int64_t k0 = kbeg + ((t < nk) ? t : nk - 1) * BK8;   // past the end: the last step again
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
@@ -973,6 +1007,9 @@ __global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
       __builtin_amdgcn_global_load_lds((const void*)src_b(run * 64 + lane, k0),
                                        (__attribute__((address_space(3))) void*)&bs[run * 128], 16, 0, 0);
     }
+    if constexpr (KS)
+      __builtin_amdgcn_global_load_lds((const void*)(g.kscale + k0 + 2 * (lane & 3)),
+                                       (__attribute__((address_space(3))) void*)&ss[wave * 128], 16, 0, 0);
   };
 
   d4_t acc[TM][TN];
@@ -982,16 +1019,17 @@ __global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
     for (int j = 0; j < TN; ++j) acc[i][j] = zero_d4();
 
   if (nk > 0) {
-    issue(0, A0, B0);
-    issue(1, A1, B1);
+    issue(0, A0, B0, S0);
+    issue(1, A1, B1, S1);
   }
   auto step = [&](int64_t t, const double* __restrict__ as, const double* __restrict__ bs,
-                  double* __restrict__ an, double* __restrict__ bn) {
+                  const double* __restrict__ ss, double* __restrict__ an, double* __restrict__ bn,
+                  double* __restrict__ sn) {
     __builtin_amdgcn_s_waitcnt(0xF70 | NPER);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    issue(t + 2, an, bn);
+    issue(t + 2, an, bn, sn);
     double a[TM][2], b[TN][2];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -1017,6 +1055,14 @@ __global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
         for (int kk = 0; kk < 2; ++kk) b[j][kk] = bs[(2 * lq + kk) * BN + n];
       }
     }
+    if constexpr (KS) {
+      const d2_t sv = *reinterpret_cast<const d2_t*>(&ss[wave * 128 + 2 * lq]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        b[j][0] *= sv[0];
+        b[j][1] *= sv[1];
+      }
+    }
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
@@ -1026,13 +1072,13 @@ __global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
   };
   int64_t t = 0;
   for (; t + 3 <= nk; t += 3) {
-    step(t, A0, B0, A2, B2);
-    step(t + 1, A1, B1, A0, B0);
-    step(t + 2, A2, B2, A1, B1);
+    step(t, A0, B0, S0, A2, B2, S2);
+    step(t + 1, A1, B1, S1, A0, B0, S0);
+    step(t + 2, A2, B2, S2, A1, B1, S1);
   }
   if (t < nk) {
-    step(t, A0, B0, A2, B2);
-    if (t + 1 < nk) step(t + 1, A1, B1, A0, B0);
+    step(t, A0, B0, S0, A2, B2, S2);
+    if (t + 1 < nk) step(t + 1, A1, B1, S1, A0, B0, S0);
   }
   // the two loads issued past the last step are still in flight: let them land
   // before the workgroup's LDS can be reused
@@ -1112,16 +1158,19 @@ void launch_big(const Gemm& g, dim3 grid, hipStream_t s) {
 
 template <int TN>
 void launch64d(const Gemm& g, dim3 grid, hipStream_t s) {
-  if (!g.transA && !g.transB) hipLaunchKernelGGL((gemm64d_kernel<4, TN, false, false>), grid, dim3(256), 0, s, g);
-  else if (g.transA && !g.transB) hipLaunchKernelGGL((gemm64d_kernel<4, TN, true, false>), grid, dim3(256), 0, s, g);
-  else if (!g.transA && g.transB) hipLaunchKernelGGL((gemm64d_kernel<4, TN, false, true>), grid, dim3(256), 0, s, g);
-  else hipLaunchKernelGGL((gemm64d_kernel<4, TN, true, true>), grid, dim3(256), 0, s, g);
+  if (g.kscale) hipLaunchKernelGGL((gemm64d_kernel<4, TN, true, false, true>), grid, dim3(256), 0, s, g);
+  else if (!g.transA && !g.transB) hipLaunchKernelGGL((gemm64d_kernel<4, TN, false, false, false>), grid, dim3(256), 0, s, g);
+  else if (g.transA && !g.transB) hipLaunchKernelGGL((gemm64d_kernel<4, TN, true, false, false>), grid, dim3(256), 0, s, g);
+  else if (!g.transA && g.transB) hipLaunchKernelGGL((gemm64d_kernel<4, TN, false, true, false>), grid, dim3(256), 0, s, g);
+  else hipLaunchKernelGGL((gemm64d_kernel<4, TN, true, true, false>), grid, dim3(256), 0, s, g);
 }
 
 // the LDS-direct FP64 kernel's requirements (see gemm64d_kernel)
 bool direct64_ok(const Gemm& g) {
   auto al = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
-  if (g.kscale || g.K % 8 != 0 || g.lda % 2 || g.ldb % 2 || !al(g.A) || !al(g.B)) return false;
+  if (g.K % 8 != 0 || g.lda % 2 || g.ldb % 2 || !al(g.A) || !al(g.B)) return false;
+  // the row scale is compiled for the Coulomb matrix's orientation only
+  if (g.kscale && (!g.transA || g.transB || !al(g.kscale))) return false;
   if ((g.transA && g.M % 2) || (!g.transB && g.N % 2)) return false;
   // both operands K-major over a long K (W = V chi^T at set-up): each 8-deep step
   // touches 64 bytes of every one of 192 rows megabytes apart, and the register-staged
@@ -1163,7 +1212,7 @@ hipError_t gemm_f64(const Gemm& g0, hipStream_t s) {
     // 128 x 64 tiles (three waves per SIMD; 128 x 128 holds two and ran slower on the
     // set-up's updates), one-dimensional grid in XCD-grouped tile order, padded to
     // whole rounds of eight
-    const int64_t ntile = ((g.N + 63) / 64) * ((g.M + 127) / 128) * g.splitk;
+    const int64_t ntile = direct64_tiles(g.M, g.N, 128, 64, g.lower_only) * g.splitk;
     if (ntile > (int64_t)UINT32_MAX - 8) return hipErrorInvalidValue;
     launch64d<2>(g, dim3((unsigned)((ntile + 7) / 8 * 8)), s);
   } else if (bn == 64) {

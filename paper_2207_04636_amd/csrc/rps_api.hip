@@ -1654,18 +1654,27 @@ void build_full_impl(rps_context& c, int32_t nocc, const double* C, double* K, i
 constexpr int64_t kCoulombChunk = 32ll << 20;   // doubles of U rows per chunk (256 MB)
 constexpr int kCoulombParts = 256;              // blocks of the E_J dot product
 
-// Split count of the J product over the grid: the smallest power of two giving at
-// least two workgroups per compute unit over the lower output tiles, at least 128
-// grid rows per split and partials within kSplitWork.
+// Split count of the J product over the grid: the count, of those that keep at least 128
+// grid rows per split and the partials within kSplitWork, with the least time by two rates
+// measured on it: the LDS-direct FP64 kernel works off rounds of 768 workgroups (lower
+// output tiles of 128 x 64, three per compute unit) at 65 TF/s, and the partials are
+// written and read back at 4 TB/s.
 int coulomb_splits(const rps_context& c) {
-  const int64_t bn = (c.Np <= 16) ? 16 : (c.Np <= 64) ? 64 : 128;   // output tile width of gemm_f64
+  const int64_t bn = (c.Np <= 16) ? 16 : 64;
   const int64_t tm = (c.Np + 127) / 128, tn = (c.Np + bn - 1) / bn;
   int64_t active = 0;
   for (int64_t i = 0; i < tm; ++i)
     for (int64_t j = 0; j < tn; ++j) active += (j * bn <= i * 128 + 127);
-  int64_t z = 1;
-  while (active * z < 512 && c.ngp / (z * 2) >= 128 && (z * 2) * c.Np * c.Np <= kSplitWork) z *= 2;
-  return (int)z;
+  int64_t best = 1;
+  double best_t = 1e300;
+  for (int64_t z = 1; z <= 512; ++z) {
+    if (z > 1 && (c.ngp / z < 128 || z * c.Np * c.Np > kSplitWork)) break;
+    const double rounds = (double)((active * z + 767) / 768);
+    const double t = rounds * (double)(c.ngp / z) * (2.0 * 128 * 64 * 768 / 65e12) +
+                     (double)z * (double)(c.Np * c.Np) * (16.0 / 4e12);
+    if (t < best_t) { best_t = t; best = z; }
+  }
+  return (int)best;
 }
 
 // Small-basis Coulomb path (one pass over Phi per step, U never stored): N <= 128, n <= 64.
