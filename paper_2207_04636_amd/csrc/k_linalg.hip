@@ -12,8 +12,11 @@
 //   projecting out the columns picked before, is largest.  That residual norm
 //   squared is the updated diagonal of a Cholesky factorisation of M^T M with
 //   the same pivot order, so the pivots are those of QRCP in exact arithmetic.
-//   Panels of 32 steps; the Gram matrix is updated after each panel.
+//   An explicit Gram matrix is updated after each panel of 32 steps; the per-atom
+//   sets of the selection never form theirs.
 #include <math.h>
+
+#include <algorithm>
 
 #include "mfma.h"
 #include "rps_internal.h"
@@ -97,68 +100,173 @@ __global__ __launch_bounds__(256) void tri64_kernel(const double* __restrict__ L
 }
 
 // ---------------- pivoted Cholesky
-__global__ void diag_init_kernel(const double* G, int64_t n, int64_t ld, double* diag) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n) diag[j] = G[j * ld + j];
+// The pivot of a step is the largest residual diagonal, ties to the lowest index; an
+// index that is taken (-inf) or not a number never wins.  No winner: index -1.
+struct PcBest {
+  double v;
+  int32_t i;
+};
+__device__ __forceinline__ PcBest pc_pick(PcBest a, PcBest b) {
+  const bool take = (b.i >= 0) && (a.i < 0 || b.v > a.v || (b.v == a.v && b.i < a.i));
+  return take ? b : a;
+}
+__device__ __forceinline__ PcBest pc_of(double d, int32_t j) { return PcBest{d, (d > -INFINITY) ? j : -1}; }
+__device__ __forceinline__ PcBest pc_wave(PcBest b) {
+  for (int off = 32; off > 0; off >>= 1) {
+    const PcBest o{__shfl_xor(b.v, off, 64), __shfl_xor(b.i, off, 64)};
+    b = pc_pick(b, o);
+  }
+  return b;
+}
+// over the 256 threads of a workgroup (every thread gets the result)
+__device__ __forceinline__ PcBest pc_block256(PcBest b, PcBest* red) {
+  b = pc_wave(b);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = b;
+  __syncthreads();
+  return pc_pick(pc_pick(red[0], red[1]), pc_pick(red[2], red[3]));
 }
 
-__global__ __launch_bounds__(1024) void argmax_kernel(const double* __restrict__ diag, int64_t n,
-                                                     int64_t* __restrict__ piv, double* __restrict__ dsel,
-                                                     int64_t k) {
-  __shared__ double sv[1024];
-  __shared__ int64_t si[1024];
-  double bv = -INFINITY;
-  int64_t bi = n;
-  for (int64_t j = threadIdx.x; j < n; j += 1024) {
-    const double v = diag[j];
-    if (v > bv) { bv = v; bi = j; }     // strided scan visits j in increasing order
+// One pivot step of every set in one launch (blockIdx.y = set, 256 candidates per
+// workgroup).  Each workgroup first reduces the block maxima that the previous step left,
+// so a step is one launch: column k of the factor
+//   L[j][k] = (G[p][j] - sum_{t=kb}^{k-1} L[j][t] L[p][t]) / sqrt(d_p),
+// the residual diagonal d_j -= L[j][k]^2, and the block maxima of the new diagonal.
+// k < 0 forms the diagonal and its block maxima only.
+//   FACT: G is never formed; G[p][j] = (a_p . a_j)(b_p . b_j) comes from the sketch
+//         products (PcArgs::AB, one column per candidate), L holds one column of the set
+//         after another.  A step reads 2p + k values per candidate: an atom's Gram matrix
+//         has |kappa|^2 (512 MB for a set of 8000) and was formed for 50-odd of its rows.
+//   else: one set with an explicit Gram matrix, updated by the caller after each panel;
+//         L row-major.
+// Bound by the launch and two dependent reads of a step: at 8 atoms of 8000 candidates
+// and 62 pivots each, 63 launches of 11 us (0.7 ms) take the place of 992 launches of
+// 4-5 us, 16 Gram products and 8 updates (14 ms in all).
+template <bool FACT>
+__global__ __launch_bounds__(256) void pchol_step_kernel(PcArgs a, int64_t k, int64_t kb) {
+  extern __shared__ double sh[];       // L[p][kb..k), then a_p and b_p
+  __shared__ PcBest red[4];
+  const PcSet it = FACT ? a.sets[blockIdx.y] : PcSet{0, a.n, a.k, 0};
+  const int64_t n = it.n;
+  const int nb = (int)((n + 255) / 256);
+  if ((int)blockIdx.x >= nb || k >= it.k) return;      // uniform over the workgroup
+  const int tid = threadIdx.x;
+  const int64_t j = (int64_t)blockIdx.x * 256 + tid;
+  double* diag = a.diag + it.row0;
+  const int64_t slot = (int64_t)blockIdx.y * a.nbmax;
+  const int64_t half = (int64_t)gridDim.y * a.nbmax;
+  double d = -INFINITY;
+  if (k < 0) {
+    if (j < n) {
+      if constexpr (FACT) {
+        double x = 0.0, y = 0.0;
+        for (int q = 0; q < a.p; ++q) {
+          const double u = a.AB[q * a.ldab + it.row0 + j], v = a.AB[(a.p + q) * a.ldab + it.row0 + j];
+          x += u * u;
+          y += v * v;
+        }
+        d = x * y;
+      } else {
+        d = a.G[j * a.ld + j];
+      }
+      diag[j] = d;
+    }
+  } else {
+    const double* bv = a.bv + ((k + 1) & 1) * half + slot;
+    const int32_t* bi = a.bi + ((k + 1) & 1) * half + slot;
+    PcBest b{0.0, -1};
+    for (int e = tid; e < nb; e += 256) b = pc_pick(b, PcBest{bv[e], bi[e]});
+    b = pc_block256(b, red);
+    const int64_t p = (b.i >= 0) ? b.i : 0;
+    const double dp = (b.i >= 0) ? b.v : 0.0;
+    if (blockIdx.x == 0 && tid == 0) a.piv[it.pofs + k] = p;
+    const int nt = (int)(k - kb);
+    double* Ls = a.L + (FACT ? it.row0 * a.ldl : 0);
+    for (int t = tid; t < nt; t += 256) sh[t] = FACT ? Ls[(kb + t) * n + p] : Ls[p * a.ldl + kb + t];
+    if constexpr (FACT)
+      for (int q = tid; q < 2 * a.p; q += 256) sh[nt + q] = a.AB[q * a.ldab + it.row0 + p];
+    __syncthreads();
+    if (j < n) {
+      d = diag[j];
+      double l = 0.0;
+      if (!(d == -INFINITY && j != p)) {       // else already selected: its residual is zero
+        double s;
+        if constexpr (FACT) {
+          double x = 0.0, y = 0.0;
+          for (int q = 0; q < a.p; ++q) {
+            x += a.AB[q * a.ldab + it.row0 + j] * sh[nt + q];
+            y += a.AB[(a.p + q) * a.ldab + it.row0 + j] * sh[nt + a.p + q];
+          }
+          s = x * y;
+          for (int t = 0; t < nt; ++t) s -= Ls[(kb + t) * n + j] * sh[t];
+        } else {
+          s = a.G[p * a.ld + j];
+          for (int t = 0; t < nt; ++t) s -= Ls[j * a.ldl + kb + t] * sh[t];
+        }
+        if (dp > 0.0) l = s / sqrt(dp);
+        d = (j == p) ? -INFINITY : d - l * l;
+        diag[j] = d;
+      }
+      if constexpr (FACT) Ls[k * n + j] = l;
+      else Ls[j * a.ldl + k] = l;
+    }
   }
-  sv[threadIdx.x] = bv;
-  si[threadIdx.x] = bi;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (threadIdx.x < off) {
-      const double v2 = sv[threadIdx.x + off];
-      const int64_t i2 = si[threadIdx.x + off];
-      if (v2 > sv[threadIdx.x] || (v2 == sv[threadIdx.x] && i2 < si[threadIdx.x])) {
-        sv[threadIdx.x] = v2;
-        si[threadIdx.x] = i2;
+  const PcBest m = pc_block256(pc_of(d, (int32_t)j), red);
+  if (tid == 0) {
+    const int64_t o = (k & 1) * half + slot + blockIdx.x;      // k = -1 and odd steps share a half
+    a.bv[o] = m.v;
+    a.bi[o] = m.i;
+  }
+}
+
+// A panel of up to 32 pivot steps of one set of at most 1024 candidates in one workgroup,
+// thread j holding candidate j's residual and panel row of L in registers (the same sums in
+// the same order as the step kernel).  A step costs two barriers and one read of a row of G:
+// 416 pivots of 496 candidates took two launches and 8.9 us a pivot, here 2.2 us.
+constexpr int PCP = 32;
+__global__ __launch_bounds__(1024) void pchol_panel_kernel(const double* __restrict__ G, int n, int64_t ld,
+                                                          double* __restrict__ L, int64_t ldl, int64_t kb,
+                                                          int steps, double* __restrict__ diag,
+                                                          int64_t* __restrict__ piv) {
+  __shared__ PcBest red[16];
+  __shared__ double lp[PCP];
+  const int j = threadIdx.x;
+  const bool live = j < n;
+  double d = live ? (kb == 0 ? G[(int64_t)j * ld + j] : diag[j]) : -INFINITY;
+  double l[PCP];
+#pragma unroll
+  for (int kk = 0; kk < PCP; ++kk) {
+    l[kk] = 0.0;
+    if (kk < steps) {      // uniform
+      PcBest b = pc_wave(pc_of(d, j));
+      if ((j & 63) == 0) red[j >> 6] = b;
+      __syncthreads();
+      b = red[j & 15];
+      for (int off = 8; off > 0; off >>= 1) {
+        const PcBest o{__shfl_xor(b.v, off, 64), __shfl_xor(b.i, off, 64)};
+        b = pc_pick(b, o);
+      }
+      const int p = (b.i >= 0) ? b.i : 0;
+      const double dp = (b.i >= 0) ? b.v : 0.0;
+      double s = live ? G[(int64_t)p * ld + j] : 0.0;
+      if (j == p) {
+#pragma unroll
+        for (int t = 0; t < kk; ++t) lp[t] = l[t];
+        piv[kb + kk] = p;
+      }
+      __syncthreads();
+      if (live) {
+        if (!(d == -INFINITY && j != p)) {
+#pragma unroll
+          for (int t = 0; t < kk; ++t) s -= l[t] * lp[t];
+          if (dp > 0.0) l[kk] = s / sqrt(dp);
+          d = (j == p) ? -INFINITY : d - l[kk] * l[kk];
+        }
+        L[(int64_t)j * ldl + kb + kk] = l[kk];
       }
     }
-    __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const int64_t p = (si[0] < n) ? si[0] : 0;
-    piv[k] = p;
-    dsel[k] = (si[0] < n) ? sv[0] : 0.0;
-  }
-}
-
-// Column k of the factor: L[j][k] = (G[p][j] - sum_{t=kb}^{k-1} L[j][t] L[p][t]) / sqrt(d_p)
-__global__ __launch_bounds__(256) void pchol_column_kernel(const double* __restrict__ G, int64_t n, int64_t ld,
-                                                          double* __restrict__ L, int64_t ldl, int64_t k,
-                                                          int64_t kb, const int64_t* __restrict__ piv,
-                                                          const double* __restrict__ dsel,
-                                                          double* __restrict__ diag) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const int64_t p = piv[k];
-  const double dp = dsel[k];                 // pivot value saved by the argmax step
-  const double dj = diag[j];
-  if (dj == -INFINITY && j != p) {           // already selected: its residual is zero
-    L[j * ldl + k] = 0.0;
-    return;
-  }
-  double s = G[p * ld + j];
-  for (int64_t t = kb; t < k; ++t) s -= L[j * ldl + t] * L[p * ldl + t];
-  double l = 0.0;
-  if (dp > 0.0) l = s / sqrt(dp);
-  L[j * ldl + k] = l;
-  if (j == p) {
-    diag[j] = -INFINITY;
-  } else {
-    diag[j] = dj - l * l;
-  }
+  if (live) diag[j] = d;
 }
 
 inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -230,16 +338,28 @@ hipError_t tri_solve_lower(const double* L, int64_t n, int64_t ldl, double* B, i
   return hipGetLastError();
 }
 
+int64_t pivoted_cholesky_work(int64_t n) { return n + 4 * ((n + 255) / 256); }
+
 hipError_t pivoted_cholesky(double* G, int64_t n, int64_t ld, int64_t k, int64_t* piv,
-                            double* Lbuf, double* diag, hipStream_t s) {
-  constexpr int64_t PB = 32;
-  hipLaunchKernelGGL(diag_init_kernel, dim3(nblk(n, 256)), dim3(256), 0, s, G, n, ld, diag);
+                            double* Lbuf, double* work, hipStream_t s) {
+  constexpr int64_t PB = PCP;
+  if (n > INT32_MAX) return hipErrorInvalidValue;
+  const bool one = n <= 1024;     // the candidates fit one workgroup
+  PcArgs a{};
+  a.n = n; a.k = k; a.nbmax = (n + 255) / 256;
+  a.G = G; a.ld = ld; a.L = Lbuf; a.ldl = k; a.diag = work; a.piv = piv;
+  a.bv = work + n;
+  a.bi = reinterpret_cast<int32_t*>(work + n + 2 * a.nbmax);
+  const dim3 grid((unsigned)a.nbmax, 1u);
+  if (!one) hipLaunchKernelGGL(pchol_step_kernel<false>, grid, dim3(256), 0, s, a, (int64_t)-1, (int64_t)0);
   for (int64_t kb = 0; kb < k; kb += PB) {
     const int64_t ke = (kb + PB < k) ? kb + PB : k;
-    for (int64_t kk = kb; kk < ke; ++kk) {
-      hipLaunchKernelGGL(argmax_kernel, dim3(1), dim3(1024), 0, s, diag, n, piv, diag + n, kk);
-      hipLaunchKernelGGL(pchol_column_kernel, dim3(nblk(n, 256)), dim3(256), 0, s, G, n, ld, Lbuf, k,
-                         kk, kb, piv, diag + n, diag);
+    if (one) {
+      hipLaunchKernelGGL(pchol_panel_kernel, dim3(1), dim3(1024), 0, s, G, (int)n, ld, Lbuf, k, kb, (int)(ke - kb),
+                         work, piv);
+    } else {
+      for (int64_t kk = kb; kk < ke; ++kk)
+        hipLaunchKernelGGL(pchol_step_kernel<false>, grid, dim3(256), (size_t)PB * 8, s, a, kk, kb);
     }
     if (ke < k) {   // G -= L[:, kb:ke] L[:, kb:ke]^T
       Gemm g;
@@ -251,6 +371,16 @@ hipError_t pivoted_cholesky(double* G, int64_t n, int64_t ld, int64_t k, int64_t
       if (e != hipSuccess) return e;
     }
   }
+  return hipGetLastError();
+}
+
+hipError_t pivoted_cholesky_sets(const PcArgs& a, int nsets, int64_t kmax, hipStream_t s) {
+  if (nsets <= 0 || kmax <= 0) return hipSuccess;
+  if (nsets > 65535 || kmax + 2 * a.p > kPcSetsMax) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)a.nbmax, (unsigned)nsets);
+  for (int64_t k = -1; k < kmax; ++k)
+    hipLaunchKernelGGL(pchol_step_kernel<true>, grid, dim3(256), (size_t)(std::max<int64_t>(k, 0) + 2 * a.p) * 8, s, a,
+                       k, (int64_t)0);
   return hipGetLastError();
 }
 

@@ -291,7 +291,7 @@ std::vector<int64_t> select_pivots(rps_context& c, const std::vector<int64_t>& c
   AB.alloc(nc * 2 * p, &tmpb);
   Gram.alloc(nc * nc, &tmpb);
   Lb.alloc(nc * k, &tmpb);
-  diag.alloc(nc + k, &tmpb);
+  diag.alloc(pivoted_cholesky_work(nc), &tmpb);
   hip_check(hipMemcpyAsync(dG.p, G12.data(), G12.size() * 8, hipMemcpyHostToDevice, st), "copy sketch");
   hip_check(hipMemcpyAsync(dcand.p, cand.data(), nc * 8, hipMemcpyHostToDevice, st), "copy candidates");
   hip_check(gather_rows(c.Phi.p, c.Np, dcand.p, nc, nc, c.Np, Phic.p, c.Np, st), "gather");
@@ -317,6 +317,96 @@ std::vector<int64_t> select_pivots(rps_context& c, const std::vector<int64_t>& c
   dpiv.release(nullptr);
   std::vector<int64_t> out(k);
   for (int64_t i = 0; i < k; ++i) out[i] = cand[piv[i]];
+  return out;
+}
+
+// The per-atom pivots of the selection (Sec. 4.3): K[I] candidates of every set kappa[I],
+// from sketches drawn on streams 2 + 2I and 3 + 2I.  The sets are independent, so a step of
+// all of them is one launch, and their Gram matrices are not formed.  Sets are taken
+// together while their sketch products and factors stay within 256 MB.
+std::vector<std::vector<int64_t>> select_atom_pivots(rps_context& c, const std::vector<std::vector<int64_t>>& kappa,
+                                                     const std::vector<int64_t>& K, uint64_t seed, hipStream_t st) {
+  const int64_t N = c.nbas, natom = (int64_t)kappa.size();
+  constexpr int64_t kDoubles = 32ll << 20;
+  std::vector<std::vector<int64_t>> out(natom);
+  auto sketch = [&](int64_t k) { return std::min<int64_t>((int64_t)ceil(sqrt((double)k)) + kOversample, N); };
+  for (int64_t i0 = 0; i0 < natom;) {
+    int64_t rows = 0, kmax = 0, pmax = 0, nmax = 0, npiv = 0, i1 = i0;
+    for (; i1 < natom; ++i1) {
+      const int64_t n = (int64_t)kappa[i1].size(), r = rows + n, k = std::max(kmax, K[i1]);
+      const int64_t p = std::max(pmax, n ? sketch(K[i1]) : 0);
+      if (i1 > i0 && r * (k + 2 * p) > kDoubles) break;
+      rows = r; kmax = k; pmax = p;
+      nmax = std::max(nmax, n);
+      npiv += K[i1];
+    }
+    if (npiv == 0) {
+      i0 = i1;
+      continue;
+    }
+    int64_t tmpb = 0;
+    DBuf<double> dG, Phic, AB, L, work;
+    DBuf<int64_t> dcand, dpiv;
+    DBuf<PcSet> dsets;
+    const int64_t nbmax = (nmax + 255) / 256, nsets = i1 - i0;
+    dG.alloc(nsets * c.Np * 2 * pmax, &tmpb);
+    Phic.alloc(nmax * c.Np, &tmpb);
+    AB.alloc(2 * pmax * rows, &tmpb);
+    L.alloc(rows * kmax, &tmpb);
+    work.alloc(rows + 4 * nsets * nbmax, &tmpb);
+    dcand.alloc(rows, &tmpb);
+    dpiv.alloc(npiv, &tmpb);
+    dsets.alloc(nsets, &tmpb);
+    std::vector<double> G12((size_t)(nsets * c.Np * 2 * pmax), 0.0);
+    std::vector<int64_t> cand;
+    std::vector<PcSet> sets;
+    cand.reserve(rows);
+    int64_t pofs = 0;
+    for (int64_t I = i0; I < i1; ++I) {
+      sets.push_back(PcSet{(int64_t)cand.size(), (int64_t)kappa[I].size(), K[I], pofs});
+      pofs += K[I];
+      cand.insert(cand.end(), kappa[I].begin(), kappa[I].end());
+      if (kappa[I].empty()) continue;
+      const int64_t p = sketch(K[I]);
+      std::vector<double> G1 = sketch_normal(N, p, seed, (uint32_t)(2 + 2 * I));
+      std::vector<double> G2 = sketch_normal(N, p, seed, (uint32_t)(3 + 2 * I));
+      orthonormalize_columns(G1, N, p);
+      orthonormalize_columns(G2, N, p);
+      double* g = G12.data() + (I - i0) * c.Np * 2 * pmax;     // columns past p stay zero
+      for (int64_t r = 0; r < N; ++r)
+        for (int64_t q = 0; q < p; ++q) {
+          g[r * 2 * pmax + q] = G1[r * p + q];
+          g[r * 2 * pmax + pmax + q] = G2[r * p + q];
+        }
+    }
+    hip_check(hipMemcpyAsync(dG.p, G12.data(), G12.size() * 8, hipMemcpyHostToDevice, st), "copy sketch");
+    hip_check(hipMemcpyAsync(dcand.p, cand.data(), rows * 8, hipMemcpyHostToDevice, st), "copy candidates");
+    hip_check(hipMemcpyAsync(dsets.p, sets.data(), nsets * sizeof(PcSet), hipMemcpyHostToDevice, st), "copy sets");
+    for (int64_t I = i0; I < i1; ++I) {
+      const PcSet& it = sets[I - i0];
+      if (it.n == 0) continue;
+      hip_check(gather_rows(c.Phi.p, c.Np, dcand.p + it.row0, it.n, it.n, c.Np, Phic.p, c.Np, st), "gather");
+      Gemm g;                                  // [A | B]^T = [G1 | G2]^T Phi_c^T
+      g.M = 2 * pmax; g.N = it.n; g.K = c.Np;
+      g.A = dG.p + (I - i0) * c.Np * 2 * pmax; g.lda = 2 * pmax; g.transA = true;
+      g.B = Phic.p; g.ldb = c.Np; g.transB = true; g.C = AB.p + it.row0; g.ldc = rows;
+      hip_check(gemm_f64(g, st), "sketch product");
+    }
+    PcArgs a{};
+    a.sets = dsets.p; a.nbmax = nbmax;
+    a.AB = AB.p; a.ldab = rows; a.p = (int)pmax;
+    a.L = L.p; a.ldl = kmax; a.diag = work.p;
+    a.bv = work.p + rows;
+    a.bi = reinterpret_cast<int32_t*>(work.p + rows + 2 * nsets * nbmax);
+    a.piv = dpiv.p;
+    hip_check(pivoted_cholesky_sets(a, (int)nsets, kmax, st), "pivoted cholesky");
+    std::vector<int64_t> piv(npiv);
+    hip_check(hipMemcpyAsync(piv.data(), dpiv.p, npiv * 8, hipMemcpyDeviceToHost, st), "copy pivots");
+    hip_check(hipStreamSynchronize(st), "sync");
+    for (int64_t I = i0; I < i1; ++I)
+      for (int64_t t = 0; t < K[I]; ++t) out[I].push_back(kappa[I][piv[sets[I - i0].pofs + t]]);
+    i0 = i1;
+  }
   return out;
 }
 
@@ -454,13 +544,22 @@ void select_points(rps_context& c, int mode, uint64_t seed, const std::vector<in
   std::vector<std::vector<int64_t>> kappa(c.natom);
   for (int64_t R = 0; R < c.ng; ++R) kappa[c.owner_host[R]].push_back(R);
   const double cfac = (double)c.naux / (double)c.nbas;
-  std::vector<int64_t> Rh;
+  std::vector<int64_t> Rh, KI(c.natom, 0);
+  int64_t kmax = 0;
   for (int I = 0; I < c.natom; ++I) {
     if (kappa[I].empty()) continue;
-    int64_t KI = (int64_t)ceil(cfac * nfunc_atom[I] - 1e-9) + 10;
-    KI = std::min<int64_t>(KI, (int64_t)kappa[I].size());
-    std::vector<int64_t> pi = select_pivots(c, kappa[I], KI, seed, 2 + 2 * I, 3 + 2 * I, st);
-    Rh.insert(Rh.end(), pi.begin(), pi.end());
+    KI[I] = std::min<int64_t>((int64_t)ceil(cfac * nfunc_atom[I] - 1e-9) + 10, (int64_t)kappa[I].size());
+    kmax = std::max(kmax, KI[I]);
+  }
+  const int64_t psk = (int64_t)ceil(sqrt((double)kmax)) + kOversample;
+  if (kmax + 2 * psk <= kPcSetsMax) {
+    for (auto& pi : select_atom_pivots(c, kappa, KI, seed, st)) Rh.insert(Rh.end(), pi.begin(), pi.end());
+  } else {     // a pivot row past the step kernel's LDS: one atom at a time on its Gram matrix
+    for (int I = 0; I < c.natom; ++I) {
+      if (kappa[I].empty()) continue;
+      std::vector<int64_t> pi = select_pivots(c, kappa[I], KI[I], seed, 2 + 2 * I, 3 + 2 * I, st);
+      Rh.insert(Rh.end(), pi.begin(), pi.end());
+    }
   }
   if ((int64_t)Rh.size() < c.naux) {
     global();

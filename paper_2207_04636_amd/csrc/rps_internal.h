@@ -142,9 +142,31 @@ hipError_t tri_solve_lower(const double* L, int64_t n, int64_t ldl, double* B, i
 // Blocked pivoted Cholesky on an explicit symmetric Gram matrix G (n x n, ld),
 // destroyed.  Writes the first k pivots (indices into 0..n-1, argmax of the
 // updated diagonal, ties to the lowest index) to piv (device int64[k]).
-// Work buffers: Lbuf (n x k doubles), diag (n + k doubles).
+// Work buffers: Lbuf (n x k doubles), work (pivoted_cholesky_work(n) doubles).
 hipError_t pivoted_cholesky(double* G, int64_t n, int64_t ld, int64_t k, int64_t* piv,
-                            double* Lbuf, double* diag, hipStream_t s);
+                            double* Lbuf, double* work, hipStream_t s);
+int64_t pivoted_cholesky_work(int64_t n);
+// The same pivots for many sets at once, each on the Gram matrix (A A^T) o (B B^T) of its
+// sketch products, which is not formed.  Set i holds n candidates (columns row0 .. row0 + n
+// of AB) and takes k <= n pivots, written to piv[pofs ..] as indices into the set.
+struct PcSet {
+  int64_t row0, n, k, pofs;
+};
+struct PcArgs {
+  const PcSet* sets;            // device array (pivoted_cholesky_sets)
+  int64_t n, k;                 // the one set of pivoted_cholesky
+  int64_t nbmax;                // 256-candidate blocks of the largest set
+  const double* AB;             // [2 p][ldab]: rows 0..p-1 are A^T, rows p..2p-1 B^T
+  int64_t ldab;
+  int p;
+  const double* G; int64_t ld;  // pivoted_cholesky: the Gram matrix
+  double* L; int64_t ldl;       // factor: row-major (pitch ldl), or per set [k][n] from row0 * ldl
+  double* diag;                 // residual diagonal, one per candidate
+  double* bv; int32_t* bi;      // block maxima, two halves of [sets][nbmax]
+  int64_t* piv;
+};
+constexpr int64_t kPcSetsMax = 7680;   // pivots + 2 p of pivoted_cholesky_sets (60 KB of LDS)
+hipError_t pivoted_cholesky_sets(const PcArgs& a, int nsets, int64_t kmax, hipStream_t s);
 
 // ---------------------------------------------------------------- Poisson solve
 // In place V <- Vc V for nrows real rows (split-complex pairs of rows, nrows even)

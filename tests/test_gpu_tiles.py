@@ -62,3 +62,62 @@ def test_coulomb_lower_tiles(lib, nfunc, mesh, monkeypatch):
     assert np.abs(J - Jref).max() < 1e-11 * np.abs(Jref).max()
     assert abs(E - Eref) < 1e-11 * abs(Eref)
     assert np.array_equal(J, J.T)
+
+
+# ---- point selection: pivots of the sketched Gram matrices
+def _greedy(Phi_c, K, seed, streams):
+    """Pivots of the Gram matrix of the sketched pair products, and the residual of each."""
+    from scipy.linalg import lapack
+    from oracle import isdf
+    p = isdf.sketch_size(min(K, len(Phi_c)), Phi_c.shape[1])
+    A, B = (Phi_c @ isdf.orthonormal_sketch(Phi_c.shape[1], p, seed, s) for s in streams)
+    L, piv, _, _ = lapack.dpstrf((A @ A.T) * (B @ B.T), lower=1, tol=0.0)
+    return piv[:K] - 1, np.diag(L)[:K] ** 2
+
+
+def _checked(got, want, resid):
+    """Equal pivots while the residual stands well above rounding: an element of the updated
+    diagonal carries about k eps of the first pivot (1e-13 of it), so two candidates can
+    only change places when they are within 1e-7 of each other there."""
+    k = int(np.argmax(resid < 1e-6 * resid[0])) if (resid < 1e-6 * resid[0]).any() else len(resid)
+    assert k > 8 and np.array_equal(got[:k], want[:k])
+    return k
+
+
+@pytest.mark.parametrize("mesh,naux", [
+    ((8, 8, 8), 31),          # one panel of pivots, less than a panel wide
+    ((16, 8, 8), 33),         # 1024 candidates: the largest set of the one-workgroup panel
+    ((5, 5, 41), 64),         # 1025 candidates: one launch per pivot
+    ((13, 12, 11), 65),
+])
+def test_global_selection_pivots(lib, mesh, naux):
+    w = dataclasses.replace(ri.tiny_cell(), mesh=np.asarray(mesh), naux=naux)
+    _say(f"case: global selection, {w.ngrid} candidates, {naux} pivots")
+    want, resid = _greedy(basis.eval_basis(w), naux, w.sketch_seed(), (0, 1))
+    with lib.Context.from_workload(w, seed=w.sketch_seed(), select=lib.SELECT_GLOBAL) as ctx:
+        got = ctx.points()
+    _say(f"  {_checked(got, want, resid)} of {naux} pivots compared")
+
+
+@pytest.mark.parametrize("w", [
+    dataclasses.replace(ri.tiny_cell(), mesh=np.array([12, 11, 10])),            # 2 sets of about 660
+    ri.diamond_supercell((1, 1, 1), (16, 15, 14), 2, c=3.0, cid=71),             # 8 sets of about 420
+    ri.diamond_supercell((2, 1, 1), (24, 13, 13), 2, c=5.2, cid=72),             # a union of more than 1024
+], ids=["2-atoms", "8-atoms", "16-atoms"])
+def test_voronoi_selection_pivots(lib, w):
+    """The sets of all atoms at once without their Gram matrices, then their union."""
+    seed, Phi = w.sketch_seed(), basis.eval_basis(w)
+    owner, Rh = basis.voronoi(w), []
+    for I, NI in enumerate(w.funcs_per_atom()):
+        kap = np.flatnonzero(owner == I)
+        piv, resid = _greedy(Phi[kap], min(len(kap), int(np.ceil(w.naux / w.nbas * NI - 1e-9)) + 10), seed,
+                             (2 + 2 * I, 3 + 2 * I))
+        assert (resid > 1e-12 * resid[0]).all()       # the reference itself is well above rounding
+        Rh.append(kap[piv])
+    Rh = np.concatenate(Rh)
+    _say(f"case: Voronoi selection, {w.natom} atoms, {len(Rh)} candidates, {w.naux} points")
+    want, resid = _greedy(Phi[Rh], w.naux, seed, (0, 1))
+    with lib.Context.from_workload(w, seed=seed) as ctx:
+        got = ctx.points()
+        assert ctx.info()["n_candidates"] == len(Rh)
+    _say(f"  {_checked(got, Rh[want], resid)} of {w.naux} points compared")
