@@ -237,8 +237,10 @@ rps_status rps_build_exchange_variant(rps_context *ctx, int32_t variant, int32_t
  * at the end of an SCF run (Sec. 3.3).  nocc, C as for
  * rps_build_exchange_occRI; K: [N][N] FP64 output (host or device per flags).
  * Works on any context (FP64 products; the precision form reads its FP32 V).
- * Allocates its temporaries for the call (about 2 GB plus 8 N_aux^2 bytes)
- * and synchronises hip_stream before returning.
+ * Its temporaries (256 MB or 1 KB per grid point, whichever is more, with 8 N_aux N
+ * and 8 N_g n bytes; at least 8 N_aux^2) stay with the context for the next call
+ * when they are at most 1 GB, and are released before returning otherwise.
+ * Synchronises hip_stream before returning.
  * Errors: RPS_ERR_ARG, RPS_ERR_STATE, RPS_ERR_NOMEM, RPS_ERR_DEVICE.
  */
 rps_status rps_build_exchange_full(rps_context *ctx, int32_t nocc, const double *C, double *K,

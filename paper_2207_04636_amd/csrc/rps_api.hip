@@ -121,6 +121,9 @@ struct rps_context {
   bool jws_small = false;
   int64_t jchunk = 0;
   DBuf<double> jCp, jCin, jU, jrho, jwork, jpart, jJ;
+  // full exchange matrix: workspace, kept between calls while it is small (build_full_impl)
+  DBuf<double> fC, fCp, fU, fUg, fA, fO, fT, fK3, fK, fwork;
+  int64_t fbytes = 0;
   // Madelung term: S = dV Phi^T Phi (kept once formed) and workspace
   DBuf<double> Sdev, mCp, mSC, mpart;
   // autotuned launch parameters (0: built-in default)
@@ -172,6 +175,8 @@ struct rps_context {
     gM1T32.release(nullptr);
     gA32.release(nullptr);
     ecount.release(nullptr);
+    DBuf<double>* fb[] = {&fC, &fCp, &fU, &fUg, &fA, &fO, &fT, &fK3, &fK, &fwork};
+    for (auto* b : fb) b->release(nullptr);
     DBuf<double>* jb[] = {&kern, &jCp, &jCin, &jU, &jrho, &jwork, &jpart, &jJ, &Sdev, &mCp, &mSC, &mpart};
     for (auto* b : jb) b->release(nullptr);
     V32.release(nullptr);
@@ -213,6 +218,8 @@ struct StageLog {
 constexpr int64_t kSplitWork = 64ll << 20;   // doubles of split-K partials (512 MB)
 constexpr int kEnergyBlocks = 256;            // most blocks the energy dot products are split over
 constexpr int kStreamMaxNp = 128;             // largest padded n of the streaming form
+constexpr int64_t kFullChunk = 32ll << 20;    // doubles of A per chunk of the full exchange matrix (256 MB)
+constexpr int64_t kFullKeep = 1ll << 30;      // its workspace stays with the context up to 1 GB (see build_full_impl)
 constexpr int64_t kChiPanel = 32768;          // grid columns per fitting-function panel (set-up)
 constexpr int64_t kWPanel = 1024;             // rows per panel of the V and W stage (set-up)
 constexpr int kStreamBlocks = 512;            // workgroups aimed at per streaming launch (default)
@@ -832,21 +839,34 @@ void setup_impl(rps_context& c, const rps_cell* cell, const rps_basis* b, int64_
       P = std::min(P, c.nauxp);                          // a multiple of 64 (rows in pairs)
       DBuf<double> X, work;
       X.alloc(P * c.ngp, &tmpb);
-      work.alloc(kSplitWork, &tmpb);
+      // part 0: W[a, a] = V[a] chi[a]^T; part 1: W[a, after a] = V[a] chi[after a]^T
+      auto block_row = [&](int64_t a0, int part) {
+        const int64_t pa = std::min(P, c.nauxp - a0);
+        double* Va = c.V.p + a0 * c.ngp;
+        Gemm g;
+        g.M = pa; g.K = c.ngp;
+        g.N = (part == 0) ? pa : c.nauxp - a0 - pa;
+        g.A = Va; g.lda = c.ngp;
+        g.B = (part == 0) ? X.p : Va + pa * c.ngp; g.ldb = c.ngp; g.transB = true;
+        g.C = c.W.p + a0 * c.nauxp + a0 + ((part == 0) ? 0 : pa); g.ldc = c.nauxp;
+        if (g.N > 0) gemm_plan(g, kSplitWork);
+        return g;
+      };
+      int64_t wk = 1;      // split partials: as many as the plans use
+      for (int64_t a0 = 0; a0 < c.nauxp; a0 += P)
+        for (int part = 0; part < 2; ++part) {
+          const Gemm g = block_row(a0, part);
+          if (g.N > 0 && g.splitk > 1) wk = std::max(wk, g.splitk * g.M * g.N);
+        }
+      work.alloc(wk, &tmpb);
       for (int64_t a0 = 0; a0 < c.nauxp; a0 += P) {
         const int64_t pa = std::min(P, c.nauxp - a0);
         double* Va = c.V.p + a0 * c.ngp;
         hip_check(hipMemcpyAsync(X.p, Va, (size_t)(pa * c.ngp) * 8, hipMemcpyDeviceToDevice, st), "chi panel");
         hip_check(poisson_rows(Va, pa, c.ngp, c.mesh, dkern, st), "poisson");
         for (int part = 0; part < 2; ++part) {
-          Gemm g;   // part 0: W[a, a] = V[a] chi[a]^T; part 1: W[a, after a] = V[a] chi[after a]^T
-          g.M = pa; g.K = c.ngp;
-          g.N = (part == 0) ? pa : c.nauxp - a0 - pa;
+          Gemm g = block_row(a0, part);
           if (g.N <= 0) continue;
-          g.A = Va; g.lda = c.ngp;
-          g.B = (part == 0) ? X.p : Va + pa * c.ngp; g.ldb = c.ngp; g.transB = true;
-          g.C = c.W.p + a0 * c.nauxp + a0 + ((part == 0) ? 0 : pa); g.ldc = c.nauxp;
-          gemm_plan(g, kSplitWork);
           g.work = work.p;
           hip_check(gemm_f64(g, st), "W block row");
         }
@@ -1674,79 +1694,95 @@ void build_full_impl(rps_context& c, int32_t nocc, const double* C, double* K, i
   if (!C || !K) fail(RPS_ERR_ARG, "C and K must not be NULL");
   if (flags != RPS_PTRS_HOST && flags != RPS_PTRS_DEVICE) fail(RPS_ERR_ARG, "flags must be RPS_PTRS_HOST or RPS_PTRS_DEVICE");
   const bool dev = (flags == RPS_PTRS_DEVICE);
-  const int64_t np = round_up(nocc, 16), Np = c.Np, G = c.nauxp, R = c.ngp;
-  int64_t tmp = 0;
-  DBuf<double> Cd, Cp, U, Ug, A, O, T, B, BP, K3, Kd, work;
+  const int64_t np = round_up(nocc, 16), Np = c.Np, G = c.nauxp, R = c.ngp, N = c.nbas;
+  // A in chunks of g rows, 256 MB each (the size of the last-level cache, which then serves
+  // much of the second product's reads), but whole 128-row output tiles
+  const int64_t gc = std::min<int64_t>(G, std::max<int64_t>(128, kFullChunk / R / 128 * 128));
+  struct Release {     // a workspace above kFullKeep goes back at the end of the call
+    rps_context& c;
+    ~Release() {
+      if (c.fbytes <= kFullKeep) return;
+      DBuf<double>* all[] = {&c.fC, &c.fCp, &c.fU, &c.fUg, &c.fA, &c.fO, &c.fT, &c.fK3, &c.fK, &c.fwork};
+      for (auto* b : all) b->release(&c.bytes);
+      c.fbytes = 0;
+    }
+  } release{c};
+  auto need = [&](DBuf<double>& b, int64_t n) {
+    if (b.n >= n) return;
+    const int64_t before = c.bytes;
+    b.alloc(n, &c.bytes);
+    c.fbytes += c.bytes - before;
+  };
+  std::vector<Gemm> split;      // the products that may split K, planned before anything runs
+  auto plan = [&](int64_t M, int64_t Nn, int64_t K, const double* A, int64_t lda, bool tA, const double* B, int64_t ldb,
+                  double* C_, int64_t ldc) {
+    Gemm g;
+    g.M = M; g.N = Nn; g.K = K;
+    g.A = A; g.lda = lda; g.transA = tA; g.B = B; g.ldb = ldb; g.C = C_; g.ldc = ldc;
+    gemm_plan(g, kSplitWork);
+    return g;
+  };
+  need(c.fCp, Np * np);
+  need(c.fU, R * np);
+  need(c.fUg, G * np);
+  need(c.fA, std::max(gc * R, G * G));
+  need(c.fO, G * Np);
+  need(c.fT, Np * Np);
+  need(c.fK3, Np * Np);
+  if (!dev) {
+    need(c.fC, N * nocc);
+    need(c.fK, N * N);
+  }
+  for (int64_t g0 = 0; g0 < G; g0 += gc)      // O[c] = A_c Phi
+    split.push_back(plan(std::min(gc, G - g0), Np, R, c.fA.p, R, false, c.Phi.p, Np, c.fO.p + g0 * Np, Np));
+  const size_t nchunk = split.size();
+  split.push_back(plan(Np, Np, G, c.Phig.p, Np, true, c.fO.p, Np, c.fT.p, Np));    // T = Phi_g^T O
+  split.push_back(plan(G, Np, G, c.fA.p, G, false, c.Phig.p, Np, c.fO.p, Np));     // B Phi_g (in O's place)
+  split.push_back(plan(Np, Np, G, c.Phig.p, Np, true, c.fO.p, Np, c.fK3.p, Np));   // K3 = Phi_g^T (B Phi_g)
+  int64_t wk = 1;
+  for (const Gemm& g : split)
+    if (g.splitk > 1) wk = std::max(wk, g.splitk * g.M * g.N);
+  need(c.fwork, wk);
+  for (Gemm& g : split) g.work = c.fwork.p;
+
   const double* Csrc = C;
   if (!dev) {
-    Cd.alloc(c.nbas * nocc, &tmp);
-    hip_check(hipMemcpyAsync(Cd.p, C, (size_t)c.nbas * nocc * 8, hipMemcpyHostToDevice, st), "copy C");
-    Csrc = Cd.p;
+    hip_check(hipMemcpyAsync(c.fC.p, C, (size_t)N * nocc * 8, hipMemcpyHostToDevice, st), "copy C");
+    Csrc = c.fC.p;
   }
-  const int64_t gc = std::min<int64_t>(G, std::max<int64_t>(64, (2000000000ll / 8) / R / 64 * 64));
-  Cp.alloc(Np * np, &tmp);
-  U.alloc(R * np, &tmp);
-  Ug.alloc(G * np, &tmp);
-  A.alloc(std::max(gc * R, G * G), &tmp);
-  O.alloc(G * Np, &tmp);
-  T.alloc(Np * Np, &tmp);
-  B.alloc(G * G, &tmp);
-  BP.alloc(G * Np, &tmp);
-  K3.alloc(Np * Np, &tmp);
-  work.alloc(kSplitWork, &tmp);
-  if (!dev) Kd.alloc(c.nbas * c.nbas, &tmp);
-  auto run = [&](Gemm g, const char* what, bool split) {
-    if (split && g.epi == EPI_AXPBY) {
-      g.splitk = gemm_splitk_for(g.M, g.N, g.K, kSplitWork);
-      g.work = work.p;
-    }
-    hip_check(gemm_f64(g, st), what);
-  };
-  hip_check(pack_matrix(Csrc, c.nbas, nocc, nocc, Cp.p, Np, np, st), "pack C");
+  hip_check(pack_matrix(Csrc, N, nocc, nocc, c.fCp.p, Np, np, st), "pack C");
   {
     Gemm g;   // U = Phi C
     g.M = R; g.N = np; g.K = Np;
-    g.A = c.Phi.p; g.lda = Np; g.B = Cp.p; g.ldb = np; g.C = U.p; g.ldc = np;
-    run(g, "U", false);
+    g.A = c.Phi.p; g.lda = Np; g.B = c.fCp.p; g.ldb = np; g.C = c.fU.p; g.ldc = np;
+    hip_check(gemm_f64(g, st), "U");
   }
-  hip_check(gather_rows(U.p, np, c.dpoints.p, c.naux, G, np, Ug.p, np, st), "U_g");
-  for (int64_t g0 = 0; g0 < G; g0 += gc) {
-    const int64_t m = std::min(gc, G - g0);
+  hip_check(gather_rows(c.fU.p, np, c.dpoints.p, c.naux, G, np, c.fUg.p, np, st), "U_g");
+  for (size_t q = 0; q < nchunk; ++q) {
+    const int64_t g0 = (int64_t)q * gc;
     Gemm a;   // A_c = V_c o (U_g[c] U^T)
-    a.M = m; a.N = R; a.K = np;
-    a.A = Ug.p + g0 * np; a.lda = np; a.B = U.p; a.ldb = np; a.transB = true;
-    a.C = A.p; a.ldc = R; a.epi = EPI_HADAMARD_SRC; a.ldd = R;
+    a.M = split[q].M; a.N = R; a.K = np;
+    a.A = c.fUg.p + g0 * np; a.lda = np; a.B = c.fU.p; a.ldb = np; a.transB = true;
+    a.C = c.fA.p; a.ldc = R; a.epi = EPI_HADAMARD_SRC; a.ldd = R;
     if (c.V.p) a.D = c.V.p + g0 * R;
     else a.D32 = c.V32.p + g0 * R;
-    run(a, "A chunk", false);
-    Gemm o;   // O[c] = A_c Phi
-    o.M = m; o.N = Np; o.K = R;
-    o.A = A.p; o.lda = R; o.B = c.Phi.p; o.ldb = Np; o.C = O.p + g0 * Np; o.ldc = Np;
-    run(o, "A Phi", true);
+    hip_check(gemm_f64(a, st), "A chunk");
+    hip_check(gemm_f64(split[q], st), "A Phi");
   }
+  hip_check(gemm_f64(split[nchunk], st), "Phi_g^T (A Phi)");
   {
-    Gemm t;   // T = Phi_g^T O
-    t.M = Np; t.N = Np; t.K = G;
-    t.A = c.Phig.p; t.lda = Np; t.transA = true; t.B = O.p; t.ldb = Np; t.C = T.p; t.ldc = Np;
-    run(t, "Phi_g^T (A Phi)", true);
     Gemm b;   // B = W o (U_g U_g^T)
     b.M = G; b.N = G; b.K = np;
-    b.A = Ug.p; b.lda = np; b.B = Ug.p; b.ldb = np; b.transB = true;
-    b.C = B.p; b.ldc = G; b.epi = EPI_HADAMARD_SRC; b.D = c.W.p; b.ldd = G;
-    run(b, "B", false);
-    Gemm bp;  // B Phi_g
-    bp.M = G; bp.N = Np; bp.K = G;
-    bp.A = B.p; bp.lda = G; bp.B = c.Phig.p; bp.ldb = Np; bp.C = BP.p; bp.ldc = Np;
-    run(bp, "B Phi_g", true);
-    Gemm k3;  // K3 = Phi_g^T (B Phi_g)
-    k3.M = Np; k3.N = Np; k3.K = G;
-    k3.A = c.Phig.p; k3.lda = Np; k3.transA = true; k3.B = BP.p; k3.ldb = Np; k3.C = K3.p; k3.ldc = Np;
-    run(k3, "Phi_g^T (B Phi_g)", true);
+    b.A = c.fUg.p; b.lda = np; b.B = c.fUg.p; b.ldb = np; b.transB = true;
+    b.C = c.fA.p; b.ldc = G; b.epi = EPI_HADAMARD_SRC; b.D = c.W.p; b.ldd = G;
+    hip_check(gemm_f64(b, st), "B");
   }
-  double* Kout = dev ? K : Kd.p;
-  hip_check(full_combine(T.p, K3.p, Np, c.nbas, c.dV, Kout, st), "combine");
-  if (!dev) hip_check(hipMemcpyAsync(K, Kd.p, (size_t)c.nbas * c.nbas * 8, hipMemcpyDeviceToHost, st), "copy K");
-  hip_check(hipStreamSynchronize(st), "sync");   // temporaries are released on return
+  hip_check(gemm_f64(split[nchunk + 1], st), "B Phi_g");
+  hip_check(gemm_f64(split[nchunk + 2], st), "Phi_g^T (B Phi_g)");
+  double* Kout = dev ? K : c.fK.p;
+  hip_check(full_combine(c.fT.p, c.fK3.p, Np, N, c.dV, Kout, st), "combine");
+  if (!dev) hip_check(hipMemcpyAsync(K, c.fK.p, (size_t)N * N * 8, hipMemcpyDeviceToHost, st), "copy K");
+  hip_check(hipStreamSynchronize(st), "sync");   // as documented; the workspace may be released now
 }
 
 // ------------------------------------------------------------------ Coulomb matrix

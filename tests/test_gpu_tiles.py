@@ -121,3 +121,24 @@ def test_voronoi_selection_pivots(lib, w):
         got = ctx.points()
         assert ctx.info()["n_candidates"] == len(Rh)
     _say(f"  {_checked(got, Rh[want], resid)} of {w.naux} points compared")
+
+
+# ---- full exchange matrix: A in chunks of interpolation points, workspace kept between calls
+def test_full_exchange_chunks_and_workspace(lib):
+    """K_full C = K_occ (both FP64, so within rounding of sums of N_g and N_aux terms) on a
+    cell whose A takes two chunks (256 and 160 points), for several n in turn on one context
+    (the kept workspace grows and is reused), and for the FP32 context's stored V."""
+    w = ri.diamond_cell(4.0)
+    with lib.Context.from_workload(w, seed=w.sketch_seed()) as ctx:
+        S, pts = ctx.overlap(), ctx.points()
+        for nocc in (3, 16, 33, 16):
+            C = ri.lowdin(np.random.default_rng(nocc).standard_normal((w.nbas, nocc)), S)
+            _say(f"case: full exchange, config 2 c=4, n={nocc}")
+            Kf, (K, _) = ctx.build_full(C), ctx.build(C)
+            assert np.array_equal(Kf, ctx.build_full(C))
+            assert np.abs(Kf - Kf.T).max() < 1e-11 * np.abs(Kf).max()
+            assert np.abs(Kf @ C - K).max() < 1e-10 * np.abs(K).max()
+    with lib.Context.from_workload(w, points=pts, precision=lib.PREC_FP32) as ctx:
+        _say("case: full exchange, FP32 context")
+        K32 = ctx.build_full(C)
+    assert np.abs(K32 - Kf).max() < 1e-6 * np.abs(Kf).max()     # V rounded to 24 bits
