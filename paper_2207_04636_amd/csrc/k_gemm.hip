@@ -1133,18 +1133,56 @@ __global__ __launch_bounds__(256, 2) void gemm_grouped_kernel(Gemm base, const G
   gemm_big_body<TM, TN, TA, TB, KS>(g, m0, n0, 0);
 }
 
-// C = alpha * sum_z work[z] + beta * C (fixed order over z)
-__global__ void splitk_reduce_kernel(const double* __restrict__ work, int splitk, int64_t M, int64_t N,
-                                     double* __restrict__ C, int64_t ldc, double beta, float* __restrict__ Cf,
-                                     int64_t ldcf) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= M * N) return;
+// C = sum_z work[z] + beta * C (fixed order over z).  ZL lanes share an output: lane q
+// sums z = q, q + ZL, ... with four loads in flight, then the lanes are added in order.
+// One lane per output left a product of few outputs and many splits (209 x 48 of K =
+// 135040, 256 splits) with 40 blocks of long serial sums: 34 us; 16 lanes: 9 us.
+template <int ZL>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const double* __restrict__ work, int splitk, int64_t M,
+                                                           int64_t N, double* __restrict__ C, int64_t ldc,
+                                                           double beta, float* __restrict__ Cf, int64_t ldcf) {
+  constexpr int XL = 256 / ZL;
+  __shared__ double red[ZL][XL + 1];
+  const int x = threadIdx.x % XL, q = threadIdx.x / XL;
+  const int64_t t = (int64_t)blockIdx.x * XL + x, cnt = M * N;
   double s = 0.0;
-  for (int z = 0; z < splitk; ++z) s += work[(int64_t)z * M * N + t];
+  if (t < cnt) {
+    int z = q;
+    for (; z + 3 * ZL < splitk; z += 4 * ZL) {
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = work[(int64_t)(z + u * ZL) * cnt + t];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += v[u];
+    }
+    for (; z < splitk; z += ZL) s += work[(int64_t)z * cnt + t];
+  }
+  if constexpr (ZL > 1) {
+    red[q][x] = s;
+    __syncthreads();
+    if (q != 0) return;
+    s = 0.0;
+#pragma unroll
+    for (int k = 0; k < ZL; ++k) s += red[k][x];
+  }
+  if (t >= cnt) return;
   const int64_t m = t / N, n = t % N;
   double* c = C + m * ldc + n;
   *c = (beta == 0.0) ? s : s + beta * *c;
   if (Cf) Cf[m * ldcf + n] = (float)*c;
+}
+
+// Several lanes per output where that is needed to fill the device (fewer outputs than
+// 256 blocks of 256 threads) and the splits are enough to share.
+void launch_splitk_reduce(const double* work, int splitk, int64_t M, int64_t N, double* C, int64_t ldc, double beta,
+                          float* Cf, int64_t ldcf, hipStream_t s) {
+  const int64_t cnt = M * N;
+  if (splitk >= 16 && cnt < 16 * 65536)
+    hipLaunchKernelGGL(splitk_reduce_kernel<16>, dim3((unsigned)((cnt + 15) / 16)), dim3(256), 0, s, work, splitk, M, N,
+                       C, ldc, beta, Cf, ldcf);
+  else
+    hipLaunchKernelGGL(splitk_reduce_kernel<1>, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, work, splitk, M, N,
+                       C, ldc, beta, Cf, ldcf);
 }
 
 template <int TM, int TN>
@@ -1223,9 +1261,7 @@ hipError_t gemm_f64(const Gemm& g0, hipStream_t s) {
     launch_big<4, 4>(g, grid, s);
   }
   if (g.splitk > 1 && !g.keep_partials) {
-    const int64_t cnt = g.M * g.N;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, g.work,
-                       g.splitk, g.M, g.N, g.C, g.ldc, g.beta, g.Cf, g.ldcf);
+    launch_splitk_reduce(g.work, g.splitk, g.M, g.N, g.C, g.ldc, g.beta, g.Cf, g.ldcf, s);
   }
   return hipGetLastError();
 }
@@ -1309,9 +1345,7 @@ hipError_t gemm_f32(const Gemm32& g0, hipStream_t s) {
     else launch32<4, true>(g, grid, s);
   }
   if (g.splitk > 1) {
-    const int64_t cnt = g.M * g.N;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, g.work,
-                       g.splitk, g.M, g.N, g.C, g.ldc, g.beta, g.Cf, g.ldcf);
+    launch_splitk_reduce(g.work, g.splitk, g.M, g.N, g.C, g.ldc, g.beta, g.Cf, g.ldcf, s);
   }
   return hipGetLastError();
 }
@@ -1365,19 +1399,37 @@ hipError_t gemm_f64_grouped(const Gemm& base, const GemmItem* items, int nitems,
   return hipGetLastError();
 }
 
+double direct64_time(int64_t tiles, int64_t K, int64_t z, int64_t outputs) {
+  const double rounds = (double)((tiles * z + 767) / 768);
+  return rounds * (double)((K + z - 1) / z) * (2.0 * 128 * 64 * 768 / 65e12) +
+         (z > 1 ? (double)z * (double)outputs * (16.0 / 4e12) + 5e-6 : 0.0);
+}
+
 void gemm_plan(Gemm& g, int64_t work_cap_doubles) {
   g.tile_n = 0;
   g.splitk = 1;
+  if (g.epi == EPI_AXPBY && g.N > 16 && direct64_ok(g)) {
+    // the LDS-direct kernel: the split count of least estimated time that keeps >= 256 of K
+    const int64_t tiles = direct64_tiles(g.M, g.N, 128, 64, g.lower_only);
+    double best = 1e300;
+    for (int64_t z = 1; z <= 768; ++z) {
+      if (z > 1 && (g.K / z < 256 || z * g.M * g.N > work_cap_doubles)) break;
+      const double t = direct64_time(tiles, g.K, z, g.M * g.N);
+      if (t < best * (1.0 - 1e-9)) {
+        best = t;
+        g.splitk = (int)z;
+      }
+    }
+    return;
+  }
   if (g.epi != EPI_AXPBY || g.kscale || g.N <= 64) {
     g.splitk = gemm_splitk_for(g.M, g.N, g.K, work_cap_doubles);
     return;
   }
-  // the LDS-direct kernel runs 128 x 64 tiles, three workgroups per CU; the
-  // register-staged one 128 x 64 or 128 x 128, two per CU
-  const bool direct = direct64_ok(g);
-  const int64_t slots = direct ? 768 : 512;
+  // the register-staged kernel: 128 x 64 or 128 x 128 tiles, two workgroups per CU
+  const int64_t slots = 512;
   double best = -1.0;
-  for (int bn = direct ? 64 : 128; bn >= 64; bn -= 64) {
+  for (int bn = 128; bn >= 64; bn -= 64) {
     const int64_t padn = (g.N + bn - 1) / bn * bn;
     const int64_t tiles = ((g.M + 127) / 128) * (padn / bn);
     for (int64_t z = 1; z <= 64; ++z) {

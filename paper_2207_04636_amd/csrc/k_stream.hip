@@ -25,6 +25,7 @@
 // of V, rounds X and Y to FP32, accumulates each 32-row tile in FP32 and adds
 // it to FP64 accumulators, so error does not grow with N_g.  The split-BF16
 // form is a separate kernel below.
+#include <algorithm>
 #include <type_traits>
 
 #include "mfma.h"
@@ -210,7 +211,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int64_t bx, int
   }
 
   if (!xvalid) return;
-  double* out = a.out + (by * a.nx) * a.np;
+  double* out = a.out + (by * a.nxo - a.xoff) * a.np;
 #pragma unroll
   for (int cb = 0; cb < NC; ++cb)
 #pragma unroll
@@ -224,10 +225,32 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, int64_t bx, int
 }
 
 
+// Work of a launch: the first a.xfull x blocks stream all of y and write their rows of
+// a.out; the blocks after them (the tail) are cut into a.tsplit pieces of a.ysplit each,
+// x fastest, whose partials go to a.part.  One grid, the whole blocks first, so that the
+// pieces fill the last round of workgroups (see stream_plan_tail).
+__device__ __forceinline__ void stream_work(StreamArgs& a, int64_t& bx, int64_t& by, int rows) {
+  const int64_t i = blockIdx.x;
+  bx = i;
+  by = 0;
+  if (i < a.xfull) {
+    a.ysplit = a.ny;
+    return;
+  }
+  const int64_t xtail = (a.nx + rows - 1) / rows - a.xfull;
+  bx = a.xfull + (i - a.xfull) % xtail;
+  by = (i - a.xfull) / xtail;
+  a.out = a.part;
+  a.xoff = a.xfull * rows;
+  a.nxo = a.nx - a.xoff;
+}
+
 template <typename TM, int NC, int TRANS, int NW>
 __global__ __launch_bounds__(NW * 64) void stream_kernel(StreamArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  stream_body<TM, NC, TRANS, NW>(a, blockIdx.x, blockIdx.y, smem_raw);
+  int64_t bx, by;
+  stream_work(a, bx, by, 16 * NW);
+  stream_body<TM, NC, TRANS, NW>(a, bx, by, smem_raw);
 }
 
 // Persistent form for the batching form: the work items of one pass class
@@ -512,7 +535,7 @@ __device__ __forceinline__ void bf16x3_body(const StreamArgs& a, int64_t bx, int
   }
 
   if (!xvalid) return;
-  double* out = a.out + (by * a.nx) * a.np;
+  double* out = a.out + (by * a.nxo - a.xoff) * a.np;
 #pragma unroll
   for (int cb = 0; cb < NC; ++cb)
 #pragma unroll
@@ -522,7 +545,9 @@ __device__ __forceinline__ void bf16x3_body(const StreamArgs& a, int64_t bx, int
 template <int NC, int TRANS, int NW>
 __global__ __launch_bounds__(NW * 64) void stream_bf16x3_kernel(StreamArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  bf16x3_body<NC, TRANS, NW>(a, blockIdx.x, blockIdx.y, smem_raw);
+  int64_t bx, by;
+  stream_work(a, bx, by, 16 * NW);
+  bf16x3_body<NC, TRANS, NW>(a, bx, by, smem_raw);
 }
 
 // Persistent split-BF16 form (see stream_queue_kernel).
@@ -545,60 +570,74 @@ __global__ __launch_bounds__(NW * 64) void bf16x3_queue_kernel(const StreamArgs*
   }
 }
 
+template <typename K>
+int resident_blocks(K kern, size_t lds) {
+  int per_cu = 0, dev = 0, cus = 0;
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 512, lds) != hipSuccess || per_cu < 1) per_cu = 1;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    cus = 256;
+  return per_cu * cus;
+}
+
 template <int NC, int TRANS>
-hipError_t launch_bf16x3(const StreamArgs& a, int nsplit, hipStream_t s) {
+hipError_t launch_bf16x3(const StreamArgs& a, hipStream_t s, int* resident) {
   constexpr int NW = 8;
   const size_t lds = Bf16Layout<NC>::LDS_BYTES;
   auto kern = stream_bf16x3_kernel<NC, TRANS, NW>;
+  if (resident) { *resident = resident_blocks(kern, lds); return hipSuccess; }
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  dim3 grid((unsigned)((a.nx + 16 * NW - 1) / (16 * NW)), (unsigned)nsplit);
+  const int64_t tail = (a.nx + 16 * NW - 1) / (16 * NW) - a.xfull;
+  dim3 grid((unsigned)(a.xfull + tail * a.tsplit));
   hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, s, a);
   return hipGetLastError();
 }
 
 template <int TRANS>
-hipError_t dispatch_bf16x3(const StreamArgs& a, int nsplit, hipStream_t s) {
+hipError_t dispatch_bf16x3(const StreamArgs& a, hipStream_t s, int* resident = nullptr) {
   switch (a.np / 16) {
-    case 1: return launch_bf16x3<1, TRANS>(a, nsplit, s);
-    case 2: return launch_bf16x3<2, TRANS>(a, nsplit, s);
-    case 3: return launch_bf16x3<3, TRANS>(a, nsplit, s);
-    case 4: return launch_bf16x3<4, TRANS>(a, nsplit, s);
-    case 5: return launch_bf16x3<5, TRANS>(a, nsplit, s);
-    case 6: return launch_bf16x3<6, TRANS>(a, nsplit, s);
-    case 7: return launch_bf16x3<7, TRANS>(a, nsplit, s);
-    case 8: return launch_bf16x3<8, TRANS>(a, nsplit, s);
+    case 1: return launch_bf16x3<1, TRANS>(a, s, resident);
+    case 2: return launch_bf16x3<2, TRANS>(a, s, resident);
+    case 3: return launch_bf16x3<3, TRANS>(a, s, resident);
+    case 4: return launch_bf16x3<4, TRANS>(a, s, resident);
+    case 5: return launch_bf16x3<5, TRANS>(a, s, resident);
+    case 6: return launch_bf16x3<6, TRANS>(a, s, resident);
+    case 7: return launch_bf16x3<7, TRANS>(a, s, resident);
+    case 8: return launch_bf16x3<8, TRANS>(a, s, resident);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <typename TM, int NC, int TRANS>
-hipError_t launch_stream(const StreamArgs& a, int nsplit, hipStream_t s) {
+hipError_t launch_stream(const StreamArgs& a, hipStream_t s, int* resident) {
   constexpr int NW = 8;
   const size_t lds = (size_t)2 * BY * stream_ldy<TM, NC>() * sizeof(TM);
   auto kern = stream_kernel<TM, NC, TRANS, NW>;
+  if (resident) { *resident = resident_blocks(kern, lds); return hipSuccess; }
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  dim3 grid((unsigned)((a.nx + 16 * NW - 1) / (16 * NW)), (unsigned)nsplit);
+  const int64_t tail = (a.nx + 16 * NW - 1) / (16 * NW) - a.xfull;
+  dim3 grid((unsigned)(a.xfull + tail * a.tsplit));
   hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, s, a);
   return hipGetLastError();
 }
 
 template <typename TM, int TRANS>
-hipError_t dispatch_nc(const StreamArgs& a, int nsplit, hipStream_t s) {
+hipError_t dispatch_nc(const StreamArgs& a, hipStream_t s, int* resident = nullptr) {
   switch (a.np / 16) {
-    case 1: return launch_stream<TM, 1, TRANS>(a, nsplit, s);
-    case 2: return launch_stream<TM, 2, TRANS>(a, nsplit, s);
-    case 3: return launch_stream<TM, 3, TRANS>(a, nsplit, s);
-    case 4: return launch_stream<TM, 4, TRANS>(a, nsplit, s);
-    case 5: return launch_stream<TM, 5, TRANS>(a, nsplit, s);
-    case 6: return launch_stream<TM, 6, TRANS>(a, nsplit, s);
-    case 7: return launch_stream<TM, 7, TRANS>(a, nsplit, s);
-    case 8: return launch_stream<TM, 8, TRANS>(a, nsplit, s);
+    case 1: return launch_stream<TM, 1, TRANS>(a, s, resident);
+    case 2: return launch_stream<TM, 2, TRANS>(a, s, resident);
+    case 3: return launch_stream<TM, 3, TRANS>(a, s, resident);
+    case 4: return launch_stream<TM, 4, TRANS>(a, s, resident);
+    case 5: return launch_stream<TM, 5, TRANS>(a, s, resident);
+    case 6: return launch_stream<TM, 6, TRANS>(a, s, resident);
+    case 7: return launch_stream<TM, 7, TRANS>(a, s, resident);
+    case 8: return launch_stream<TM, 8, TRANS>(a, s, resident);
     default: return hipErrorInvalidValue;
   }
 }
@@ -619,25 +658,45 @@ hipError_t stream_prepare(const StreamArgs& a, int prec, int nsplit, StreamArgs&
   if (nsplit < 1 || prec < 0 || prec > 2) return hipErrorInvalidValue;
   if (prec == 0 ? !a.V : (!a.V32 || !a.Y32)) return hipErrorInvalidValue;
   b = a;
+  if (a.xfull < 0 || a.xfull > stream_xblocks(a.nx) || (a.xfull > 0 && nsplit > 1 && !a.part)) return hipErrorInvalidValue;
   // y rows per split, a multiple of the tile
   const int64_t tiles = a.ny / BY;
   b.ysplit = ((tiles + nsplit - 1) / nsplit) * BY;
+  b.tsplit = nsplit;
+  if (!b.part) b.part = b.out;
+  b.xoff = 0;
+  b.nxo = a.nx;
   return hipSuccess;
+}
+
+// Workgroups of a pass that are resident at once on the current device.
+int stream_resident(int prec, const StreamArgs& a) {
+  int r = 0;
+  if (prec == 2) (void)(a.trans ? dispatch_bf16x3<1>(a, nullptr, &r) : dispatch_bf16x3<0>(a, nullptr, &r));
+  else if (prec == 1) (void)(a.trans ? dispatch_nc<float, 1>(a, nullptr, &r) : dispatch_nc<float, 0>(a, nullptr, &r));
+  else (void)(a.trans ? dispatch_nc<double, 1>(a, nullptr, &r) : dispatch_nc<double, 0>(a, nullptr, &r));
+  return std::max(1, r);
+}
+
+// A pass whose x blocks all stream the whole of y (the M1 pass) ends in a partly empty
+// round: 1055 blocks on 512 resident workgroups ran three rounds for 2.06 rounds of work.
+// Whole rounds stay whole; the blocks of the last round are cut along y into as many
+// pieces as fill it, unless it is nearly full (over 7/8) anyway.
+int stream_plan_tail(int prec, const StreamArgs& a, int64_t part_rows, int64_t* xfull) {
+  const int64_t xb = stream_xblocks(a.nx), slots = stream_resident(prec, a);
+  const int64_t rem = xb % slots;
+  *xfull = xb;
+  if (rem == 0 || rem * 8 > slots * 7) return 1;
+  int64_t sp = std::min(slots / rem, a.ny / (4 * BY));       // at least four tiles per piece
+  sp = std::min(sp, part_rows / (rem * 128));
+  if (sp <= 1) return 1;
+  *xfull = xb - rem;
+  return (int)sp;
 }
 
 int64_t stream_xblocks(int64_t nx) { return (nx + 127) / 128; }
 
 namespace {
-template <typename K>
-int resident_blocks(K kern, size_t lds) {
-  int per_cu = 0, dev = 0, cus = 0;
-  if (lds > 65536) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 512, lds) != hipSuccess || per_cu < 1) per_cu = 1;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    cus = 256;
-  return per_cu * cus;
-}
-
 template <typename TM, int NC, int TRANS>
 hipError_t queue_stream(const StreamArgs* args, const StreamItem* items, int nitems, unsigned* counter, int nblocks,
                         hipStream_t s, int* resident) {
@@ -706,14 +765,14 @@ hipError_t stream_product(const StreamArgs& a, int prec, int nsplit, hipStream_t
   if (pe != hipSuccess) return pe;
   if (prec == 2) {
     if (!a.V32 || !a.Y32) return hipErrorInvalidValue;
-    return a.trans ? dispatch_bf16x3<1>(b, nsplit, s) : dispatch_bf16x3<0>(b, nsplit, s);
+    return a.trans ? dispatch_bf16x3<1>(b, s) : dispatch_bf16x3<0>(b, s);
   }
   if (prec == 1) {
     if (!a.V32 || !a.Y32) return hipErrorInvalidValue;
-    return a.trans ? dispatch_nc<float, 1>(b, nsplit, s) : dispatch_nc<float, 0>(b, nsplit, s);
+    return a.trans ? dispatch_nc<float, 1>(b, s) : dispatch_nc<float, 0>(b, s);
   }
   if (!a.V) return hipErrorInvalidValue;
-  return a.trans ? dispatch_nc<double, 1>(b, nsplit, s) : dispatch_nc<double, 0>(b, nsplit, s);
+  return a.trans ? dispatch_nc<double, 1>(b, s) : dispatch_nc<double, 0>(b, s);
 }
 
 }  // namespace rps

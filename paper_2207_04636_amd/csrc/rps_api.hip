@@ -109,6 +109,8 @@ struct rps_context {
   // general path workspace
   int gws_np = -1;
   int64_t gchunk = 0;
+  int64_t gm1_full = 0;      // streaming form: whole x blocks of the M1 pass, pieces of each other block
+  int gm1_split = 1;
   DBuf<double> gCp, gU, gUg, gA, gSp, gM2, gM1T, gK1, gK3, gY, gwork, epart;
   DBuf<float> gU32, gUg32, gA32;   // precision form of the GEMM form: FP32 operands and A chunk
   DBuf<float> gPhi32, gM1T32;      // and the FP32 operands of K1 = Phi^T M1^T (basis, padded M1^T)
@@ -1121,6 +1123,8 @@ void ensure_sparse_ws(rps_context& c, int np) {
   c.sws_np = np;
 }
 
+StreamArgs pass_m1(const rps_context& c, int np);
+
 void ensure_general(rps_context& c, int np) {
   if (c.sparse) ensure_sparse_ws(c, np);
   if (c.gws_np == np) return;
@@ -1178,6 +1182,7 @@ void ensure_general(rps_context& c, int np) {
   c.gK1.alloc(c.Np * np, cnt);
   c.gK3.alloc(c.Np * np, cnt);
   c.gY.alloc(c.nauxp * np, cnt);
+  if (c.gSp.p) c.gm1_split = stream_plan_tail(c.precision, pass_m1(c, np), kStreamPartRows, &c.gm1_full);
   c.gwork.alloc(kSplitWork, cnt);
   ensure_energy_parts(c);
   c.Cdev.alloc(c.nbas * np, cnt);
@@ -1299,7 +1304,17 @@ void build_general(rps_context& c, int variant, int nocc, const double* Csrc, do
       hip_check(stream_product(m2, prec, sp, st), "stream M2");
       hip_check(sum_partials3(c.gSp.p, sp, c.nauxp * np, c.gM2.p, nullptr, 0, 0, nullptr, nullptr, 0, 0, nullptr, st),
                 "M2 partials");
-      if (k1) hip_check(stream_product(pass_m1(c, np), prec, 1, st), "stream M1");
+      if (k1) {
+        StreamArgs m1 = pass_m1(c, np);
+        m1.xfull = c.gm1_full;
+        m1.part = c.gSp.p;
+        hip_check(stream_product(m1, prec, c.gm1_split, st), "stream M1");
+        const int64_t r0 = c.gm1_full * 128;
+        if (c.gm1_split > 1)
+          hip_check(sum_partials3(c.gSp.p, c.gm1_split, (c.ngp - r0) * np, c.gM1T.p + r0 * np, nullptr, 0, 0, nullptr,
+                                  nullptr, 0, 0, nullptr, st),
+                    "M1 partials");
+      }
       prof_mark(c, 2, st);
       if (k1 && c.sparse) {
         sparse_k1(c, c.gM1T.p, np, c.gK1.p, st);
@@ -1789,11 +1804,9 @@ void build_full_impl(rps_context& c, int32_t nocc, const double* C, double* K, i
 constexpr int64_t kCoulombChunk = 32ll << 20;   // doubles of U rows per chunk (256 MB)
 constexpr int kCoulombParts = 256;              // blocks of the E_J dot product
 
-// Split count of the J product over the grid: the count, of those that keep at least 128
-// grid rows per split and the partials within kSplitWork, with the least time by two rates
-// measured on it: the LDS-direct FP64 kernel works off rounds of 768 workgroups (lower
-// output tiles of 128 x 64, three per compute unit) at 65 TF/s, and the partials are
-// written and read back at 4 TB/s.
+// Split count of the J product over the grid (lower output tiles of 128 x 64): the count of
+// least estimated time of those that keep at least 128 grid rows per split and the
+// partials within kSplitWork.
 int coulomb_splits(const rps_context& c) {
   const int64_t bn = (c.Np <= 16) ? 16 : 64;
   const int64_t tm = (c.Np + 127) / 128, tn = (c.Np + bn - 1) / bn;
@@ -1804,9 +1817,7 @@ int coulomb_splits(const rps_context& c) {
   double best_t = 1e300;
   for (int64_t z = 1; z <= 512; ++z) {
     if (z > 1 && (c.ngp / z < 128 || z * c.Np * c.Np > kSplitWork)) break;
-    const double rounds = (double)((active * z + 767) / 768);
-    const double t = rounds * (double)(c.ngp / z) * (2.0 * 128 * 64 * 768 / 65e12) +
-                     (double)z * (double)(c.Np * c.Np) * (16.0 / 4e12);
+    const double t = direct64_time(active, c.ngp, z, c.Np * c.Np);
     if (t < best_t) { best_t = t; best = z; }
   }
   return (int)best;

@@ -33,10 +33,15 @@ struct Gemm {
   float* Cf = nullptr; int64_t ldcf = 0;   // also the final C rounded to FP32 here (EPI_AXPBY only)
 };
 hipError_t gemm_f64(const Gemm& g, hipStream_t s);
-// Split count and tile width of an AXPBY product together: the pair whose workgroups fill
-// their last round (two per CU) best, weighted by the share of the tile columns that
-// are not padding; splits keep >= 256 of K and fit work_cap doubles.
+// Split count (and, for the register-staged kernel, tile width) of an AXPBY product; splits
+// keep >= 256 of K and fit work_cap doubles.  LDS-direct kernel: the count of least time by
+// direct64_time; register-staged: the count and width whose workgroups fill their last round
+// (two per CU) best, weighted by the share of the tile columns that are not padding.
 void gemm_plan(Gemm& g, int64_t work_cap_doubles);
+// Estimated seconds of an LDS-direct FP64 product by two rates measured on it: rounds of 768
+// workgroups (tiles of 128 x 64 times z splits of K, three workgroups per compute unit) at
+// 65 TF/s, and the z x outputs partials written and read back at 4 TB/s.
+double direct64_time(int64_t tiles, int64_t K, int64_t z, int64_t outputs);
 // One launch of many independent products: item i computes C_i = alpha op(A_i) op(B_i)
 // + beta C_i with A_i = base.A + aofs etc. (its own sizes and pitches), and with
 // base.kscale + kofs as the row scale when base.kscale is set (transA only).  Items
@@ -302,7 +307,16 @@ struct StreamArgs {
   int64_t ysplit = 0;       // set by stream_product
   int np = 0;
   double* out = nullptr;
+  // the first xfull x blocks (of 128 rows) stream all of y into out [nx][np]; the rest is
+  // split nsplit ways into part [nsplit][nx - 128 xfull][np] (NULL, with xfull = 0: into out)
+  int64_t xfull = 0;
+  double* part = nullptr;
+  int tsplit = 1;                 // set by stream_product, with
+  int64_t xoff = 0, nxo = 0;      // the first row and the rows of a partial
 };
+// xfull and the split count of an unsplit pass's last round, with at most part_rows rows of
+// partials (1: no split).
+int stream_plan_tail(int prec, const StreamArgs& a, int64_t part_rows, int64_t* xfull);
 // Split count along y giving about target_blocks workgroups.
 int stream_splits(int64_t nx, int64_t ny, int target_blocks);
 // prec: 0 FP64 (V), 1 FP32 (V32, FP32 products), 2 split-BF16 products on V32.

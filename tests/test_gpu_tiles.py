@@ -142,3 +142,32 @@ def test_full_exchange_chunks_and_workspace(lib):
         _say("case: full exchange, FP32 context")
         K32 = ctx.build_full(C)
     assert np.abs(K32 - Kf).max() < 1e-6 * np.abs(Kf).max()     # V rounded to 24 bits
+
+
+# ---- streaming passes: the M1 pass's last round of workgroups cut along the points
+@pytest.mark.parametrize("prec,nocc", [("fp32", 16), ("bf16x3", 16), ("fp32", 33), ("fp64", 20), ("fp64", 65)])
+def test_streaming_pass_tail(lib, prec, nocc, monkeypatch):
+    """48^3 grid (864 blocks of 128 rows): at the FP32 and split-BF16 forms' residency the last
+    round is partly empty, so its blocks run in pieces beside whole ones.  Against the FP64
+    fused kernels (n <= 64) or the GEMM form, which share nothing with the passes; the bars are
+    those of the precision forms (1e-6 Ha, 1e-6 of max|K|) and 1e-11 for FP64."""
+    w = ri.diamond_cell(4.0)
+    with lib.Context.from_workload(w, seed=w.sketch_seed()) as ctx:
+        pts = ctx.points()
+        C = ri.lowdin(np.random.default_rng(nocc).standard_normal((w.nbas, nocc)), ctx.overlap())
+        if nocc > 64:
+            monkeypatch.setenv("RPS_GENERAL_GEMM", "1")
+        Kref, Eref = ctx.build(C)
+    monkeypatch.delenv("RPS_GENERAL_GEMM", raising=False)
+    monkeypatch.setenv("RPS_BUILD_PATH", "general")
+    p = {"fp64": lib.PREC_FP64, "fp32": lib.PREC_FP32, "bf16x3": lib.PREC_BF16X3}[prec]
+    with lib.Context.from_workload(w, points=pts, precision=p) as ctx:
+        K, E = ctx.build(C)
+        K2, E2 = ctx.build(C)
+    dk = np.abs(K - Kref).max() / np.abs(Kref).max()
+    _say(f"case: streaming pass tail {prec} n={nocc} dE={E - Eref:.2e} dK={dk:.2e}")
+    assert np.array_equal(K, K2) and E == E2
+    if prec == "fp64":
+        assert dk < 1e-11 and abs(E - Eref) < 1e-11 * abs(Eref)
+    else:
+        assert dk < 1e-6 and abs(E - Eref) < 1e-6
