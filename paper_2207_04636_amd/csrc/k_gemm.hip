@@ -11,6 +11,8 @@
 // fetches of the MFMA read consecutive addresses across the 16 lanes of a row.
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "mfma.h"
 #include "rps_internal.h"
 
@@ -439,6 +441,9 @@ __device__ __forceinline__ int kmajor_row(int q) {
   return ((t >> 2) << 3) + (t & 3) + ((q & 1) << 2);
 }
 
+// Parts of K that run as workgroups of their own on the LDS-direct kernel.
+__host__ __device__ __forceinline__ int gemm32_parts(const Gemm32& g) { return g.splitk / g.merge * g.sub; }
+
 // The same products with the operands moved from global memory straight into LDS
 // (global_load_lds_dwordx4: lane L of a wave writes bytes [16 L, 16 L + 16) after a
 // wave-uniform LDS base), three LDS stages, loads issued two K steps ahead.  With
@@ -450,8 +455,9 @@ __device__ __forceinline__ int kmajor_row(int q) {
 // unrolled over the three stages (one LDS array each, passed to each step as
 // restrict pointers), so the compiler can tell a step's reads from the loads in
 // flight to the other stages and adds no wait of its own beyond the explicit one.
-// FP64 output on 128 x 64 tiles (on 128 x 128 its accumulators spill registers);
-// FP32 output on 128 x 128 tiles, or 128 x 64 where those pad N less.
+// FP64 output on 128 x 64 or 128 x 96 tiles (on 128 x 128 its accumulators spill
+// registers; see gemm32_tile_n64); FP32 output on 128 x 128 tiles, or 128 x 64 where
+// those pad N less.
 //
 // LDS layouts are unpadded, with 16-byte chunks permuted within a row (the DMA
 // writes whole 1 KB runs): K-major rows (16 floats, 4 chunks) hold logical chunk q
@@ -467,10 +473,13 @@ template <int TM, int TN, bool TA, bool TB, bool OUT32>
 __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
   constexpr int BK = 16;
   constexpr int BM = 32 * TM, BN = 32 * TN;
-  constexpr int ASZ = BM * BK, BSZ = BN * BK;                // floats per stage
+  // floats per stage; B in whole 4 KB rounds of the workgroup (96-wide tiles: the second
+  // round's upper half re-reads row BK - 1 into space that is not read)
+  constexpr int ASZ = BM * BK, BSZ = (BN * BK + 1023) / 1024 * 1024;
   constexpr int NA = ASZ / 4 / 256, NB = BSZ / 4 / 256;      // 16-byte pieces per thread per stage
   constexpr int NPER = NA + NB;                              // loads per thread per stage
   static_assert(NA >= 1 && NB >= 1 && NPER < 16, "stage split");
+  static_assert(!TB || BSZ == BN * BK, "a K-major B tile fills whole rounds");
   // one array per stage: the loop is unrolled by the three stages, so the compiler
   // sees that a step's LDS reads and the loads it issues touch different arrays
   __shared__ __attribute__((aligned(16))) float A0[ASZ], A1[ASZ], A2[ASZ];
@@ -480,7 +489,7 @@ __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
   const int l16 = lane & 15, lq = lane >> 4;
   // tile order: as gemm32v_kernel (XCD-contiguous ranges, K splits outermost, groups of 8 row panels)
   const int64_t tiles_n = (g.N + BN - 1) / BN, tiles_m = (g.M + BM - 1) / BM;
-  const int64_t ntile = tiles_n * tiles_m * g.splitk;
+  const int64_t ntile = tiles_n * tiles_m * gemm32_parts(g);
   const int64_t per = ((ntile + 7) / 8);
   const int64_t T = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   if (T >= ntile) return;
@@ -491,12 +500,20 @@ __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
   const int64_t gh = (tiles_m - grp * GROUP < GROUP) ? tiles_m - grp * GROUP : GROUP;
   const int64_t m0 = (grp * GROUP + r2 % gh) * BM, n0 = (r2 / gh) * BN;
 
-  int64_t kbeg = 0, kend = g.K;
-  if (g.splitk > 1) {
-    const int64_t kper = ((g.K + g.splitk - 1) / g.splitk + BK - 1) / BK * BK;
-    kbeg = (int64_t)bz * kper;
-    kend = (kbeg + kper < g.K) ? kbeg + kper : g.K;
+  // part bz of K: g.merge whole splits, or one of g.sub pieces of a split cut at multiples
+  // of 64 from its start; the FP32 sums start anew at each split and every 64 terms in it
+  int64_t kbeg = 0, kend = g.K, kper = g.K;
+  if (g.splitk > 1) kper = ((g.K + g.splitk - 1) / g.splitk + BK - 1) / BK * BK;
+  if (g.sub > 1) {
+    const int64_t k0 = bz / g.sub * kper, sl = (kper + 64 * g.sub - 1) / (64 * g.sub) * 64;
+    const int64_t k1 = (k0 + kper < g.K) ? k0 + kper : g.K;
+    kbeg = k0 + bz % g.sub * sl;
+    kend = (kbeg + sl < k1) ? kbeg + sl : k1;
+  } else if (g.splitk > 1) {
+    kbeg = (int64_t)bz * g.merge * kper;
+    kend = (kbeg + g.merge * kper < g.K) ? kbeg + g.merge * kper : g.K;
   }
+  const int seg = (int)(kper / BK);      // steps of a split
   const int64_t nk = (kend > kbeg) ? (kend - kbeg) / BK : 0;
   const int64_t nread = (g.Nread > g.N) ? g.Nread : g.N;
   const int64_t lda = g.lda, ldb = g.ldb;
@@ -523,7 +540,7 @@ __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
       return g.B + gn * ldb + k0 + 4 * q;
     } else {                                 // MN-major: row k = P / (BN / 4)
       constexpr int CW = BN / 4;
-      const int k = P / CW, c = (P % CW) ^ (k & 4);
+      const int k = (P / CW < BK) ? P / CW : BK - 1, c = (P % CW) ^ (k & 4);
       const int64_t gc = (n0 + 4 * c < nread) ? n0 + 4 * c : n0;
       return g.B + (k0 + k) * ldb + gc;
     }
@@ -560,6 +577,7 @@ __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
         for (int r = 0; r < 4; ++r) acc64[i][j][r] = 0.0;
   }
 
+  int pos = 0;                           // step within the split
   if (nk > 0) {
     issue(0, A0, B0);
     issue(1, A1, B1);
@@ -610,7 +628,9 @@ __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = mfma_f32(a[i][kk], b[j][kk], acc[i][j]);
     if constexpr (!OUT32) {
-      if ((t + 1) % FLUSH == 0 || t + 1 == nk) {
+      ++pos;
+      if (pos % FLUSH == 0 || pos == seg || t + 1 == nk) {
+        if (pos == seg) pos = 0;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -667,7 +687,7 @@ __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
             g.C32[gm * g.ldc + gn] = g.D32[gm * g.ldd + gn] * ((float)g.alpha * acc[i][j][r]);
           } else {
             const double v = g.alpha * acc64[i][j][r];
-            if (g.splitk > 1) {
+            if (gemm32_parts(g) > 1) {
               g.work[((int64_t)bz * g.M + gm) * g.N + gn] = v;
               continue;
             }
@@ -1305,10 +1325,49 @@ bool vec4_ok(const Gemm32& g) {
 }
 }  // namespace
 
+// Tile width of an FP64-output product on the LDS-direct kernel, B MN-major: 96 or 64,
+// whichever has less padded work.  Per padded column 96-wide tiles run 1.04 times as fast
+// (A^T U_g and A U at 7552 x 65536: 119 against 115 TF/s, fewer operand bytes per product),
+// although their accumulators leave two waves per SIMD instead of three; at n = 288, three
+// tiles against five of 64 with a half empty, they took 2.39 and 2.9 ms against 2.74 and
+// 3.14.
+static int gemm32_tile_n64(int64_t N) {
+  const int64_t p96 = (N + 95) / 96 * 96, p64 = (N + 63) / 64 * 64;
+  return (100 * p96 < 104 * p64) ? 96 : 64;
+}
+
 int gemm32_tile_n(int64_t N) {
   // 128-wide output tiles unless 64-wide ones pad N less (N = 432: 448 against 512)
   const int64_t p128 = (N + 127) / 128 * 128, p64 = (N + 63) / 64 * 64;
   return (p64 < p128) ? 64 : 128;
+}
+
+// How the splits of K run on the LDS-direct kernel: several in one workgroup (merge) or each
+// in several pieces (sub), whichever takes least by two rates measured on it (rounds of the
+// resident workgroups at 115 TF/s, partials written and read back at 4 TB/s).  Only the FP64
+// sums are grouped differently.  M1^T of a full chunk at n = 288 goes from three splits to
+// one workgroup per tile (2.52 -> 2.39 ms), M2 from 5 x 177 workgroups on 512 places (1.73
+// rounds) to 20 x 177 (6.9).
+static void gemm32_regroup(Gemm32& g, int bn) {
+  const int64_t tiles = ((g.M + 127) / 128) * ((g.N + bn - 1) / bn), slots = (bn == 96) ? 512 : 768;
+  const int64_t kper = ((g.K + g.splitk - 1) / g.splitk + 15) / 16 * 16;
+  double best = 1e300;
+  auto consider = [&](int merge, int sub) {
+    const int64_t parts = (int64_t)g.splitk / merge * sub;
+    const int64_t len = (sub > 1) ? (kper + 64 * sub - 1) / (64 * sub) * 64 : merge * kper;
+    if (parts > 1 && (!g.work || parts * g.M * g.N > std::max<int64_t>(g.work_cap, (int64_t)g.splitk * g.M * g.N))) return;
+    const double rounds = (double)((tiles * parts + slots - 1) / slots);
+    const double t = rounds * (double)len * (2.0 * 128 * bn * slots / 115e12) +
+                     (parts > 1 ? (double)(parts * g.M * g.N) * (16.0 / 4e12) + 5e-6 : 0.0);
+    if (t < best * (1.0 - 1e-9)) {
+      best = t;
+      g.merge = merge;
+      g.sub = sub;
+    }
+  };
+  for (int m = 1; m <= g.splitk; ++m)
+    if (g.splitk % m == 0) consider(m, 1);
+  for (int u = 2; u <= 8 && kper / u >= 512; ++u) consider(1, u);
 }
 
 hipError_t gemm_f32(const Gemm32& g0, hipStream_t s) {
@@ -1327,15 +1386,21 @@ hipError_t gemm_f32(const Gemm32& g0, hipStream_t s) {
   const char* dv = getenv("RPS_GEMM32_DIRECT");    // "0": the register-staged kernel (comparison runs)
   const bool vec = vec4_ok(g);
   const bool direct = vec && g.K % 16 == 0 && !(dv && dv[0] == '0');
-  const int bn = out32 ? gemm32_tile_n(g.N) : 64;
-  dim3 grid((unsigned)((g.N + bn - 1) / bn), (unsigned)((g.M + 127) / 128), (unsigned)g.splitk);
+  const int bn = out32 ? gemm32_tile_n(g.N) : (direct && !g.transB) ? gemm32_tile_n64(g.N) : 64;
+  g.merge = g.sub = 1;
+  if (direct && !out32) gemm32_regroup(g, bn);
+  const int parts = gemm32_parts(g);
+  dim3 grid((unsigned)((g.N + bn - 1) / bn), (unsigned)((g.M + 127) / 128), (unsigned)parts);
   if (grid.y > 65535u) return hipErrorInvalidValue;
   // the 16-byte kernels order their tiles themselves: one dimension, padded to whole rounds
   // of the eight XCDs (the padding workgroups exit at once)
   const int64_t ntile = (int64_t)grid.x * grid.y * grid.z;
   const dim3 grid1((unsigned)((ntile + 7) / 8 * 8));
   if (vec && ntile > (int64_t)UINT32_MAX - 8) return hipErrorInvalidValue;
-  if (bn == 64) {
+  if (bn == 96) {
+    if (g.transA) hipLaunchKernelGGL((gemm32d_kernel<4, 3, true, false, false>), grid1, dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((gemm32d_kernel<4, 3, false, false, false>), grid1, dim3(256), 0, s, g);
+  } else if (bn == 64) {
     if (direct) { if (out32) launch32d<2, true>(g, grid1, s); else launch32d<2, false>(g, grid1, s); }
     else if (vec) { if (out32) launch32v<2, true>(g, grid1, s); else launch32v<2, false>(g, grid1, s); }
     else { if (out32) launch32<2, true>(g, grid, s); else launch32<2, false>(g, grid, s); }
@@ -1344,20 +1409,21 @@ hipError_t gemm_f32(const Gemm32& g0, hipStream_t s) {
     else if (vec) launch32v<4, true>(g, grid1, s);
     else launch32<4, true>(g, grid, s);
   }
-  if (g.splitk > 1) {
-    launch_splitk_reduce(g.work, g.splitk, g.M, g.N, g.C, g.ldc, g.beta, g.Cf, g.ldcf, s);
+  if (parts > 1) {
+    launch_splitk_reduce(g.work, parts, g.M, g.N, g.C, g.ldc, g.beta, g.Cf, g.ldcf, s);
   }
   return hipGetLastError();
 }
 
 int gemm32_splitk_for(int64_t M, int64_t N, int64_t K, int64_t kmax, int64_t work_cap_doubles) {
   // K per split at most kmax, then >= 1024 workgroups while each split keeps
-  // >= 1024 of K, within the workspace (FP64-output tiles are 128 x 64)
+  // >= 1024 of K, within the workspace.  Planned for 128 x 64 tiles whatever the tile width
+  // used: the split boundaries are where the 64-term FP32 sums start anew, so they fix the
+  // rounding of the result.
   const int bn = 64;
   const int64_t tiles = ((M + 127) / 128) * ((N + bn - 1) / bn);
   // among the split counts that keep >= 1024 of K per split, the one whose workgroups
-  // fill the last round of 768 (three per CU, as the FP64-output tiles run) best, the
-  // smaller on a tie
+  // fill the last round of 768 (three per CU) best, the smaller on a tie
   int64_t z0 = 1;
   while ((K + z0 - 1) / z0 > kmax) ++z0;
   int64_t best = z0;

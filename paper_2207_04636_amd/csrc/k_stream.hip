@@ -659,9 +659,12 @@ hipError_t stream_prepare(const StreamArgs& a, int prec, int nsplit, StreamArgs&
   if (prec == 0 ? !a.V : (!a.V32 || !a.Y32)) return hipErrorInvalidValue;
   b = a;
   if (a.xfull < 0 || a.xfull > stream_xblocks(a.nx) || (a.xfull > 0 && nsplit > 1 && !a.part)) return hipErrorInvalidValue;
-  // y rows per split, a multiple of the tile
+  // y rows per split, a multiple of the tile; of two tiles (the length of its FP32 sums) for
+  // the pieces of a split-BF16 pass's tail, which then sum the same rows together as a whole
+  // block does
   const int64_t tiles = a.ny / BY;
   b.ysplit = ((tiles + nsplit - 1) / nsplit) * BY;
+  if (prec == 2 && a.part) b.ysplit = (b.ysplit + 2 * BY - 1) / (2 * BY) * (2 * BY);
   b.tsplit = nsplit;
   if (!b.part) b.part = b.out;
   b.xoff = 0;

@@ -1363,14 +1363,14 @@ void build_general(rps_context& c, int variant, int nocc, const double* Csrc, do
           m1.A = c.gA32.p; m1.lda = rc; m1.transA = true; m1.B = c.gUg32.p; m1.ldb = npg;
           m1.C = c.gM1T.p + r0 * np; m1.ldc = np;
           if (c.gM1T32.p) { m1.Cf = c.gM1T32.p + r0 * npg; m1.ldcf = npg; }   // FP32 copy for K1
-          m1.splitk = gemm32_splitk_for(m1.M, m1.N, m1.K, kF32Terms, kSplitWork); m1.work = c.gwork.p;
+          m1.splitk = gemm32_splitk_for(m1.M, m1.N, m1.K, kF32Terms, kSplitWork); m1.work = c.gwork.p; m1.work_cap = kSplitWork;
           hip_check(gemm_f32(m1, st), "M1");
         }
         Gemm32 m2;     // M2 += A_c U[c]
         m2.M = c.nauxp; m2.N = np; m2.Nread = npg; m2.K = rc;
         m2.A = c.gA32.p; m2.lda = rc; m2.B = c.gU32.p + r0 * npg; m2.ldb = npg;
         m2.C = c.gM2.p; m2.ldc = np; m2.beta = (r0 == 0) ? 0.0 : 1.0;
-        m2.splitk = gemm32_splitk_for(m2.M, m2.N, m2.K, kF32Terms, kSplitWork); m2.work = c.gwork.p;
+        m2.splitk = gemm32_splitk_for(m2.M, m2.N, m2.K, kF32Terms, kSplitWork); m2.work = c.gwork.p; m2.work_cap = kSplitWork;
         hip_check(gemm_f32(m2, st), "M2");
       } else {
         Gemm a;     // A_c = V[:, c] o (U_g U[c]^T)
@@ -1404,7 +1404,7 @@ void build_general(rps_context& c, int variant, int nocc, const double* Csrc, do
       g.A = c.gPhi32.p; g.lda = c.Np; g.transA = true; g.B = c.gM1T32.p; g.ldb = npg;
       g.C = c.gK1.p; g.ldc = np;
       // 22 x 7 output tiles at the 3x3x3 cell: the long K is split 32-39 ways for parallelism
-      g.splitk = gemm32_splitk_for(g.M, g.N, g.K, (g.K + 31) / 32, kSplitWork); g.work = c.gwork.p;
+      g.splitk = gemm32_splitk_for(g.M, g.N, g.K, (g.K + 31) / 32, kSplitWork); g.work = c.gwork.p; g.work_cap = kSplitWork;
       hip_check(gemm_f32(g, st), "K1");
     } else if (k1) {
       Gemm g;   // K1 = Phi^T M1^T

@@ -69,6 +69,10 @@ struct Gemm32 {
   const float* D32 = nullptr; int64_t ldd = 0;
   int splitk = 1;
   double* work = nullptr;
+  // doubles that work holds (0: splitk * M * N); the LDS-direct kernel may cut the splits
+  // further within it, or join them (merge, sub: set by gemm_f32)
+  int64_t work_cap = 0;
+  int merge = 1, sub = 1;
   // B holds Nread >= N columns (zero beyond N) that may be read: tiles reaching
   // past N but not past Nread load B whole; outputs stay within N (0: Nread = N)
   int64_t Nread = 0;

@@ -171,3 +171,26 @@ def test_streaming_pass_tail(lib, prec, nocc, monkeypatch):
         assert dk < 1e-11 and abs(E - Eref) < 1e-11 * abs(Eref)
     else:
         assert dk < 1e-6 and abs(E - Eref) < 1e-6
+
+
+# ---- FP32 products of the GEMM form: 96- and 64-wide tiles, splits of K joined or cut
+@pytest.mark.parametrize("nocc", [65, 81, 96, 97, 150, 160, 176, 193, 200])
+def test_gemm_form_tiles(lib, nocc, monkeypatch):
+    """n around the edges of the 64- and 96-wide tiles (padded n 80, 96, 112, 160, 176, 208),
+    several chunks with a ragged last one; against the FP64 form, with the bars of the
+    precision forms (1e-6 Ha, 1e-6 of max|K|)."""
+    monkeypatch.setenv("RPS_GENERAL_GEMM", "1")
+    monkeypatch.setenv("RPS_GEMM_RCHUNK", "2048")
+    w = ri.diamond_supercell((2, 1, 1), (36, 17, 18), 2, c=4.0, cid=73)
+    rng = np.random.default_rng(nocc)
+    with lib.Context.from_workload(w, seed=w.sketch_seed()) as ctx:
+        pts = ctx.points()
+        C = ri.lowdin(rng.standard_normal((w.nbas, nocc)), ctx.overlap()) * (16 / nocc) ** 0.5
+        Kref, Eref = ctx.build(C)
+    with lib.Context.from_workload(w, points=pts, precision=lib.PREC_FP32) as ctx:
+        K, E = ctx.build(C)
+        K2, E2 = ctx.build(C)
+    dk = np.abs(K - Kref).max() / np.abs(Kref).max()
+    _say(f"case: GEMM form n={nocc} dE={E - Eref:.2e} dK={dk:.2e}")
+    assert np.array_equal(K, K2) and E == E2
+    assert dk < 1e-6 and abs(E - Eref) < 1e-6
