@@ -736,10 +736,12 @@ void setup_impl(rps_context& c, const rps_cell* cell, const rps_basis* b, int64_
   c.W.alloc(c.nauxp * c.nauxp, &c.bytes);
   hip_check(fill(c.W.p, c.nauxp * c.nauxp, 0.0, st), "fill");
   std::vector<double> kern = coulomb_kernel_table(c.lat, c.mesh);
-  c.kern.alloc(c.ng, &c.bytes);   // kept for the Coulomb matrix builds
+  kern.resize(poisson_table_size(c.mesh));
+  poisson_roots(c.mesh, kern.data() + c.ng);
+  c.kern.alloc((int64_t)kern.size(), &c.bytes);   // kept for the Coulomb matrix builds
   const double* dkern = c.kern.p;
   int64_t tmpb = 0;
-  hip_check(hipMemcpyAsync(c.kern.p, kern.data(), c.ng * 8, hipMemcpyHostToDevice, st), "copy kernel");
+  hip_check(hipMemcpyAsync(c.kern.p, kern.data(), kern.size() * 8, hipMemcpyHostToDevice, st), "copy kernel");
 
   if (given) {
     // rows of the caller's V and W into the padded device arrays (padding stays zero)

@@ -179,7 +179,11 @@ hipError_t pivoted_cholesky_sets(const PcArgs& a, int nsets, int64_t kmax, hipSt
 
 // ---------------------------------------------------------------- Poisson solve
 // In place V <- Vc V for nrows real rows (split-complex pairs of rows, nrows even)
-// of the grid mesh, leading dimension ld.  kern[N_g]: k(G) / N_g in FFT order.
+// of the grid mesh, leading dimension ld.  kern: k(G) / N_g in FFT order (N_g values),
+// followed by the roots of unity of the three axes (poisson_roots).
+int64_t poisson_table_size(const int mesh[3]);
+// For each axis: cos(2 pi m / L), m < L, then the sines (host).
+void poisson_roots(const int mesh[3], double* out);
 hipError_t poisson_rows(double* V, int64_t nrows, int64_t ld, const int mesh[3],
                         const double* kern, hipStream_t s);
 
