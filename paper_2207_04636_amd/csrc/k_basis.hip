@@ -129,7 +129,8 @@ __global__ void gather_kernel(const double* __restrict__ src, int64_t lds, const
   const int64_t t = flat_id();
   if (t >= nrows * ncols) return;
   const int64_t r = t / ncols, c = t % ncols;
-  dst[r * ldd + c] = (r < nidx) ? src[idx[r] * lds + c] : 0.0;
+  const int64_t i = (r < nidx) ? idx[r] : -1;
+  dst[r * ldd + c] = (i >= 0) ? src[i * lds + c] : 0.0;
 }
 
 __global__ void add_diag_kernel(double* X, int64_t ld, int64_t i0, int64_t i1, double v) {

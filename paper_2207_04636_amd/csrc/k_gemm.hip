@@ -113,8 +113,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(Gemm g) {
 // operands prefetched into registers while the matrix cores work on the
 // current LDS buffer (two buffers, one barrier per K step).  KS: row k of
 // op(B) is scaled by kscale[k] as it is loaded.  The body computes the output
-// tile at (m0, n0) of K split bz; gemm_big_kernel and the grouped kernel below
-// differ only in how they pick the tile and the operands.
+// tile at (m0, n0) of K split bz.
 template <int TM, int TN, bool TA, bool TB, bool KS>
 __device__ __forceinline__ void gemm_big_body(const Gemm& g, int64_t m0, int64_t n0, int bz) {
   constexpr int BM = 32 * TM, BN = 32 * TN;
@@ -933,7 +932,7 @@ __host__ __device__ __forceinline__ int64_t direct64_tiles(int64_t M, int64_t N,
 // for an MN-major operand; whole 16-byte pieces past M or N are read from the
 // matrix's edge (their products reach only outputs that are not stored).
 template <int TM, int TN, bool TA, bool TB, bool KS>
-__global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
+__device__ __forceinline__ void gemm64d_body(const Gemm& g, int64_t m0, int64_t n0, int bz) {
   constexpr int BK8 = 8;
   constexpr int BM = 32 * TM, BN = 32 * TN;
   constexpr int ASZ = BM * BK8, BSZ = BN * BK8;              // doubles per stage
@@ -949,35 +948,6 @@ __global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int l16 = lane & 15, lq = lane >> 4;
-  const int64_t tiles_n = (g.N + BN - 1) / BN, tiles_m = (g.M + BM - 1) / BM;
-  const int64_t tiles = direct64_tiles(g.M, g.N, BM, BN, g.lower_only);
-  const int64_t ntile = tiles * g.splitk;
-  const int64_t per = ((ntile + 7) / 8);
-  const int64_t T = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (T >= ntile) return;
-  const int bz = (int)(T / tiles);
-  const int64_t T2 = T % tiles;
-  int64_t m0, n0;
-  if (g.lower_only) {
-    // only the tiles that reach the lower triangle, row panel by row panel: all of a K
-    // split's tiles read the same rows of both operands
-    int64_t i = 0, first = 0;
-    while (true) {
-      const int64_t w = lower_tiles(i, tiles_n, BM, BN);
-      if (T2 < first + w) break;
-      first += w;
-      ++i;
-    }
-    m0 = i * BM;
-    n0 = (T2 - first) * BN;
-  } else {
-    constexpr int64_t GROUP = 8;
-    const int64_t grp = T2 / (GROUP * tiles_n), r2 = T2 % (GROUP * tiles_n);
-    const int64_t gh = (tiles_m - grp * GROUP < GROUP) ? tiles_m - grp * GROUP : GROUP;
-    m0 = (grp * GROUP + r2 % gh) * BM;
-    n0 = (r2 / gh) * BN;
-  }
-
   int64_t kbeg = 0, kend = g.K;
   if (g.splitk > 1) {
     const int64_t kper = ((g.K + g.splitk - 1) / g.splitk + BK8 - 1) / BK8 * BK8;
@@ -1131,18 +1101,63 @@ __global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
       }
 }
 
-// 128 x 64 tiles without the row scale fit three waves per SIMD (168 registers)
-template <int TM, int TN, bool TA, bool TB, bool KS = false>
-__global__ __launch_bounds__(256, (TN == 2 && !KS) ? 3 : 2) void gemm_big_kernel(Gemm g) {
-  gemm_big_body<TM, TN, TA, TB, KS>(g, (int64_t)blockIdx.y * 32 * TM, (int64_t)blockIdx.x * 32 * TN, blockIdx.z);
+// Output tile T2 of a product whose tiles that reach the lower triangle are the only ones:
+// row panel by row panel (all of a K split's tiles read the same rows of both operands).
+__device__ __forceinline__ void lower_tile_at(int64_t T2, int64_t tiles_n, int64_t bm, int64_t bn, int64_t& m0,
+                                              int64_t& n0) {
+  int64_t i = 0, first = 0;
+  while (true) {
+    const int64_t w = lower_tiles(i, tiles_n, bm, bn);
+    if (T2 < first + w) break;
+    first += w;
+    ++i;
+  }
+  m0 = i * bm;
+  n0 = (T2 - first) * bn;
 }
 
-// Many independent products in one launch: item blockIdx.z takes the base operands
-// at its own offsets, sizes and pitches (no K split).
 template <int TM, int TN, bool TA, bool TB, bool KS>
-__global__ __launch_bounds__(256, 2) void gemm_grouped_kernel(Gemm base, const GemmItem* __restrict__ items) {
-  const GemmItem it = items[blockIdx.z];
-  const int64_t m0 = (int64_t)blockIdx.y * 32 * TM, n0 = (int64_t)blockIdx.x * 32 * TN;
+__global__ __launch_bounds__(256, 2) void gemm64d_kernel(Gemm g) {
+  constexpr int BM = 32 * TM, BN = 32 * TN;
+  const int64_t tiles_n = (g.N + BN - 1) / BN, tiles_m = (g.M + BM - 1) / BM;
+  const int64_t tiles = direct64_tiles(g.M, g.N, BM, BN, g.lower_only);
+  const int64_t ntile = tiles * g.splitk;
+  const int64_t per = ((ntile + 7) / 8);
+  const int64_t T = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (T >= ntile) return;
+  const int bz = (int)(T / tiles);
+  const int64_t T2 = T % tiles;
+  int64_t m0, n0;
+  if (g.lower_only) {
+    lower_tile_at(T2, tiles_n, BM, BN, m0, n0);
+  } else {
+    constexpr int64_t GROUP = 8;
+    const int64_t grp = T2 / (GROUP * tiles_n), r2 = T2 % (GROUP * tiles_n);
+    const int64_t gh = (tiles_m - grp * GROUP < GROUP) ? tiles_m - grp * GROUP : GROUP;
+    m0 = (grp * GROUP + r2 % gh) * BM;
+    n0 = (r2 / gh) * BN;
+  }
+  gemm64d_body<TM, TN, TA, TB, KS>(g, m0, n0, bz);
+}
+
+// Many independent products in one launch: an item takes the base operands at its own
+// offsets, sizes and pitches (no K split).  Every item gets the tiles of the largest one
+// (those outside it end at once), and all tiles of an item run on one XCD, whose L2 then
+// holds its operands: workgroup L is on XCD L % 8, which takes the items L % 8, + 8, ...
+template <int TM, int TN, bool TA, bool TB, bool KS>
+__global__ __launch_bounds__(256, 2) void gemm64d_grouped_kernel(Gemm base, const GemmItem* __restrict__ items,
+                                                                int nitems, int64_t tiles, int64_t tiles_n) {
+  constexpr int BM = 32 * TM, BN = 32 * TN;
+  const int64_t seq = blockIdx.x / 8, i = seq / tiles * 8 + blockIdx.x % 8, T2 = seq % tiles;
+  if (i >= nitems) return;
+  const GemmItem it = items[i];
+  int64_t m0, n0;
+  if (base.lower_only) {
+    lower_tile_at(T2, tiles_n, BM, BN, m0, n0);
+  } else {
+    m0 = T2 / tiles_n * BM;
+    n0 = T2 % tiles_n * BN;
+  }
   if (m0 >= it.M || n0 >= it.N) return;
   Gemm g = base;
   g.M = it.M; g.N = it.N; g.K = it.K;
@@ -1150,7 +1165,13 @@ __global__ __launch_bounds__(256, 2) void gemm_grouped_kernel(Gemm base, const G
   g.A = base.A + it.aofs; g.B = base.B + it.bofs; g.C = base.C + it.cofs;
   if (KS) g.kscale = base.kscale + it.kofs;
   g.splitk = 1;
-  gemm_big_body<TM, TN, TA, TB, KS>(g, m0, n0, 0);
+  gemm64d_body<TM, TN, TA, TB, KS>(g, m0, n0, 0);
+}
+
+// 128 x 64 tiles without the row scale fit three waves per SIMD (168 registers)
+template <int TM, int TN, bool TA, bool TB, bool KS = false>
+__global__ __launch_bounds__(256, (TN == 2 && !KS) ? 3 : 2) void gemm_big_kernel(Gemm g) {
+  gemm_big_body<TM, TN, TA, TB, KS>(g, (int64_t)blockIdx.y * 32 * TM, (int64_t)blockIdx.x * 32 * TN, blockIdx.z);
 }
 
 // C = sum_z work[z] + beta * C (fixed order over z).  ZL lanes share an output: lane q
@@ -1438,30 +1459,24 @@ int gemm32_splitk_for(int64_t M, int64_t N, int64_t K, int64_t kmax, int64_t wor
   return (int)best;
 }
 
-namespace {
-template <int TN>
-void launch_grouped(const Gemm& g, const GemmItem* items, dim3 grid, hipStream_t s) {
-  if (g.kscale) hipLaunchKernelGGL((gemm_grouped_kernel<4, TN, true, false, true>), grid, dim3(256), 0, s, g, items);
-  else if (!g.transA && !g.transB)
-    hipLaunchKernelGGL((gemm_grouped_kernel<4, TN, false, false, false>), grid, dim3(256), 0, s, g, items);
-  else if (g.transA && !g.transB)
-    hipLaunchKernelGGL((gemm_grouped_kernel<4, TN, true, false, false>), grid, dim3(256), 0, s, g, items);
-  else if (!g.transA && g.transB)
-    hipLaunchKernelGGL((gemm_grouped_kernel<4, TN, false, true, false>), grid, dim3(256), 0, s, g, items);
-  else hipLaunchKernelGGL((gemm_grouped_kernel<4, TN, true, true, false>), grid, dim3(256), 0, s, g, items);
-}
-}  // namespace
-
 hipError_t gemm_f64_grouped(const Gemm& base, const GemmItem* items, int nitems, int64_t maxM, int64_t maxN,
                             hipStream_t s) {
   if (nitems <= 0 || maxM <= 0 || maxN <= 0) return hipSuccess;
-  if (nitems > 65535 || base.splitk > 1 || base.epi != EPI_AXPBY || base.Cf) return hipErrorInvalidValue;
-  if (base.kscale && !(base.transA && !base.transB)) return hipErrorInvalidValue;
-  const int bn = (maxN <= 64) ? 64 : 128;
-  dim3 grid((unsigned)((maxN + bn - 1) / bn), (unsigned)((maxM + 127) / 128), (unsigned)nitems);
-  if (grid.y > 65535u) return hipErrorInvalidValue;
-  if (bn == 64) launch_grouped<2>(base, items, grid, s);
-  else launch_grouped<4>(base, items, grid, s);
+  if (base.splitk > 1 || base.epi != EPI_AXPBY || base.Cf || base.transB) return hipErrorInvalidValue;
+  if (base.kscale && !base.transA) return hipErrorInvalidValue;
+  const int64_t tiles = direct64_tiles(maxM, maxN, 128, 64, base.lower_only), tiles_n = (maxN + 63) / 64;
+  const int64_t blocks = ((int64_t)nitems + 7) / 8 * 8 * tiles;
+  if (blocks > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks);
+  if (base.kscale)
+    hipLaunchKernelGGL((gemm64d_grouped_kernel<4, 2, true, false, true>), grid, dim3(256), 0, s, base, items, nitems,
+                       tiles, tiles_n);
+  else if (base.transA)
+    hipLaunchKernelGGL((gemm64d_grouped_kernel<4, 2, true, false, false>), grid, dim3(256), 0, s, base, items, nitems,
+                       tiles, tiles_n);
+  else
+    hipLaunchKernelGGL((gemm64d_grouped_kernel<4, 2, false, false, false>), grid, dim3(256), 0, s, base, items, nitems,
+                       tiles, tiles_n);
   return hipGetLastError();
 }
 

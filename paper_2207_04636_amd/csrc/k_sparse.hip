@@ -9,7 +9,9 @@
 //   K1 = Phi^T M1^T:      K1[mu] = sum_{I : mu in S_I} (Phi_I^T M1^T[kappa_I])[pos_I(mu)]
 //   J = Phi^T diag(v) Phi: J[mu][nu] = sum_{I : mu, nu in S_I} (Phi_I^T diag(v) Phi_I)[pos_I(mu)][pos_I(nu)]
 // The per-atom products run as ordinary matrix-core GEMMs; the kernels here are
-// the screening, the block structure and the fixed-order sums over atoms.
+// the screening, the block structure and the fixed-order sums over atoms.  Rows and
+// functions of a block are padded to multiples of 8 with zeros (index -1), which is what
+// the LDS-direct products need of their K and pitches.
 #include "rps_internal.h"
 
 namespace rps {
@@ -39,33 +41,36 @@ __global__ void sig_flags_kernel(const double* __restrict__ Phi, int64_t ng, int
   if (Phi[R * Np + mu] != 0.0) flags[(int64_t)owner[R] * N + mu] = 1;
 }
 
-// dst[r][c] = Phi[rows[r]][cols[c]] for r < nr, c < nc
+// dst[r][c] = Phi[rows[r]][cols[c]] for r < nr, c < nc (0 for the padding's negative entries)
 __global__ void pack_block_kernel(const double* __restrict__ Phi, int Np, const int64_t* __restrict__ rows,
                                   int64_t nr, const int64_t* __restrict__ cols, int nc, double* __restrict__ dst) {
   const int64_t t = flat_id2();
   if (t >= nr * nc) return;
   const int64_t r = t / nc;
   const int c = (int)(t % nc);
-  dst[t] = Phi[rows[r] * Np + cols[c]];
+  const int64_t R = rows[r], m = cols[c];
+  dst[t] = (R >= 0 && m >= 0) ? Phi[R * Np + m] : 0.0;
 }
 
-// out[mu][i] = sum over e in [ofs[mu], ofs[mu+1]) of part[rows[e]][i] (in order), mu < N;
-// rows N..Np-1 of out are zero
-__global__ void csr_rowsum_kernel(const double* __restrict__ part, int np, const int64_t* __restrict__ ofs,
+// out[mu][i] = sum over e in [ofs[mu], ofs[mu+1]) and pieces z < nz of part[z][rows[e]][i]
+// (in order), mu < N; rows N..Np-1 of out are zero
+__global__ void csr_rowsum_kernel(const double* __restrict__ part, int nz, int64_t stride, int np, const int64_t* __restrict__ ofs,
                                   const int64_t* __restrict__ rows, int N, int Np, double* __restrict__ out) {
   const int64_t t = flat_id2();
   if (t >= (int64_t)Np * np) return;
   const int mu = (int)(t / np), i = (int)(t % np);
   double s = 0.0;
   if (mu < N)
-    for (int64_t e = ofs[mu]; e < ofs[mu + 1]; ++e) s += part[rows[e] * np + i];
+    for (int64_t e = ofs[mu]; e < ofs[mu + 1]; ++e)
+      for (int z = 0; z < nz; ++z) s += part[z * stride + rows[e] * np + i];
   out[t] = s;
 }
 
 // J[mu][nu] = J[nu][mu] = scale * sum over the atoms I holding mu (in order) of
-// Q_I[pos_I(mu)][pos_I(nu)] where nu is held too; nu <= mu, so pos_I(nu) <= pos_I(mu)
-// (function lists ascending) and only the lower triangle of each Q_I is read
-__global__ void j_reduce_kernel(const double* __restrict__ Q, const int64_t* __restrict__ qofs,
+// Q_I[pos_I(mu)][pos_I(nu)] where nu is held too (Q_I in nz pieces, one after another);
+// nu <= mu, so pos_I(nu) <= pos_I(mu) (function lists ascending) and only the lower
+// triangle of each Q_I is read
+__global__ void j_reduce_kernel(const double* __restrict__ Q, int nz, const int64_t* __restrict__ qofs,
                                 const int64_t* __restrict__ fofs, const int32_t* __restrict__ pos,
                                 const int64_t* __restrict__ ofs, const int32_t* __restrict__ atom, int N,
                                 double scale, double* __restrict__ J) {
@@ -80,7 +85,7 @@ __global__ void j_reduce_kernel(const double* __restrict__ Q, const int64_t* __r
     if (pn < 0) continue;
     const int pm = pos[(int64_t)I * N + mu];
     const int64_t nI = fofs[I + 1] - fofs[I];
-    s += Q[qofs[I] + (int64_t)pm * nI + pn];
+    for (int z = 0; z < nz; ++z) s += Q[qofs[I] + ((int64_t)z * nI + pm) * nI + pn];
   }
   J[(int64_t)mu * N + nu] = scale * s;
   J[(int64_t)nu * N + mu] = scale * s;
@@ -108,16 +113,16 @@ hipError_t pack_block(const double* Phi, int Np, const int64_t* rows, int64_t nr
   return hipGetLastError();
 }
 
-hipError_t csr_rowsum(const double* part, int np, const int64_t* ofs, const int64_t* rows, int N, int Np,
+hipError_t csr_rowsum(const double* part, int nz, int64_t stride, int np, const int64_t* ofs, const int64_t* rows, int N, int Np,
                       double* out, hipStream_t s) {
-  hipLaunchKernelGGL(csr_rowsum_kernel, flat_grid2((int64_t)Np * np), dim3(256), 0, s, part, np, ofs, rows, N, Np,
+  hipLaunchKernelGGL(csr_rowsum_kernel, flat_grid2((int64_t)Np * np), dim3(256), 0, s, part, nz, stride, np, ofs, rows, N, Np,
                      out);
   return hipGetLastError();
 }
 
-hipError_t j_reduce(const double* Q, const int64_t* qofs, const int64_t* fofs, const int32_t* pos,
+hipError_t j_reduce(const double* Q, int nz, const int64_t* qofs, const int64_t* fofs, const int32_t* pos,
                     const int64_t* ofs, const int32_t* atom, int N, double scale, double* J, hipStream_t s) {
-  hipLaunchKernelGGL(j_reduce_kernel, flat_grid2((int64_t)N * N), dim3(256), 0, s, Q, qofs, fofs, pos, ofs, atom, N,
+  hipLaunchKernelGGL(j_reduce_kernel, flat_grid2((int64_t)N * N), dim3(256), 0, s, Q, nz, qofs, fofs, pos, ofs, atom, N,
                      scale, J);
   return hipGetLastError();
 }

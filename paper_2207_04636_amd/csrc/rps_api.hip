@@ -90,18 +90,21 @@ struct rps_context {
   DBuf<float> Phi32;   // precision form, N <= 128: FP32 basis for the in-kernel orbitals
   DBuf<int64_t> dpoints;
   // Voronoi-screened basis (Sec. 4.1; set up when eps1 > 0): atom I holds grid rows
-  // perm[vofs[I] .. vofs[I+1]) and functions fun[fofs[I] .. fofs[I+1]) (ascending); its
-  // block Phi_I sits at pofs[I] in sPhi (row-major, pitch n_I) and its J block at qofs[I]
+  // perm[vofs[I] .. vofs[I+1]) and functions fun[fofs[I] .. fofs[I+1]) (ascending), both
+  // padded to multiples of 8 with -1; its block Phi_I sits at pofs[I] in sPhi (row-major,
+  // zeros in the padding) and the pieces of its J block at qofs[I]
   double basis_eps = 0.0;
   bool sparse = false;
   std::vector<int64_t> vofs, fofs, pofs, qofs;
   DBuf<int64_t> sperm, sinv, sfun, smu_ofs, smu_rows, sqofs, sfofs;
   DBuf<int32_t> spos, smu_atom;   // pos[I][mu] (-1 if absent); atom of each CSR entry
   DBuf<double> sPhi;
-  int sws_np = -1, sjws_np = -1;
+  int sws_np = -1;
   DBuf<double> sCg, sUv, sK1p, sQ, svv, sUj;
   DBuf<GemmItem> sitU, sitK1, sitJ;   // per-atom products of one grouped launch each
-  int64_t smaxr = 0, smaxc = 0;       // largest Voronoi set, largest function list
+  int64_t smaxr = 0, smaxc = 0;       // largest Voronoi set, largest function list (both padded)
+  double sfill = 1.0, spair = 1.0;    // rps_info.basis_fill, basis_pair_fill
+  int sjns = 1, skns = 1;             // pieces along the grid of an atom's J and K1 products
   // build workspace (grows on demand)
   int ws_np = -1;
   DBuf<double> U, Ug, Ugp, M2p, K1p, K3p, e1p, e3p, M2, K1, K3, Kdev, Cdev, exdev, e3u;
@@ -436,6 +439,27 @@ void compute_owners(rps_context& c, const double* atoms, hipStream_t st) {
   datoms.release(nullptr);
 }
 
+// Pieces along the grid of the atoms' products over their Voronoi sets (J and K1): the count
+// of least estimated time that keeps >= 256 rows per piece, given the largest set, the
+// output tiles of one piece of every atom and their outputs.  (32 atoms of 8000 points with
+// 416 functions: 320 tiles of K = 8000 took 3.5 ms for J; in 4 pieces each on the LDS-direct kernel, 0.8 ms.)
+int sparse_pieces(int64_t rows, int64_t tiles, int64_t outputs) {
+  int best = 1;
+  double best_t = 1e300;
+  for (int z = 1; z <= 64; ++z) {
+    if (z > 1 && rows / z < 256) break;
+    const double t = direct64_time(tiles, rows, z, outputs);
+    if (t < best_t) { best_t = t; best = z; }
+  }
+  return best;
+}
+// First row and row count (a multiple of 8, possibly 0) of piece z of nr rows
+void sparse_piece(int64_t nr, int pieces, int z, int64_t& r0, int64_t& k) {
+  const int64_t seg = round_up((nr + pieces - 1) / pieces, 8);
+  r0 = std::min(z * seg, nr);
+  k = std::min(seg, nr - r0);
+}
+
 // Atom blocks of the screened basis: grid rows of each Voronoi set, the functions not
 // all zero there, the packed blocks and the maps of the fixed-order sums over atoms.
 void build_screened_blocks(rps_context& c, const double* atoms, hipStream_t st) {
@@ -462,21 +486,41 @@ void build_screened_blocks(rps_context& c, const double* atoms, hipStream_t st) 
   c.fofs.assign(natom + 1, 0);
   c.pofs.assign(natom + 1, 0);
   c.qofs.assign(natom + 1, 0);
+  double filled = 0.0, pairs = 0.0;
   for (int I = 0; I < natom; ++I) {
     for (int64_t R : kap[I]) {
       inv[R] = (int64_t)perm.size();
       perm.push_back(R);
     }
+    while (perm.size() % 8) perm.push_back(-1);
     int k = 0;
     for (int mu = 0; mu < N; ++mu)
       if (fl[(size_t)I * N + mu]) {
         pos[(size_t)I * N + mu] = k++;
         fun.push_back(mu);
       }
+    while (fun.size() % 8) fun.push_back(-1);
+    filled += (double)kap[I].size() * k;
+    pairs += (double)kap[I].size() * k * k;
     c.vofs[I + 1] = (int64_t)perm.size();
     c.fofs[I + 1] = (int64_t)fun.size();
-    c.pofs[I + 1] = c.pofs[I] + (int64_t)kap[I].size() * k;
-    c.qofs[I + 1] = c.qofs[I] + (int64_t)k * k;
+    c.pofs[I + 1] = c.pofs[I] + (c.vofs[I + 1] - c.vofs[I]) * (c.fofs[I + 1] - c.fofs[I]);
+  }
+  c.sfill = filled / ((double)c.ng * (double)c.nbas);
+  c.spair = pairs / ((double)c.ng * (double)c.nbas * (double)c.nbas);
+  c.smaxr = c.smaxc = 0;
+  int64_t jtiles = 0, jout = 0;
+  for (int I = 0; I < natom; ++I) {
+    const int64_t nc = c.fofs[I + 1] - c.fofs[I];
+    c.smaxr = std::max(c.smaxr, c.vofs[I + 1] - c.vofs[I]);
+    c.smaxc = std::max(c.smaxc, nc);
+    for (int64_t i = 0; i < (nc + 127) / 128; ++i) jtiles += std::min((nc + 63) / 64, 2 * i + 2);
+    jout += nc * nc;
+  }
+  c.sjns = sparse_pieces(c.smaxr, jtiles, jout);
+  for (int I = 0; I < natom; ++I) {
+    const int64_t nc = c.fofs[I + 1] - c.fofs[I];
+    c.qofs[I + 1] = c.qofs[I] + c.sjns * nc * nc;
   }
   // for every function, the atoms holding it (ascending) and its packed row there
   std::vector<int64_t> mofs(N + 1, 0), mrows;
@@ -516,13 +560,15 @@ void build_screened_blocks(rps_context& c, const double* atoms, hipStream_t st) 
   }
   // J blocks: lower triangles of Phi_I^T diag(v[kappa_I]) Phi_I, one grouped launch
   std::vector<GemmItem> jt;
-  c.smaxr = c.smaxc = 0;
   for (int I = 0; I < natom; ++I) {
     const int64_t nr = c.vofs[I + 1] - c.vofs[I], nc = c.fofs[I + 1] - c.fofs[I];
-    c.smaxr = std::max(c.smaxr, nr);
-    c.smaxc = std::max(c.smaxc, nc);
     if (nc == 0) continue;
-    jt.push_back(GemmItem{nc, nc, nr, nc, nc, nc, c.pofs[I], c.pofs[I], c.qofs[I], c.vofs[I]});
+    for (int z = 0; z < c.sjns; ++z) {
+      int64_t r0, k;
+      sparse_piece(nr, c.sjns, z, r0, k);
+      jt.push_back(GemmItem{nc, nc, k, nc, nc, nc, c.pofs[I] + r0 * nc, c.pofs[I] + r0 * nc, c.qofs[I] + z * nc * nc,
+                            c.vofs[I] + r0});
+    }
   }
   c.sitJ.alloc(std::max<int64_t>((int64_t)jt.size(), 1), &c.bytes);
   if (!jt.empty())
@@ -1103,17 +1149,26 @@ FusedWs context_ws(rps_context& c, int np) {
 void ensure_sparse_ws(rps_context& c, int np) {
   if (c.sws_np == np) return;
   c.clear_graphs();
-  c.sCg.alloc(std::max<int64_t>(c.fofs[c.natom], 1) * np, &c.bytes);
-  c.sK1p.alloc(std::max<int64_t>(c.fofs[c.natom], 1) * np, &c.bytes);
-  c.sUv.alloc(c.ng * np, &c.bytes);
+  const int64_t F = std::max<int64_t>(c.fofs[c.natom], 1);
+  int64_t tiles = 0;
+  for (int I = 0; I < c.natom; ++I) tiles += (c.fofs[I + 1] - c.fofs[I] + 127) / 128 * ((np + 63) / 64);
+  c.skns = sparse_pieces(c.smaxr, tiles, c.fofs[c.natom] * np);
+  c.sCg.alloc(F * np, &c.bytes);
+  c.sK1p.alloc(c.skns * F * np, &c.bytes);
+  c.sUv.alloc(std::max<int64_t>(c.vofs[c.natom], 1) * np, &c.bytes);
   // U rows of atom I = Phi_I C[S_I] (an empty function list gives zero rows: K = 0);
-  // K1 partial rows of atom I = Phi_I^T M1T[kappa_I]
+  // K1 partial rows of atom I = Phi_I^T M1T[kappa_I], in skns pieces along the grid
   std::vector<GemmItem> ut, kt;
   for (int I = 0; I < c.natom; ++I) {
     const int64_t nr = c.vofs[I + 1] - c.vofs[I], nc = c.fofs[I + 1] - c.fofs[I];
-    if (nr > 0) ut.push_back(GemmItem{nr, np, nc, std::max<int64_t>(nc, 1), np, np, c.pofs[I], c.fofs[I] * np,
+    if (nr > 0) ut.push_back(GemmItem{nr, np, nc, std::max<int64_t>(nc, 8), np, np, c.pofs[I], c.fofs[I] * np,
                                       c.vofs[I] * np, 0});
-    if (nc > 0) kt.push_back(GemmItem{nc, np, nr, nc, np, np, c.pofs[I], c.vofs[I] * np, c.fofs[I] * np, 0});
+    for (int z = 0; nc > 0 && z < c.skns; ++z) {
+      int64_t r0, k;
+      sparse_piece(nr, c.skns, z, r0, k);
+      kt.push_back(GemmItem{nc, np, k, nc, np, np, c.pofs[I] + r0 * nc, (c.vofs[I] + r0) * np,
+                            (z * F + c.fofs[I]) * np, 0});
+    }
   }
   auto up = [&](DBuf<GemmItem>& d, const std::vector<GemmItem>& h) {
     d.alloc(std::max<int64_t>((int64_t)h.size(), 1), &c.bytes);
@@ -1204,25 +1259,30 @@ void gemm_run(Gemm g, rps_context& c, hipStream_t st, const char* what, bool all
 }
 
 // ---- products with the screened basis (atom blocks; see k_sparse.hip)
-// U (ngp x np, grid order) = Phi C from the atom blocks; Cp is C packed [Np][np]
-void sparse_u(rps_context& c, const double* Cp, int np, double* U, hipStream_t st) {
+// sUv (np columns, Voronoi order) = Phi C from the atom blocks; Cp is C packed [Np][np]
+void sparse_uv(rps_context& c, const double* Cp, int np, hipStream_t st) {
   ensure_sparse_ws(c, np);
   const int64_t F = c.fofs[c.natom];
   if (F > 0) hip_check(gather_rows(Cp, np, c.sfun.p, F, F, np, c.sCg.p, np, st), "C rows");
   Gemm g;   // U[kappa_I] = Phi_I C[S_I] for every atom
   g.A = c.sPhi.p; g.B = c.sCg.p; g.C = c.sUv.p;
   hip_check(gemm_f64_grouped(g, c.sitU.p, (int)c.sitU.n, c.smaxr, np, st), "U blocks");
+}
+// the same in grid order (U: ngp x np)
+void sparse_u(rps_context& c, const double* Cp, int np, double* U, hipStream_t st) {
+  sparse_uv(c, Cp, np, st);
   hip_check(gather_rows(c.sUv.p, np, c.sinv.p, c.ng, c.ngp, np, U, np, st), "U rows");
 }
 
 // K1 (Np x np) = Phi^T M1T from the atom blocks (M1T: ngp x np, grid order)
 void sparse_k1(rps_context& c, const double* M1T, int np, double* K1, hipStream_t st) {
   ensure_sparse_ws(c, np);
-  hip_check(gather_rows(M1T, np, c.sperm.p, c.ng, c.ng, np, c.sUv.p, np, st), "M1 rows");
+  const int64_t P = c.vofs[c.natom], F = std::max<int64_t>(c.fofs[c.natom], 1);
+  hip_check(gather_rows(M1T, np, c.sperm.p, P, P, np, c.sUv.p, np, st), "M1 rows");
   Gemm g;   // partial K1 rows of every atom: Phi_I^T M1T[kappa_I]
   g.A = c.sPhi.p; g.transA = true; g.B = c.sUv.p; g.C = c.sK1p.p;
   hip_check(gemm_f64_grouped(g, c.sitK1.p, (int)c.sitK1.n, c.smaxc, np, st), "K1 blocks");
-  hip_check(csr_rowsum(c.sK1p.p, np, c.smu_ofs.p, c.smu_rows.p, (int)c.nbas, (int)c.Np, K1, st), "K1 sums");
+  hip_check(csr_rowsum(c.sK1p.p, c.skns, F * np, np, c.smu_ofs.p, c.smu_rows.p, (int)c.nbas, (int)c.Np, K1, st), "K1 sums");
 }
 
 // The streaming passes of a general-path build (one description, used by the eager
@@ -1853,14 +1913,14 @@ void ensure_coulomb(rps_context& c, int np) {
 void sparse_j(rps_context& c, const double* vh, double* J, hipStream_t st) {
   if (!c.sQ.p) {
     c.sQ.alloc(std::max<int64_t>(c.qofs[c.natom], 1), &c.bytes);
-    c.svv.alloc(c.ng, &c.bytes);
+    c.svv.alloc(std::max<int64_t>(c.vofs[c.natom], 1), &c.bytes);
   }
-  hip_check(gather_rows(vh, 1, c.sperm.p, c.ng, c.ng, 1, c.svv.p, 1, st), "V_H rows");
+  hip_check(gather_rows(vh, 1, c.sperm.p, c.vofs[c.natom], c.vofs[c.natom], 1, c.svv.p, 1, st), "V_H rows");
   Gemm g;
   g.A = c.sPhi.p; g.transA = true; g.B = c.sPhi.p; g.C = c.sQ.p;
   g.kscale = c.svv.p; g.lower_only = true;
   hip_check(gemm_f64_grouped(g, c.sitJ.p, (int)c.sitJ.n, c.smaxc, c.smaxc, st), "J blocks");
-  hip_check(j_reduce(c.sQ.p, c.sqofs.p, c.sfofs.p, c.spos.p, c.smu_ofs.p, c.smu_atom.p, (int)c.nbas, c.dV, J, st),
+  hip_check(j_reduce(c.sQ.p, c.sjns, c.sqofs.p, c.sfofs.p, c.spos.p, c.smu_ofs.p, c.smu_atom.p, (int)c.nbas, c.dV, J, st),
             "J sums");
 }
 
@@ -1887,13 +1947,15 @@ void build_coulomb_impl(rps_context& c, int32_t nocc, const double* C, double* J
   else
     hip_check(pack_matrix(Csrc, N, nocc, nocc, c.jCp.p, Np, np, st), "pack C");
   if (!small && c.sparse) {
-    // step 1 from the atom blocks of the screened basis: U in grid order, then rho
-    if (c.sjws_np != np) {
-      c.sUj.alloc(R * np, &c.bytes);
-      c.sjws_np = np;
-    }
-    sparse_u(c, c.jCp.p, np, c.sUj.p, st);
-    hip_check(density_rows(c.sUj.p, R, np, c.jrho.p, R, st), "density");
+    // step 1 from the atom blocks of the screened basis: U and rho in Voronoi order, then
+    // rho (not U, np times as much) put in grid order
+    const int64_t P = std::max<int64_t>(c.vofs[c.natom], 1);
+    if (!c.sUj.p) c.sUj.alloc(3 * P, &c.bytes);
+    sparse_uv(c, c.jCp.p, np, st);
+    hip_check(density_rows(c.sUv.p, P, np, c.sUj.p, P, st), "density");
+    hip_check(gather_rows(c.sUj.p, 1, c.sinv.p, c.ng, R, 1, c.jrho.p, 1, st), "rho rows");
+    hip_check(gather_rows(c.sUj.p, 1, c.sinv.p, c.ng, R, 1, c.jrho.p + 2 * R, 1, st), "rho rows");
+    hip_check(fill(c.jrho.p + R, R, 0.0, st), "clear");
   }
   // step 1: density, one chunk of grid rows at a time (rows past N_g have Phi = 0, so rho = 0)
   for (int64_t r0 = 0; !small && !c.sparse && r0 < R; r0 += c.jchunk) {
@@ -2659,13 +2721,8 @@ rps_status rps_get_info(const rps_context* ctx, rps_info* info) {
     info->n_candidates = c.ncand; info->dvol = c.dV; info->chol_shift = c.shift;
     info->setup_seconds = c.setup_seconds; info->device_bytes = c.bytes;
     info->precision = c.precision; info->exact = c.exact; info->madelung = c.madelung;
-    info->basis_fill = c.sparse ? (double)c.pofs[c.natom] / ((double)c.ng * (double)c.nbas) : 1.0;
-    double pair = 0.0;
-    for (int I = 0; c.sparse && I < c.natom; ++I) {
-      const double nc = (double)(c.fofs[I + 1] - c.fofs[I]);
-      pair += (double)(c.vofs[I + 1] - c.vofs[I]) * nc * nc;
-    }
-    info->basis_pair_fill = c.sparse ? pair / ((double)c.ng * (double)c.nbas * (double)c.nbas) : 1.0;
+    info->basis_fill = c.sfill;
+    info->basis_pair_fill = c.spair;
     info->build_arith = c.last_arith;
   });
 }

@@ -42,10 +42,12 @@ void gemm_plan(Gemm& g, int64_t work_cap_doubles);
 // workgroups (tiles of 128 x 64 times z splits of K, three workgroups per compute unit) at
 // 65 TF/s, and the z x outputs partials written and read back at 4 TB/s.
 double direct64_time(int64_t tiles, int64_t K, int64_t z, int64_t outputs);
-// One launch of many independent products: item i computes C_i = alpha op(A_i) op(B_i)
-// + beta C_i with A_i = base.A + aofs etc. (its own sizes and pitches), and with
-// base.kscale + kofs as the row scale when base.kscale is set (transA only).  Items
-// live in device memory; maxM / maxN bound their sizes.  No K split; EPI_AXPBY only.
+// One launch of many independent products on the LDS-direct kernel: item i computes
+// C_i = alpha op(A_i) B_i + beta C_i with A_i = base.A + aofs etc. (its own sizes and
+// pitches), and with base.kscale + kofs as the row scale when base.kscale is set (transA
+// only).  Items live in device memory; maxM / maxN bound their sizes.  The caller's layout
+// gives every item a K that is a multiple of 8 (or 0: C_i = beta C_i), even pitches and
+// widths and 16-byte aligned operands.  No K split; EPI_AXPBY only.
 struct GemmItem {
   int64_t M, N, K, lda, ldb, ldc, aofs, bofs, cofs, kofs;
 };
@@ -89,14 +91,16 @@ hipError_t screen_basis(double* Phi, int64_t count, double thr, hipStream_t s);
 // flags[owner[R] * N + mu] = 1 where Phi[R][mu] != 0 (flags zeroed by the caller)
 hipError_t basis_flags(const double* Phi, int64_t ng, int Np, int N, const int32_t* owner, int32_t* flags,
                        hipStream_t s);
-// dst[r][c] = Phi[rows[r]][cols[c]] (dst row-major, pitch nc)
+// dst[r][c] = Phi[rows[r]][cols[c]], 0 for a negative row or column (dst row-major, pitch nc)
 hipError_t pack_block(const double* Phi, int Np, const int64_t* rows, int64_t nr, const int64_t* cols, int nc,
                       double* dst, hipStream_t s);
-// out[mu][i] = sum_{e in [ofs[mu], ofs[mu+1])} part[rows[e]][i], in order (mu < N; rows N..Np-1 zero)
-hipError_t csr_rowsum(const double* part, int np, const int64_t* ofs, const int64_t* rows, int N, int Np,
+// out[mu][i] = sum_{e in [ofs[mu], ofs[mu+1])} sum_{z < nz} part[z][rows[e]][i], in order (mu < N;
+// rows N..Np-1 zero; stride doubles between the pieces z)
+hipError_t csr_rowsum(const double* part, int nz, int64_t stride, int np, const int64_t* ofs, const int64_t* rows, int N, int Np,
                       double* out, hipStream_t s);
-// J[mu][nu] = J[nu][mu] = scale * sum_{e in ofs[mu]..} Q_atom[e][pos(mu)][pos(nu)] (lower triangles read)
-hipError_t j_reduce(const double* Q, const int64_t* qofs, const int64_t* fofs, const int32_t* pos,
+// J[mu][nu] = J[nu][mu] = scale * sum_{e in ofs[mu]..} sum_{z < nz} Q_{atom[e], z}[pos(mu)][pos(nu)]
+// (lower triangles read; the nz pieces of an atom's block follow one another)
+hipError_t j_reduce(const double* Q, int nz, const int64_t* qofs, const int64_t* fofs, const int32_t* pos,
                     const int64_t* ofs, const int32_t* atom, int N, double scale, double* J, hipStream_t s);
 
 // ---------------------------------------------------------------- basis / grid
@@ -118,7 +122,7 @@ hipError_t basis_eval(const CellDev& cell, const ShellDev* shells, int nshell, i
 // owner[R] = nearest atom over periodic images (ties -> lower index).
 hipError_t voronoi_assign(const CellDev& cell, const double* atoms, int natom, int64_t ngrid,
                           int32_t* owner, hipStream_t s);
-// dst[r][0:ncols] = src[idx[r]][0:ncols] for r < nidx, 0 for nidx <= r < nrows.
+// dst[r][0:ncols] = src[idx[r]][0:ncols] for r < nidx (0 for a negative index), 0 for nidx <= r < nrows.
 hipError_t gather_rows(const double* src, int64_t lds, const int64_t* idx, int64_t nidx,
                        int64_t nrows, int64_t ncols, double* dst, int64_t ldd, hipStream_t s);
 // X[g][idx[g]] = 1 for g < n (fitting functions of the exact case, chi = identity)

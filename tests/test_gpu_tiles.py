@@ -194,3 +194,30 @@ def test_gemm_form_tiles(lib, nocc, monkeypatch):
     _say(f"case: GEMM form n={nocc} dE={E - Eref:.2e} dK={dk:.2e}")
     assert np.array_equal(K, K2) and E == E2
     assert dk < 1e-6 and abs(E - Eref) < 1e-6
+
+
+# ---- screened basis: atom blocks padded to multiples of 8, products in pieces along the grid
+@pytest.mark.parametrize("w,nocc,eps", [
+    (ri.diamond_supercell((1, 1, 1), (24, 24, 23), 2, c=4.0, cid=74), 17, 1e-2),      # |kappa| about 1650, ragged
+    (ri.diamond_supercell((2, 1, 1), (33, 16, 15), 2, c=4.0, cid=75), 65, 1e-3),
+    (ri.tiny_cell(), 3, 3e-2),                                                        # pieces of K1 and J
+    (_s_cell(9, (6, 7, 5), nocc=2, lmax=2), 2, 3e-1),                                 # blocks of few functions
+], ids=["8-atoms", "16-atoms", "2-atoms", "9-atoms"])
+def test_screened_blocks(lib, w, nocc, eps, monkeypatch):
+    """K and J from the atom blocks against the screened values in dense form (FP64 both,
+    other summation orders: 1e-11), through the general path."""
+    monkeypatch.setenv("RPS_BUILD_PATH", "general")
+    monkeypatch.setenv("RPS_COULOMB_GEMM", "1")
+    C = np.linalg.qr(np.random.default_rng(5).standard_normal((w.nbas, nocc)))[0].copy()
+    pts = np.linspace(0, w.ngrid - 1, 6).astype(np.int64)
+    out = []
+    for blocks in ("1", "0"):
+        monkeypatch.setenv("RPS_SCREENED_BLOCKS", blocks)
+        kw = dict(seed=w.sketch_seed()) if w.naux > 10 else dict(points=pts[:w.naux])
+        with lib.Context.from_workload(w, basis_eps=eps, **kw) as ctx:
+            out.append((*ctx.build(C), *ctx.build_coulomb(C), ctx.info()["basis_fill"]))
+    (K, E, J, EJ, fill), (K0, E0, J0, EJ0, _) = out
+    _say(f"case: screened blocks N={w.nbas} n={nocc} fill={fill:.3f}")
+    assert 0.0 < fill < 1.0
+    assert np.abs(K - K0).max() < 1e-11 * np.abs(K0).max() and abs(E - E0) < 1e-11 * abs(E0)
+    assert np.abs(J - J0).max() < 1e-11 * np.abs(J0).max() and abs(EJ - EJ0) < 1e-11 * abs(EJ0)
