@@ -74,12 +74,23 @@ __global__ __launch_bounds__(256) void sum_scaled_kernel(const double* __restric
 
 // J[i][j] = J[j][i] = scale * sum_z work[z][i][j] for j <= i < N.  Block (64, ZG):
 // 64 consecutive elements of the [Np][Np] partials, ZG interleaved groups of z
-// summed separately, then combined in a fixed order.
+// summed separately, then combined in a fixed order.  With ej, one more block forms
+// *ej = scale * sum of ejpart.
 constexpr int ZG = 16;
 __global__ __launch_bounds__(64 * ZG) void sym_from_lower_kernel(const double* __restrict__ work, int nz, int64_t Np,
-                                                                 int64_t N, double scale, double* __restrict__ J) {
+                                                                 int64_t N, double scale, double* __restrict__ J,
+                                                                 const double* __restrict__ ejpart, int nej,
+                                                                 double* __restrict__ ej) {
   __shared__ double red[ZG][64];
   const int tx = threadIdx.x, ty = threadIdx.y;
+  if (ej && blockIdx.x == gridDim.x - 1) {       // the extra block: *ej = scale * sum of ejpart
+    if (ty != 0) return;
+    double s = 0.0;
+    for (int i = tx; i < nej; i += 64) s += ejpart[i];
+    s = wave_sum(s);
+    if (tx == 0) *ej = scale * s;
+    return;
+  }
   const int64_t e = (int64_t)blockIdx.x * 64 + tx;
   const int64_t i = e / Np, j = e % Np;
   const bool live = (i < N) && (j <= i);
@@ -192,73 +203,128 @@ __global__ __launch_bounds__(256) void density_small_kernel(const double* __rest
   }
 }
 
-// J partials: workgroup b sums v[R] phi[R][mu] phi[R][nu] over its chunks of 64 grid
-// rows (b, b + gridDim.x, ...) for the lower 16 x 16 tiles (mb >= nb) and writes them
-// to part[b][Np][Np] (upper tiles untouched).  Chunks are staged in LDS with the next
-// one requested into registers meanwhile; tile t of the lower triangle belongs to wave
-// t % 8.
-template <int MT>
-__global__ __launch_bounds__(512) void coulomb_small_kernel(const double* __restrict__ Phi, int64_t rows,
-                                                           const double* __restrict__ v,
-                                                           double* __restrict__ part) {
-  constexpr int NPK = 16 * MT, RC = 64, PPD = NPK + 1;
-  constexpr int NT = MT * (MT + 1) / 2, TPW = (NT + 7) / 8;
-  constexpr int PER = RC * NPK / 512;          // doubles per thread of a chunk
-  static_assert(PER * 512 == RC * NPK, "chunk split");
-  __shared__ double sP[RC * PPD];
-  __shared__ double sv[RC];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+// J partials: a pair of waves (4 pairs per workgroup) takes the groups of four grid rows W,
+// W + all pairs, ... and sums v[R] phi[R][mu] phi[R][nu] over them for every lower 16 x 16
+// tile (mb >= nb), each wave for half of the tile rows mb; the workgroup's sum goes to
+// part[b][Np][Np] (upper tiles untouched) and the sum of rho v over its rows to ejpart[b].
+//
+// The A and the B operand of a 16-column block of four rows are the same register (lane
+// (lq, l16) holds phi[4 g + lq][16 m + l16]), so a group costs MT loads straight from
+// global memory, a few multiplications by v and MT (MT + 1) / 2 matrix-core instructions
+// between the two waves, with no LDS and no barrier, and PF groups in flight.  Bound by the
+// basis read and the matrix cores alike (22 and 21 us at N = 104, N_g = 48^3).  Measured
+// there: 64-row chunks staged in LDS for eight waves with a share of the tiles each 41 us
+// (three LDS reads per matrix-core instruction); one wave with all 28 tiles 45 us (its 224
+// accumulator registers travel between the two register files); this form 36 us.
+constexpr int csm_half(int mt, int mb) {       // which wave of the pair has tile row mb
+  int load[2] = {0, 0}, h = 0;
+  for (int m = mt - 1; m >= mb; --m) {         // longest row first, to the lighter wave
+    h = (load[1] < load[0]) ? 1 : 0;
+    load[h] += m + 1;
+  }
+  return h;
+}
+constexpr int csm_tiles(int mt, int half, int below) {   // tiles of a wave in rows < below
+  int n = 0;
+  for (int m = 0; m < below; ++m)
+    if (csm_half(mt, m) == half) n += m + 1;
+  return n;
+}
+template <int MT, int HALF>
+__device__ __forceinline__ void coulomb_small_wave(const double* __restrict__ Phi, int64_t rows,
+                                                   const double* __restrict__ v, const double* __restrict__ rho,
+                                                   double* __restrict__ part, double* lds, double& ej) {
+  constexpr int NPK = 16 * MT, NT = csm_tiles(MT, HALF, MT), PF = 4;
+  const int lane = threadIdx.x & 63, pair = threadIdx.x >> 7;
   const int l16 = lane & 15, lq = lane >> 4;
-  const int64_t nchunk = rows / RC;
-  // this wave's tiles (mb, nb), mb >= nb
-  int tmb[TPW], tnb[TPW];
+  const int64_t ngroup = rows / 4, stride = (int64_t)gridDim.x * 4, first = (int64_t)blockIdx.x * 4 + pair;
+  const int64_t mine = (ngroup + stride - 1) / stride;     // steps, the same for every pair
+  d4_t acc[NT > 0 ? NT : 1];
 #pragma unroll
-  for (int q = 0; q < TPW; ++q) {
-    int t = w + 8 * q, mb = 0;
-    while (t > mb) { t -= mb + 1; ++mb; }
-    tmb[q] = (w + 8 * q < NT) ? mb : -1;
-    tnb[q] = t;
-  }
-  d4_t acc[TPW];
+  for (int t = 0; t < NT; ++t) acc[t] = zero_d4();
+  double x[PF][MT], xv[PF], xr[PF];
+  auto fetch = [&](int64_t i, double (&d)[MT], double& dv, double& dr) {
+    const int64_t g = first + i * stride, gc = (g < ngroup) ? g : ngroup - 1;     // in bounds; counts as 0
+    const double* src = Phi + (gc * 4 + lq) * NPK + l16;
 #pragma unroll
-  for (int q = 0; q < TPW; ++q) acc[q] = zero_d4();
-  double nx[PER];
-  double nv = 0.0;
-  auto fetch = [&](int64_t c) {
-    const double* src = Phi + c * RC * NPK;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) nx[i] = src[tid + 512 * i];
-    if (tid < RC) nv = v[c * RC + tid];
+    for (int m = 0; m < MT; ++m) d[m] = src[16 * m];       // (rows above this wave's last are dropped)
+    dv = v[gc * 4 + lq];
+    dr = rho[gc * 4 + lq];
   };
-  int64_t c = blockIdx.x;
-  if (c < nchunk) fetch(c);
-  for (; c < nchunk; c += gridDim.x) {
-    __syncthreads();
+  // the compiler must not sink a group's loads to their use in the next pass of the loop
+  // (nothing here writes memory): an empty statement that may, after each request
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = tid + 512 * i;
-      sP[(e / NPK) * PPD + e % NPK] = nx[i];
-    }
-    if (tid < RC) sv[tid] = nv;
-    __syncthreads();
-    if (c + gridDim.x < nchunk) fetch(c + gridDim.x);
+  for (int p = 0; p < PF; ++p) fetch(p, x[p], xv[p], xr[p]);
+  asm volatile("" ::: "memory");
+  for (int64_t i = 0; i < mine; i += PF) {
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-      if (tmb[q] < 0) continue;
-      const double* pa = sP + lq * PPD + 16 * tmb[q] + l16;
-      const double* pb = sP + lq * PPD + 16 * tnb[q] + l16;
+    for (int p = 0; p < PF; ++p) {
+      const double s = (first + (i + p) * stride < ngroup) ? xv[p] : 0.0;
+      ej += s * xr[p];
 #pragma unroll
-      for (int kk = 0; kk < RC / 4; ++kk)
-        acc[q] = mfma_f64(pa[4 * kk * PPD], sv[4 * kk + lq] * pb[4 * kk * PPD], acc[q]);
+      for (int mb = 0; mb < MT; ++mb)
+        if (csm_half(MT, mb) == HALF) {
+          const double a = s * x[p][mb];
+#pragma unroll
+          for (int nb = 0; nb <= mb; ++nb)
+            acc[csm_tiles(MT, HALF, mb) + nb] = mfma_f64(a, x[p][nb], acc[csm_tiles(MT, HALF, mb) + nb]);
+        }
+      fetch(i + p + PF, x[p], xv[p], xr[p]);
+      asm volatile("" ::: "memory");
     }
   }
-  double* o = part + (int64_t)blockIdx.x * NPK * NPK;
+  // sum of the four pairs: (0 + 2) + (1 + 3); each half has its own part of the buffers
+  constexpr int ALL = MT * (MT + 1) / 2, T0 = (HALF == 0) ? 0 : csm_tiles(MT, 0, MT);
+  double* buf = lds + T0 * 256 + lane;
+  if (pair >= 2)
 #pragma unroll
-  for (int q = 0; q < TPW; ++q) {
-    if (tmb[q] < 0) continue;
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) o[(16 * tmb[q] + 4 * r + lq) * NPK + 16 * tnb[q] + l16] = acc[q][r];
+      for (int r = 0; r < 4; ++r) buf[(pair & 1) * ALL * 256 + (t * 4 + r) * 64] = acc[t][r];
+  __syncthreads();
+  if (pair < 2)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[t][r] += buf[pair * ALL * 256 + (t * 4 + r) * 64];
+  __syncthreads();
+  if (pair == 1)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) buf[(t * 4 + r) * 64] = acc[t][r];
+  __syncthreads();
+  if (pair == 0) {
+    double* o = part + (int64_t)blockIdx.x * NPK * NPK;
+#pragma unroll
+    for (int mb = 0; mb < MT; ++mb)
+      if (csm_half(MT, mb) == HALF)
+#pragma unroll
+        for (int nb = 0; nb <= mb; ++nb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int t = csm_tiles(MT, HALF, mb) + nb;
+            o[(16 * mb + 4 * r + lq) * NPK + 16 * nb + l16] = acc[t][r] + buf[(t * 4 + r) * 64];
+          }
   }
+}
+
+template <int MT>
+__global__ __launch_bounds__(512, 2) void coulomb_small_kernel(const double* __restrict__ Phi, int64_t rows,
+                                                              const double* __restrict__ v,
+                                                              const double* __restrict__ rho,
+                                                              double* __restrict__ part,
+                                                              double* __restrict__ ejpart) {
+  extern __shared__ double lds[];              // [2][MT (MT + 1) / 2][4][64], the waves' sums
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double ej = 0.0;
+  if ((w & 1) == 0) coulomb_small_wave<MT, 0>(Phi, rows, v, rho, part, lds, ej);
+  else coulomb_small_wave<MT, 1>(Phi, rows, v, rho, part, lds, ej);
+  __syncthreads();
+  const double es = wave_sum((lane & 15) == 0 ? ej : 0.0);
+  if (lane == 0) lds[w] = es;
+  __syncthreads();
+  if (threadIdx.x == 0) ejpart[blockIdx.x] = (lds[0] + lds[4]) + (lds[2] + lds[6]);
 }
 
 }  // namespace
@@ -291,19 +357,24 @@ hipError_t density_small(const double* Phi, int64_t rows, int Np, const double* 
   return hipGetLastError();
 }
 
-hipError_t coulomb_small(const double* Phi, int64_t rows, int Np, const double* v, double* part, hipStream_t s) {
+hipError_t coulomb_small(const double* Phi, int64_t rows, int Np, const double* v, const double* rho, double* part,
+                         double* ejpart, hipStream_t s) {
   if (rows % 64 != 0 || Np % 16 != 0 || Np > 128) return hipErrorInvalidValue;
   const int blocks = coulomb_small_blocks(rows);
-  switch (Np / 16) {
-    case 1: hipLaunchKernelGGL((coulomb_small_kernel<1>), dim3(blocks), dim3(512), 0, s, Phi, rows, v, part); break;
-    case 2: hipLaunchKernelGGL((coulomb_small_kernel<2>), dim3(blocks), dim3(512), 0, s, Phi, rows, v, part); break;
-    case 3: hipLaunchKernelGGL((coulomb_small_kernel<3>), dim3(blocks), dim3(512), 0, s, Phi, rows, v, part); break;
-    case 4: hipLaunchKernelGGL((coulomb_small_kernel<4>), dim3(blocks), dim3(512), 0, s, Phi, rows, v, part); break;
-    case 5: hipLaunchKernelGGL((coulomb_small_kernel<5>), dim3(blocks), dim3(512), 0, s, Phi, rows, v, part); break;
-    case 6: hipLaunchKernelGGL((coulomb_small_kernel<6>), dim3(blocks), dim3(512), 0, s, Phi, rows, v, part); break;
-    case 7: hipLaunchKernelGGL((coulomb_small_kernel<7>), dim3(blocks), dim3(512), 0, s, Phi, rows, v, part); break;
-    default: hipLaunchKernelGGL((coulomb_small_kernel<8>), dim3(blocks), dim3(512), 0, s, Phi, rows, v, part); break;
+  const int mt = Np / 16;
+  const size_t lds = (size_t)mt * (mt + 1) * 256 * 8;      // up to 147 KB
+#define RPS_CSM(MT_)                                                                                                  \
+  do {                                                                                                                \
+    hipError_t e_ = hipFuncSetAttribute((const void*)coulomb_small_kernel<MT_>,                                       \
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                        \
+    if (e_ != hipSuccess) return e_;                                                                                  \
+    hipLaunchKernelGGL((coulomb_small_kernel<MT_>), dim3(blocks), dim3(512), lds, s, Phi, rows, v, rho, part, ejpart); \
+  } while (0)
+  switch (mt) {
+    case 1: RPS_CSM(1); break; case 2: RPS_CSM(2); break; case 3: RPS_CSM(3); break; case 4: RPS_CSM(4); break;
+    case 5: RPS_CSM(5); break; case 6: RPS_CSM(6); break; case 7: RPS_CSM(7); break; default: RPS_CSM(8); break;
   }
+#undef RPS_CSM
   return hipGetLastError();
 }
 
@@ -331,11 +402,11 @@ hipError_t dot_scaled(const double* x, const double* y, int64_t n, double scale,
 }
 
 hipError_t sym_from_lower(const double* work, int nz, int64_t Np, int64_t N, double scale, double* J,
-                          hipStream_t s) {
+                          hipStream_t s, const double* ejpart, int nej, double* ej) {
   if (N <= 0) return hipSuccess;
   const int64_t cnt = N * Np;   // rows below N of the partials
-  hipLaunchKernelGGL(sym_from_lower_kernel, dim3((unsigned)((cnt + 63) / 64)), dim3(64, ZG), 0, s, work, nz, Np, N,
-                     scale, J);
+  hipLaunchKernelGGL(sym_from_lower_kernel, dim3((unsigned)((cnt + 63) / 64) + (ej ? 1u : 0u)), dim3(64, ZG), 0, s,
+                     work, nz, Np, N, scale, J, ejpart, nej, ej);
   return hipGetLastError();
 }
 

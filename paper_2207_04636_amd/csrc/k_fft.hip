@@ -76,36 +76,121 @@ __device__ __forceinline__ void butterfly(double (&xr)[R], double (&xi)[R], doub
 // One Stockham stage of radix R after sub-transforms of length ns: butterfly j (< L / R)
 // takes the R points j + r L / R, turns them by exp(sg 2 pi i r (j mod ns) / (ns R)),
 // applies the R-point transform and writes point r' to (j / ns) ns R + (j mod ns) + r' ns.
-// Thread t works on pencil t mod PEN.  wr, wi: exp(2 pi i m / L), ns R divides L.
+// The elements of a pencil lie st apart.  wr, wi: exp(2 pi i m / L), ns R divides L.
+template <int R>
+__device__ __forceinline__ void stage_point(const double* sr, const double* si, double* dr, double* di, int st, int L,
+                                            int ns, int j, const double* wr, const double* wi, double sg) {
+  const int nb = L / R, ts = nb / ns;
+  const int jd = (j * ((65536 + ns - 1) / ns)) >> 16;        // j / ns for j, ns <= 256
+  const int k = j - jd * ns;
+  double xr[R], xi[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    xr[r] = sr[(j + r * nb) * st];
+    xi[r] = si[(j + r * nb) * st];
+  }
+  if (ns > 1) {
+#pragma unroll
+    for (int r = 1; r < R; ++r) {
+      const double c = wr[r * k * ts], w = sg * wi[r * k * ts];
+      const double a = xr[r], b = xi[r];
+      xr[r] = a * c - b * w;
+      xi[r] = a * w + b * c;
+    }
+  }
+  butterfly<R>(xr, xi, sg);
+  const int d0 = jd * ns * R + k;
+#pragma unroll
+  for (int o = 0; o < R; ++o) {
+    dr[(d0 + o * ns) * st] = xr[o];
+    di[(d0 + o * ns) * st] = xi[o];
+  }
+}
+
+// A stage for the PEN pencils of an axis workgroup: thread t works on pencil t mod PEN.
 template <int R, int PEN, int NT>
 __device__ __forceinline__ void stage(const double* sr, const double* si, double* dr, double* di, int L, int ns,
                                       const double* wr, const double* wi, double sg, int tid) {
-  const int nb = L / R, ts = nb / ns;
-  const int inv = (65536 + ns - 1) / ns;        // j / ns = j inv >> 16 for j, ns <= 256
-  for (int j = tid / PEN; j < nb; j += NT / PEN) {
-    const int jd = (j * inv) >> 16, k = j - jd * ns;
-    double xr[R], xi[R];
+  for (int j = tid / PEN; j < L / R; j += NT / PEN) stage_point<R>(sr, si, dr, di, 1, L, ns, j, wr, wi, sg);
+}
+
+// A stage for npen pencils, sp apart, of a plane (elements st apart): consecutive threads
+// take consecutive pencils.
+template <int R, int NT>
+__device__ __forceinline__ void plane_stage(const double* sr, const double* si, double* dr, double* di, int npen,
+                                            int sp, int st, int L, int ns, const double* wr, const double* wi,
+                                            double sg, int tid) {
+  const int nb = L / R;
+  const float rn = 1.0f / (float)npen;
+  for (int e = tid; e < npen * nb; e += NT) {
+    const int j = (int)(((float)e + 0.5f) * rn), o = (e - j * npen) * sp;
+    stage_point<R>(sr + o, si + o, dr + o, di + o, st, L, ns, j, wr, wi, sg);
+  }
+}
+
+__host__ __device__ __forceinline__ bool smooth235(int L) {
+  while (L % 2 == 0) L /= 2;
+  while (L % 3 == 0) L /= 3;
+  while (L % 5 == 0) L /= 5;
+  return L == 1;
+}
+
+// Both inner axes of one plane (L1 x L2, contiguous) of a row pair in LDS, forward (axis 2,
+// then axis 1) or inverse (axis 1, then axis 2): three launches for a Poisson solve instead
+// of five, and three passes over the rows.  A latency chain for the Coulomb build's one
+// pair (48 planes of 48 x 48: two launches of 7 us became one), bandwidth for the set-up.
+// LDS pitch L2 + 1 (or + 2 to make it odd) spreads rows and columns over the banks.
+constexpr int PLANE_NT = 512;
+__host__ __device__ __forceinline__ int plane_pitch(int L2) { return L2 | 1; }
+inline size_t plane_lds(int L1, int L2) {
+  return ((size_t)4 * L1 * plane_pitch(L2) + 2 * (L1 + L2)) * sizeof(double);
+}
+template <bool INV>
+__global__ __launch_bounds__(PLANE_NT) void dft_plane_kernel(double* __restrict__ V, int64_t ld, int L1, int L2,
+                                                            const double* __restrict__ tw1,
+                                                            const double* __restrict__ tw2) {
+  extern __shared__ double sm[];
+  const int tid = threadIdx.x, P = plane_pitch(L2), n = L1 * L2, half = L1 * P;
+  double* w1 = sm + 4 * half;            // cosines and sines of axis 1, then of axis 2
+  double* w2 = w1 + 2 * L1;
+  double* re = V + (int64_t)(2 * blockIdx.y) * ld + (int64_t)blockIdx.x * n;
+  double* im = re + ld;
+  const float r2 = 1.0f / (float)L2;
+  for (int m = tid; m < 2 * L1; m += PLANE_NT) w1[m] = tw1[m];
+  for (int m = tid; m < 2 * L2; m += PLANE_NT) w2[m] = tw2[m];
+  for (int e = tid; e < n; e += PLANE_NT) {
+    const int i = (int)(((float)e + 0.5f) * r2);
+    sm[i * P + e - i * L2] = re[e];
+    sm[half + i * P + e - i * L2] = im[e];
+  }
+  __syncthreads();
+  const double sg = INV ? 1.0 : -1.0;
+  int cur = 0;                           // buffer: re at 2 cur half, im at (2 cur + 1) half
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      xr[r] = sr[j + r * nb];
-      xi[r] = si[j + r * nb];
+  for (int pass = 0; pass < 2; ++pass) {
+    const bool inner = INV ? (pass == 1) : (pass == 0);      // along axis 2
+    const int L = inner ? L2 : L1, npen = inner ? L1 : L2, sp = inner ? P : 1, st = inner ? 1 : P;
+    const double *wr = inner ? w2 : w1, *wi = wr + L;
+    int ns = 1, left = L;
+    while (left > 1) {
+      const int R = (left % 4 == 0) ? 4 : (left % 2 == 0) ? 2 : (left % 3 == 0) ? 3 : 5;
+      const double *sr = sm + 2 * cur * half, *si = sr + half;
+      double *dr = sm + 2 * (cur ^ 1) * half, *di = dr + half;
+      if (R == 4) plane_stage<4, PLANE_NT>(sr, si, dr, di, npen, sp, st, L, ns, wr, wi, sg, tid);
+      else if (R == 2) plane_stage<2, PLANE_NT>(sr, si, dr, di, npen, sp, st, L, ns, wr, wi, sg, tid);
+      else if (R == 3) plane_stage<3, PLANE_NT>(sr, si, dr, di, npen, sp, st, L, ns, wr, wi, sg, tid);
+      else plane_stage<5, PLANE_NT>(sr, si, dr, di, npen, sp, st, L, ns, wr, wi, sg, tid);
+      __syncthreads();
+      cur ^= 1;
+      ns *= R;
+      left /= R;
     }
-    if (ns > 1) {
-#pragma unroll
-      for (int r = 1; r < R; ++r) {
-        const double c = wr[r * k * ts], w = sg * wi[r * k * ts];
-        const double a = xr[r], b = xi[r];
-        xr[r] = a * c - b * w;
-        xi[r] = a * w + b * c;
-      }
-    }
-    butterfly<R>(xr, xi, sg);
-    const int d0 = jd * ns * R + k;
-#pragma unroll
-    for (int o = 0; o < R; ++o) {
-      dr[d0 + o * ns] = xr[o];
-      di[d0 + o * ns] = xi[o];
-    }
+  }
+  const double* out = sm + 2 * cur * half;
+  for (int e = tid; e < n; e += PLANE_NT) {
+    const int i = (int)(((float)e + 0.5f) * r2);
+    re[e] = out[i * P + e - i * L2];
+    im[e] = out[half + i * P + e - i * L2];
   }
 }
 
@@ -155,11 +240,7 @@ __global__ __launch_bounds__(NT) void dft_axis_kernel(double* __restrict__ V, in
   constexpr int PASSES = (MODE == 2) ? 2 : 1;
   int cur = 0;
   // lengths whose factors are all 2, 3 and 5 take the fast transform
-  int rest = L;
-  while (rest % 2 == 0) rest /= 2;
-  while (rest % 3 == 0) rest /= 3;
-  while (rest % 5 == 0) rest /= 5;
-  const bool fast = (rest == 1);
+  const bool fast = smooth235(L);
 #pragma unroll
   for (int pass = 0; pass < PASSES; ++pass) {
     // out[k] = sum_j x[j] exp(sg * 2 pi i j k / L), sg = -1 forward, +1 inverse
@@ -274,11 +355,25 @@ hipError_t poisson_rows(double* V, int64_t nrows, int64_t ld, const int mesh[3],
         go<4, 64, 128>(Vc, ld, L, inner[axis], np, kern, tw[axis], cn, mode, s);
       }
     };
-    launch(2, 0);
-    launch(1, 0);
-    launch(0, 2);
-    launch(1, 1);
-    launch(2, 1);
+    // a plane of up to about 5000 points fits in LDS; the direct sum of other lengths stays
+    // with the axis kernel
+    const size_t lds = plane_lds(mesh[1], mesh[2]);
+    if (lds <= 160 * 1024 && smooth235(mesh[1]) && smooth235(mesh[2])) {
+      const dim3 grid((unsigned)mesh[0], (unsigned)cn);
+      hipError_t e = hipFuncSetAttribute((const void*)dft_plane_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void*)dft_plane_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(dft_plane_kernel<false>, grid, dim3(PLANE_NT), lds, s, Vc, ld, mesh[1], mesh[2], tw[1], tw[2]);
+      launch(0, 2);
+      hipLaunchKernelGGL(dft_plane_kernel<true>, grid, dim3(PLANE_NT), lds, s, Vc, ld, mesh[1], mesh[2], tw[1], tw[2]);
+    } else {
+      launch(2, 0);
+      launch(1, 0);
+      launch(0, 2);
+      launch(1, 1);
+      launch(2, 1);
+    }
   }
   return hipGetLastError();
 }

@@ -1864,7 +1864,7 @@ void build_full_impl(rps_context& c, int32_t nocc, const double* C, double* K, i
 
 // ------------------------------------------------------------------ Coulomb matrix
 constexpr int64_t kCoulombChunk = 32ll << 20;   // doubles of U rows per chunk (256 MB)
-constexpr int kCoulombParts = 256;              // blocks of the E_J dot product
+constexpr int kCoulombParts = 256;              // most partials of E_J (its host copy's source follows them)
 
 // Split count of the J product over the grid (lower output tiles of 128 x 64): the count of
 // least estimated time of those that keep at least 128 grid rows per split and the
@@ -1902,7 +1902,7 @@ void ensure_coulomb(rps_context& c, int np) {
   if (!c.jrho.p) c.jrho.alloc(3 * c.ngp, cnt);
   const int64_t nw = std::max<int64_t>({1, coulomb_splits(c), small ? coulomb_small_blocks(c.ngp) : 1});
   if (c.jwork.n < nw * c.Np * c.Np) c.jwork.alloc(nw * c.Np * c.Np, cnt);
-  if (!c.jpart.p) c.jpart.alloc(kCoulombParts, cnt);
+  if (!c.jpart.p) c.jpart.alloc(kCoulombParts + 1, cnt);
   c.jws_np = np;
   c.jws_small = small;
 }
@@ -1970,14 +1970,17 @@ void build_coulomb_impl(rps_context& c, int32_t nocc, const double* C, double* J
   hip_check(poisson_rows(c.jrho.p, 2, R, c.mesh, c.kern.p, st), "poisson");
   double* exout = nullptr;
   if (ej) {
-    exout = dev ? ej : c.jpart.p + (kCoulombParts - 1);
-    hip_check(dot_scaled(c.jrho.p, c.jrho.p + 2 * R, R, c.dV, c.jpart.p, kCoulombParts - 1, exout, st), "E_J");
+    exout = dev ? ej : c.jpart.p + kCoulombParts;
+    if (!small)
+      hip_check(dot_scaled(c.jrho.p, c.jrho.p + 2 * R, R, c.dV, c.jpart.p, kCoulombParts - 1, exout, st), "E_J");
   }
   // step 4: lower tiles of Phi^T diag(V_H) Phi, split over the grid, mirrored and scaled by dV
   double* Jout = dev ? J : c.jJ.p;
   if (small) {
-    hip_check(coulomb_small(c.Phi.p, R, (int)Np, c.jrho.p, c.jwork.p, st), "Phi^T diag(V_H) Phi");
-    hip_check(sym_from_lower(c.jwork.p, coulomb_small_blocks(R), Np, N, c.dV, Jout, st), "J");
+    const int nb = coulomb_small_blocks(R);      // at most kCoulombParts
+    hip_check(coulomb_small(c.Phi.p, R, (int)Np, c.jrho.p, c.jrho.p + 2 * R, c.jwork.p, c.jpart.p, st),
+              "Phi^T diag(V_H) Phi");
+    hip_check(sym_from_lower(c.jwork.p, nb, Np, N, c.dV, Jout, st, c.jpart.p, nb, exout), "J and E_J");
   } else if (c.sparse) {
     sparse_j(c, c.jrho.p, Jout, st);
   } else {

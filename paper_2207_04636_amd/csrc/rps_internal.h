@@ -200,18 +200,20 @@ hipError_t density_rows(const double* U, int64_t rows, int np, double* out, int6
 hipError_t dot_scaled(const double* x, const double* y, int64_t n, double scale, double* part, int nparts,
                       double* out, hipStream_t s);
 // J[i][j] = scale * sum_{z < nz} work[z][max(i,j)][min(i,j)] for i, j < N (work [nz][Np][Np],
-// lower triangle valid).
+// lower triangle valid).  With ej also *ej = scale * sum_{i < nej} ejpart[i].
 hipError_t sym_from_lower(const double* work, int nz, int64_t Np, int64_t N, double scale, double* J,
-                          hipStream_t s);
+                          hipStream_t s, const double* ejpart = nullptr, int nej = 0, double* ej = nullptr);
 
 // Small-basis Coulomb path (Np <= 128): rho of rows [0, rows) of Phi [rows][Np] with
 // U = Phi C (np <= 64) written as density_rows does; and the lower 16 x 16 tiles of the
 // partials part[b][Np][Np] = sum over workgroup b's 64-row chunks of v[R] phi[R] phi[R]^T
-// (rows % 64 == 0; coulomb_small_blocks(rows) partials).
+// (rows % 64 == 0; coulomb_small_blocks(rows) partials), with ejpart[b] = sum of rho v over
+// the same rows.
 hipError_t density_small(const double* Phi, int64_t rows, int Np, const double* C, int N, int n, int np,
                          double* out, int64_t ld, hipStream_t s);
 int coulomb_small_blocks(int64_t rows);
-hipError_t coulomb_small(const double* Phi, int64_t rows, int Np, const double* v, double* part, hipStream_t s);
+hipError_t coulomb_small(const double* Phi, int64_t rows, int Np, const double* v, const double* rho, double* part,
+                         double* ejpart, hipStream_t s);
 
 // Madelung term: K[mu][i] += M SC[mu][i] (K, C: [N][n]; SC pitch ldsc) and, if ex,
 // *ex -= M sum C o SC, summed over nparts (<= 256) blocks in a fixed order (part: workspace).

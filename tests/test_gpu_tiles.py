@@ -221,3 +221,25 @@ def test_screened_blocks(lib, w, nocc, eps, monkeypatch):
     assert 0.0 < fill < 1.0
     assert np.abs(K - K0).max() < 1e-11 * np.abs(K0).max() and abs(E - E0) < 1e-11 * abs(E0)
     assert np.abs(J - J0).max() < 1e-11 * np.abs(J0).max() and abs(EJ - EJ0) < 1e-11 * abs(EJ0)
+
+
+# ---- Coulomb matrix of small bases: lower tiles shared by a pair of waves, groups of four rows
+@pytest.mark.parametrize("nfunc,mesh", [
+    (1, (4, 4, 4)), (16, (4, 5, 13)), (17, (9, 8, 7)), (33, (8, 8, 9)), (49, (12, 11, 10)), (65, (16, 16, 17)),
+    (81, (15, 16, 10)), (97, (20, 18, 16)), (112, (24, 24, 24)), (113, (9, 10, 8)), (128, (32, 30, 31)),
+])
+def test_coulomb_small_basis(lib, nfunc, mesh):
+    """One case per padded N up to 128 with grids from one 64-row block to several groups per
+    pair of waves (and lengths that do and do not take the plane transform)."""
+    w = _s_cell(nfunc, mesh, nocc=min(3, nfunc), cid=91)
+    _say(f"case: small Coulomb N={w.nbas} mesh={mesh}")
+    Phi = basis.eval_basis(w)
+    C = _coefficients(w)
+    Jref, Eref, _ = coulomb.build_j(Phi, C, w.lattice, w.mesh)
+    pts = np.linspace(0, w.ngrid - 1, w.naux).astype(np.int64)
+    with lib.Context.from_workload(w, points=pts) as ctx:
+        J, E = ctx.build_coulomb(C)
+        J2, E2 = ctx.build_coulomb(C)
+    assert np.abs(J - Jref).max() < 1e-11 * np.abs(Jref).max()
+    assert abs(E - Eref) < 1e-11 * abs(Eref)
+    assert np.array_equal(J, J2) and E == E2
