@@ -705,7 +705,8 @@ __global__ __launch_bounds__(512) void fused_f32u_kernel(FusedArgs a) {
   constexpr int RP = NP + 1;               // M1 partial pitch
   constexpr int SL = T + 4;                // FP32 slab pitch (floats)
   extern __shared__ double smem[];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: addresses stay scalar
   const int l16 = lane & 15, lq = lane >> 4;
   const int Np = a.Np, PP = Np + 4;
 
@@ -833,8 +834,8 @@ __global__ __launch_bounds__(512) void fused_f32u_kernel(FusedArgs a) {
   // the h rows of the unit (W is symmetric, so W o P_g^T is B^T), and its registers feed
   // the product directly.  Units go round-robin over all waves of the grid, FP64; the
   // operands of a wave's first unit were requested at the top of the kernel.
-  for (; u3 < n3; u3 += (int64_t)gridDim.x * NW) {
-    const int64_t ys = u3 / nsub3, hc = u3 % nsub3;
+  auto l3_unit = [&](int64_t u) {
+    const int64_t ys = u / nsub3, hc = u % nsub3;
     const int64_t y0 = ys * 16;
     d4_t pt = zero_d4();    // P_g^T[h0 + 4r + lq][y0 + l16]
 #pragma unroll
@@ -850,8 +851,12 @@ __global__ __launch_bounds__(512) void fused_f32u_kernel(FusedArgs a) {
       e += l3yr[r] * yacc[r];
     }
     e = wave_sum(e);
-    if (lane == 0) a.e3u[u3] = e;
-    if (u3 + (int64_t)gridDim.x * NW < n3) l3_load(u3 + (int64_t)gridDim.x * NW);
+    if (lane == 0) a.e3u[u] = e;
+  };
+  if (u3 < n3) l3_unit(u3);
+  for (u3 += (int64_t)gridDim.x * NW; u3 < n3; u3 += (int64_t)gridDim.x * NW) {
+    l3_load(u3);     // requested and used inside the round: none is pending in the tile loop's waits
+    l3_unit(u3);
   }
 
   auto tile = [&](auto tau, int64_t rt) {
@@ -990,10 +995,14 @@ __global__ __launch_bounds__(512) void fused_f32u_kernel(FusedArgs a) {
     }
   };
 
-  for (int64_t rt = rt0; rt < rt1; rt += 2) {
+  // (an odd last tile by itself: a way from the first tile of a pair back to the loop's head
+  // would leave the V buffers in the other order there, and every pair would wait for all of V)
+  int64_t rt = rt0;
+  for (; rt + 1 < rt1; rt += 2) {
     tile(std::integral_constant<int, 0>{}, rt);
-    if (rt + 1 < rt1) tile(std::integral_constant<int, 1>{}, rt + 1);
+    tile(std::integral_constant<int, 1>{}, rt + 1);
   }
+  if (rt < rt1) tile(std::integral_constant<int, 0>{}, rt);
 
   const int wg = blockIdx.x;
   if (a.want_k1 && w < mt) {
@@ -1009,6 +1018,323 @@ __global__ __launch_bounds__(512) void fused_f32u_kernel(FusedArgs a) {
       const int64_t g0 = (gs0 + w + si * NW) * 16;
 #pragma unroll
       for (int r = 0; r < 4; ++r) out[(g0 + 4 * lq + r) * NP + l16] = m2acc[si][r];
+    }
+}
+
+// FP64, n <= 16, with the orbitals formed tile by tile in the kernel (N <= 128).
+// Per R tile the FP64 basis rows are staged in LDS once and serve both ends of the
+// tile: U = Phi C at its start, K1 += Phi^T M1^T at its end.  The kernel is bound by
+// the V stream, and everything is arranged to keep V requests in flight:
+//  * U never goes to memory and Phi is read once (the separate orbitals pass read it
+//    a first time and cost 23 us of the 104-function cell's build);
+//  * M2 accumulates in registers (NMY g subtiles per wave, at most 5), which leaves
+//    LDS to the basis rows;
+//  * V is requested two steps ahead and the next tile's basis rows a few pieces per
+//    step.  Loads return in order, so within a step the U_g operands of the next step
+//    go out first, then the basis pieces, then V: no wait ever covers the newest V;
+//  * columns are paired (position 16 (2 h + e) + j of a tile is grid row
+//    R0 + 32 h + 2 j + e), so V is read and A is staged 16 bytes at a time.
+// The fit-fit line is folded in as in fused_f32u_kernel.  NW = 8 waves.
+constexpr int SL2 = T + 2;   // pitch of the paired A slab (doubles, 16-byte aligned rows)
+
+template <int NMY, int PF>
+__global__ __launch_bounds__(512) void fused_f64u_kernel(FusedArgs a) {
+  constexpr int NW = 8;
+  constexpr int NP = 16;
+  constexpr int LDU = NP + 1;
+  extern __shared__ double smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: addresses stay scalar
+  const int l16 = lane & 15, lq = lane >> 4;
+  constexpr int PP = 16 * PF + 2;          // sPhi pitch
+  const int Np = a.Np;
+
+  const int64_t gsub_total = a.G / 16;
+  const int64_t gper = ((a.G / T + a.gblocks - 1) / a.gblocks) * (T / 16);
+  const int gb = blockIdx.x % a.gblocks;
+  const int rb = blockIdx.x / a.gblocks;
+  const int64_t gs0 = gb * gper;
+  const int64_t gs1 = (gs0 + gper < gsub_total) ? gs0 + gper : gsub_total;
+  const int64_t rtiles_valid = (a.R_valid + T - 1) / T;
+  const int64_t rt0 = (int64_t)rb * a.rtiles;
+  const int64_t rt1 = (rt0 + a.rtiles < rtiles_valid) ? rt0 + a.rtiles : rtiles_valid;
+
+  // LDS (doubles): slabs [NW][16][SL2] | sPhi [T][PP] | sC [Np][16] | sU [T][LDU].
+  // A wave's slab also takes its M1 partial [T][16]; the summed M1 overwrites sU.
+  double* slab = smem + w * 16 * SL2;
+  double* sPhi = smem + NW * 16 * SL2;
+  double* sC = sPhi + T * PP;
+  double* sU = sC + Np * NP;
+  double* m1s = sU;
+  const int nmy = (gs1 - gs0 > w) ? (int)((gs1 - gs0 - w + NW - 1) / NW) : 0;   // <= NMY (host check)
+
+  // operands of this wave's first fit-fit unit, requested before anything else
+  const int64_t nsub3 = a.Wl ? a.G / 16 : 0, n3 = nsub3 * nsub3;
+  int64_t u3 = (int64_t)blockIdx.x * NW + w;
+  double l3ha[4], l3ya[4], l3w[4], l3hb[4], l3yr[4];
+  auto l3_load = [&](int64_t u) {
+    const int64_t y0 = (u / nsub3) * 16, h0 = (u % nsub3) * 16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      l3ha[q] = a.Ug[(h0 + l16) * NP + 4 * q + lq];
+      l3ya[q] = a.Ug[(y0 + l16) * NP + 4 * q + lq];
+      l3w[q] = a.Wl[(h0 + 4 * q + lq) * a.ldw + y0 + l16];
+      l3hb[q] = a.Ug[(h0 + 4 * q + lq) * NP + l16];
+      l3yr[q] = a.Ug[(y0 + 4 * q + lq) * NP + l16];
+    }
+  };
+  if (u3 < n3) l3_load(u3);
+#pragma unroll 4
+  for (int e = tid; e < Np * NP; e += NW * 64) {
+    const int r = e / NP, c = e % NP;
+    sC[e] = (r < a.N && c < a.n) ? a.Cm[(int64_t)r * a.n + c] : 0.0;
+  }
+
+  // V fragment of step (tile rt, subtile si): lane holds rows g0 + 4r + lq, columns
+  // R0 + 32 h + 2 l16 + e as element [r][2h + e].  A step that does not exist re-reads
+  // V row 0 of the first tile, so that every wait counts the same loads.
+  double vb[2][4][4];
+  typedef double pair_t __attribute__((ext_vector_type(2)));
+  // Addresses are a uniform base in scalar registers and a 32-bit lane offset (three rows of
+  // V: ldv < 2^27, checked on the host).  The offset is made opaque at each use: folded into
+  // 64-bit lane addresses kept over the loop it spills.
+  const uint32_t voff = (uint32_t)((lq * a.ldv + 2 * l16) * 8);
+  auto opaque = [](uint32_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+  auto load_v = [&](double (&dst)[4][4], int64_t rt, int si) {
+    const bool ok = rt < rt1 && si < nmy;
+    const int64_t R0 = (ok ? rt : rt0) * T, g0 = ok ? (gs0 + w + (int64_t)si * NW) * 16 : 0;
+    const uint32_t vo = opaque(voff);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const char* row = reinterpret_cast<const char*>(a.Vm + (g0 + 4 * r) * a.ldv + R0);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const pair_t q = *reinterpret_cast<const pair_t*>(row + vo + 256 * h);
+        dst[r][2 * h] = q.x;
+        dst[r][2 * h + 1] = q.y;
+      }
+    }
+  };
+  double ugA[4], ugB[4];      // U_g operands of a step: A of P, B of M1
+  auto load_ug = [&](int si) {
+    const double* ug = a.Ug + (si < nmy ? (gs0 + w + (int64_t)si * NW) * 16 : 0) * NP;
+    const uint32_t ln = opaque((uint32_t)lane);
+    const char* ub = reinterpret_cast<const char*>(ug);
+    const uint32_t oa = (ln & 15) * (NP * 8) + (ln >> 4) * 8, ob = ln * 8;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      ugA[q] = *reinterpret_cast<const double*>(ub + oa + 32 * q);
+      ugB[q] = *reinterpret_cast<const double*>(ub + ob + 4 * q * NP * 8);
+    }
+  };
+  // Basis rows of a tile (T x Np doubles, contiguous): thread tid takes row tid / 8, the
+  // pairs tid % 8 + 8 j, j < Np / 16 <= PF (a piece past the row re-reads its last one)
+  const int mt = Np / 16;
+  pair_t pf[PF];
+  auto fetch_phi = [&](pair_t& d, int j, int64_t rt) {
+    const char* src = reinterpret_cast<const char*>(a.Phir + rt * T * Np) + 128 * min(j, mt - 1);
+    const uint32_t t = opaque((uint32_t)tid);
+    d = *reinterpret_cast<const pair_t*>(src + (t >> 3) * (uint32_t)(Np * 8) + (t & 7) * 16);
+  };
+
+  d4_t m2[NMY];               // M2[g0 + 4r + lq][l16] of the wave's subtiles
+#pragma unroll
+  for (int si = 0; si < NMY; ++si) m2[si] = zero_d4();
+  d4_t k1 = zero_d4();        // K1[16 w + 4r + lq][l16]
+
+#pragma unroll
+  for (int j = 0; j < PF; ++j) fetch_phi(pf[j], j, rt0);
+  // in the order the tile loop leaves them: its waits then count alike on both ways in
+  asm volatile("" ::: "memory");
+  load_v(vb[0], rt0, 0);
+  asm volatile("" ::: "memory");
+  load_ug(0);
+  asm volatile("" ::: "memory");
+  load_v(vb[1], rt0 + 1 / NMY, 1 % NMY);
+  asm volatile("" ::: "memory");
+
+  // fit-fit units (see fused_f32u_kernel), while the first loads are in flight
+  auto l3_unit = [&](int64_t u) {
+    const int64_t ys = u / nsub3, hc = u % nsub3;
+    const int64_t y0 = ys * 16;
+    d4_t pt = zero_d4();
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) pt = mfma_f64(l3ha[kk], l3ya[kk], pt);
+    d4_t yacc = zero_d4();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) yacc = mfma_f64(l3w[r] * pt[r], l3hb[r], yacc);
+    double* yo = a.Yneg + (hc * a.G + y0) * NP;
+    double e = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      yo[(4 * r + lq) * NP + l16] = -yacc[r];
+      e += l3yr[r] * yacc[r];
+    }
+    e = wave_sum(e);
+    if (lane == 0) a.e3u[u] = e;
+  };
+  if (u3 < n3) l3_unit(u3);
+  for (u3 += (int64_t)gridDim.x * NW; u3 < n3; u3 += (int64_t)gridDim.x * NW) {
+    l3_load(u3);     // requested and used inside the round: none is pending in the tile loop's waits
+    l3_unit(u3);
+  }
+
+  auto tile = [&](auto tau, int64_t rt) {
+    constexpr int TAU = decltype(tau)::value;
+    const int64_t rn = rt + 1 < rt1 ? rt + 1 : rt;
+    __syncthreads();   // the previous tile is done with sPhi and m1s
+    // The addresses used once per tile are formed there from an opaque copy of the thread
+    // index: kept over the steps they spill, and a reload waits for every V in flight.
+    int ti = tid;
+    asm volatile("" : "+v"(ti));
+    double* dphi = sPhi + (ti >> 3) * PP + 2 * (ti & 7);
+#pragma unroll
+    for (int j = 0; j < PF; ++j)
+      if (j < mt) *reinterpret_cast<pair_t*>(dphi + 16 * j) = pf[j];
+    __syncthreads();
+    if (w < 4) {
+      // U rows 16 w .. 16 w + 15 in two accumulator chains
+      const int tl = ti & 15, tq = (ti >> 4) & 3;
+      const double* pa = sPhi + (16 * w + tl) * PP + tq;
+      const double* pb = sC + tq * NP + tl;
+      d4_t u0 = zero_d4(), u1 = zero_d4();
+      double xa[2][4], xb[2][4];       // operands of 16 basis functions, one block ahead
+      auto load_u = [&](double (&ua)[4], double (&ub)[4], int m) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          ua[q] = pa[16 * m + 4 * q];
+          ub[q] = pb[(16 * m + 4 * q) * NP];
+        }
+      };
+      load_u(xa[0], xb[0], 0);
+#pragma unroll
+      for (int m = 0; m < PF; ++m)
+        if (m < mt) {
+          if (m + 1 < PF) load_u(xa[(m + 1) & 1], xb[(m + 1) & 1], min(m + 1, mt - 1));
+#pragma unroll
+          for (int q = 0; q < 4; q += 2) {
+            u0 = mfma_f64(xa[m & 1][q], xb[m & 1][q], u0);
+            u1 = mfma_f64(xa[m & 1][q + 1], xb[m & 1][q + 1], u1);
+          }
+        }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sU[(16 * w + 4 * r + tq) * LDU + tl] = u0[r] + u1[r];
+    }
+    __syncthreads();
+
+    d4_t m1[4];               // M1^T, position 16 c + 4r + lq, column l16
+#pragma unroll
+    for (int c = 0; c < 4; ++c) m1[c] = zero_d4();
+#pragma unroll
+    for (int si = 0; si < NMY; ++si) {
+      const int b = (TAU * NMY + si) & 1;
+      double (&v)[4][4] = vb[b];
+      if (si < nmy) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          d4_t p0 = zero_d4(), p1 = zero_d4();
+          const double* u = sU + (32 * h + 2 * l16) * LDU + lq;
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) {
+            p0 = mfma_f64(ugA[kk], u[4 * kk], p0);
+            p1 = mfma_f64(ugA[kk], u[LDU + 4 * kk], p1);
+          }
+          double a0[4], a1[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            a0[r] = v[r][2 * h] * p0[r];
+            a1[r] = v[r][2 * h + 1] * p1[r];
+            *reinterpret_cast<double2*>(slab + (4 * r + lq) * SL2 + 32 * h + 2 * l16) = make_double2(a0[r], a1[r]);
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            m1[2 * h] = mfma_f64(a0[r], ugB[r], m1[2 * h]);
+            m1[2 * h + 1] = mfma_f64(a1[r], ugB[r], m1[2 * h + 1]);
+          }
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+      // requests of the coming steps, oldest need first
+      load_ug((si + 1) % NMY);
+#pragma unroll
+      for (int j = 0; j < PF; ++j)
+        if (j * (NMY > 1 ? NMY - 1 : 1) / PF == si) fetch_phi(pf[j], j, rn);   // none in the last step: older than its V
+      load_v(vb[b], rt + (si + 2) / NMY, (si + 2) % NMY);
+      asm volatile("" ::: "memory");   // keeps the requests above the products below
+      if (si < nmy) {
+        // M2 += A U over the tile's 64 rows; slice (j, e) takes rows 16 lq + 2 j + e
+        const double* as = slab + l16 * SL2 + 16 * lq;
+        const double* us = sU + 16 * lq * LDU + l16;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const double2 x = *reinterpret_cast<const double2*>(as + 2 * j);
+          m2[si] = mfma_f64(x.x, us[2 * j * LDU], m2[si]);
+          m2[si] = mfma_f64(x.y, us[(2 * j + 1) * LDU], m2[si]);
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+
+    if (a.want_k1) {
+      int tj = tid;
+      asm volatile("" : "+v"(tj));
+      const int tl = tj & 15, tq = (tj >> 4) & 3;
+      // M1^T of the tile: the waves' partials (each in its own slab) summed in order
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          slab[(32 * (c >> 1) + 2 * (4 * r + tq) + (c & 1)) * NP + tl] = m1[c][r];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int e = tj + 512 * i;
+        double s = 0.0;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) s += smem[ww * 16 * SL2 + e];
+        m1s[e] = s;
+      }
+      __syncthreads();
+      if (w < mt) {
+        const double* ph = sPhi + tq * PP + 16 * w + tl;
+#pragma unroll
+        for (int s0 = 0; s0 < 16; s0 += 8) {
+          double xa[8], xb[8];
+#pragma unroll
+          for (int s = 0; s < 8; ++s) {
+            xa[s] = ph[4 * (s0 + s) * PP];
+            xb[s] = m1s[(4 * (s0 + s) + tq) * NP + tl];
+          }
+#pragma unroll
+          for (int s = 0; s < 8; ++s) k1 = mfma_f64(xa[s], xb[s], k1);
+        }
+      }
+    }
+  };
+  // (an odd last tile by itself: a way from the first tile of a pair back to the loop's head
+  // would leave the V buffers in the other order there, and every pair would wait for all of V)
+  int64_t rt = rt0;
+  for (; rt + 1 < rt1; rt += 2) {
+    tile(std::integral_constant<int, 0>{}, rt);
+    tile(std::integral_constant<int, 1>{}, rt + 1);
+  }
+  if (rt < rt1) tile(std::integral_constant<int, 0>{}, rt);
+
+  if (a.want_k1 && w < mt) {
+    double* out = a.K1p + (int64_t)blockIdx.x * Np * NP;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[(int64_t)(16 * w + 4 * r + lq) * NP + l16] = k1[r];
+  }
+  double* out = a.M2p + (int64_t)rb * a.G * NP;
+#pragma unroll
+  for (int si = 0; si < NMY; ++si)
+    if (si < nmy) {
+      const int64_t g0 = (gs0 + w + si * NW) * 16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(g0 + 4 * r + lq) * NP + l16] = m2[si][r];
     }
 }
 
@@ -1367,6 +1693,19 @@ hipError_t launch_f32u(const FusedArgs& a, int blocks, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int NMY>
+hipError_t launch_f64u(const FusedArgs& a, int blocks, hipStream_t s) {
+  // basis pieces per thread: Np / 16, rounded up to a compiled count
+  const int pf = a.Np <= 64 ? 4 : a.Np <= 112 ? 7 : 8;
+  const int64_t lds = ((int64_t)8 * 16 * SL2 + (int64_t)T * (16 * pf + 2) + (int64_t)a.Np * 16 + (int64_t)T * 17) * 8;
+  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  auto k = pf == 4 ? fused_f64u_kernel<NMY, 4> : pf == 7 ? fused_f64u_kernel<NMY, 7> : fused_f64u_kernel<NMY, 8>;
+  hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(512), (size_t)lds, s, a);
+  return hipGetLastError();
+}
+
 template <int NW>
 hipError_t launch_f32_mt(const FusedArgs& a, int blocks, hipStream_t s) {
   const int mt = a.want_k1 ? a.Np / 16 : 0;
@@ -1406,7 +1745,18 @@ hipError_t launch_fused1(const FusedArgs& a, int blocks, hipStream_t s) {
     if (a.nwaves == 8) return launch_m4_mt<8, 0>(a, blocks, s);
     return launch_m4_mt<4, 0>(a, blocks, s);
   }
-  if (a.nwaves == 8) return launch_fused2<8, NI>(a, blocks, s);
+  if (NI == 1 && a.Cm) {
+    // FP64, orbitals formed in the kernel: M2 (and K1), energy from M2
+    if (!a.want_m2 || a.want_m1 || a.want_e || a.nwaves != 8 || a.Np > 128) return hipErrorInvalidValue;
+    switch (fused_f32u_nmy(a)) {
+      case 1: return launch_f64u<1>(a, blocks, s);
+      case 2: return launch_f64u<2>(a, blocks, s);
+      case 3: return launch_f64u<3>(a, blocks, s);
+      case 4: return launch_f64u<4>(a, blocks, s);
+      case 5: return launch_f64u<5>(a, blocks, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
   return launch_fused2<4, NI>(a, blocks, s);
 }
 

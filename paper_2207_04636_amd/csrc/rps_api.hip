@@ -120,6 +120,7 @@ struct rps_context {
   DBuf<unsigned> ecount;   // last-block counter of the finalize kernel's energy sum (zero between builds)
   int64_t rblocks_main = 0, blocks_main = 0, blocks_l3 = 0;
   int rtiles = 4, gblocks = 1, nwaves = 4;
+  bool fused_fold = false;   // fit-fit line folded into the fused kernel
   // Coulomb matrix: kernel table k(G) / N_g kept from the set-up, and workspace
   DBuf<double> kern;
   int jws_np = -1;
@@ -981,19 +982,27 @@ void prof_mark(rps_context& c, int slot, hipStream_t st) {
 // basis is stored (N <= 128).
 bool uses_f32u(const rps_context& c, int np) { return c.Phi32.p && np == 16; }
 
+// FP64 with n <= 16 (N <= 128 on the fused path) forms them in its kernel too, unless
+// the 4x4x4 instruction is asked for (grids of 2^27 points and more, beyond its 32-bit
+// lane offsets, keep the kernel that reads U from memory).
+bool uses_f64u(const rps_context& c, int np) {
+  return c.precision == RPS_PREC_FP64 && np == 16 && !c.use_m4 && c.Np <= 128 && c.ngp < (1ll << 27);
+}
+
 void choose_shape(rps_context& c, int np, FusedArgs& a) {
-  a.nwaves = (np == 16) ? 8 : 4;
+  a.nwaves = (np == 16 && (c.precision != RPS_PREC_FP64 || c.use_m4 || uses_f64u(c, np))) ? 8 : 4;
   a.np = np;
   a.G = c.nauxp;
   a.want_m2 = 1;
   const int64_t lds_cap = 160 * 1024;
   const int64_t gt = c.nauxp / 64;
-  const bool f32u = uses_f32u(c, np);
-  // the in-kernel-orbitals kernel holds M2 in registers (at most 8 g subtiles per
-  // wave); the others hold this workgroup's M2 block in LDS
+  const bool f32u = uses_f32u(c, np), f64u = uses_f64u(c, np);
+  // the in-kernel-orbitals kernels hold M2 in registers; the others hold this
+  // workgroup's M2 block in LDS
   a.Np = (int)c.Np;
   auto fits = [&](const FusedArgs& t) {
-    // (the in-kernel-orbitals kernel stays within its registers up to 5 subtiles per wave)
+    // (the in-kernel-orbitals kernels stay within their registers up to 5 subtiles per wave)
+    if (f64u) return fused_f32u_nmy(t) <= 5;
     return f32u ? (fused_f32u_nmy(t) <= 5 && fused_f32u_lds(t) <= lds_cap) : fused_lds_bytes(t) <= lds_cap;
   };
   a.gblocks = 1;
@@ -1037,11 +1046,11 @@ void ensure_energy_parts(rps_context& c) {
 struct FusedPlan {
   int rtiles, gblocks, nwaves;
   int64_t rblocks_main, blocks_main, blocks_l3;
-  bool f32u, m4;
+  bool f32u, inner, fold, m4;   // orbitals formed in the kernel; fit-fit line folded into it (rPS variant)
   int64_t nU, nUg, nUgp, nM2p, ne3u, nK1p, nK3p, ne1p, ne3p, nM2, nK1, nK3;
 };
 
-FusedPlan fused_plan(rps_context& c, int np) {
+FusedPlan fused_plan_fold(rps_context& c, int np, bool fold) {
   FusedPlan p{};
   FusedArgs a{};
   a.R_valid = c.ng;
@@ -1053,14 +1062,16 @@ FusedPlan fused_plan(rps_context& c, int np) {
   p.blocks_main = p.rblocks_main * p.gblocks;
   p.blocks_l3 = (c.nauxp / 64) * ((c.naux + 63) / 64);   // one 64 x 64 tile of W per workgroup
   p.f32u = uses_f32u(c, np);
+  p.inner = p.f32u || uses_f64u(c, np);
+  p.fold = p.inner && fold;
   p.m4 = (np == 16) && c.use_m4;
   const int64_t nsub = c.nauxp / 16;
   p.nU = c.ngp * np;
   p.nUg = c.nauxp * np;
   p.nUgp = c.nauxp * np;
   // M2 partials, followed by the negated fit-fit partials of the in-kernel-orbitals kernel
-  p.nM2p = (p.rblocks_main + (p.f32u ? nsub : 0)) * c.nauxp * np;
-  p.ne3u = p.f32u ? nsub * nsub : 1;
+  p.nM2p = (p.rblocks_main + (p.fold ? nsub : 0)) * c.nauxp * np;
+  p.ne3u = p.fold ? nsub * nsub : 1;
   p.nK1p = p.blocks_main * c.Np * np;
   p.nK3p = std::max<int64_t>(p.blocks_l3, 1) * c.Np * np;
   p.ne1p = p.blocks_main;
@@ -1081,6 +1092,44 @@ struct FusedWs {
   unsigned* ecount = nullptr;
 };
 
+// Carve the workspace of plan p from base (256-byte aligned pieces); returns the
+// doubles used (the caller checks them against the scratch size before use).
+int64_t carve_fused_ws(const FusedPlan& p, double* base, FusedWs& w) {
+  int64_t off = 0;
+  auto take = [&](int64_t n) {
+    double* q = base ? base + off : nullptr;
+    off += (n + 31) / 32 * 32;
+    return q;
+  };
+  w.plan = p;
+  w.U = p.f32u ? nullptr : take(p.nU);      // (FP64: the scratch limit stays where it was before U moved into the kernel)
+  w.Ug = take(p.nUg);
+  w.Ugp = p.m4 ? take(p.nUgp) : nullptr;
+  w.M2p = take(p.nM2p);
+  w.e3u = take(p.ne3u);
+  w.K1p = take(p.nK1p);
+  w.K3p = take(p.nK3p);
+  w.e1p = take(p.ne1p);
+  w.e3p = take(p.ne3p);
+  w.M2 = take(p.nM2);
+  w.K1 = take(p.nK1);
+  w.K3 = take(p.nK3);
+  w.epart = take(kEnergyBlocks);
+  w.ecount = reinterpret_cast<unsigned*>(take(32));
+  return off;
+}
+
+// The fit-fit line is folded into the in-kernel-orbitals kernels; the FP64 one leaves it
+// to its own kernel when the folded form's partials ((N_aux/16) N_aux n more) would not
+// fit the no-allocation entry point's scratch.
+FusedPlan fused_plan(rps_context& c, int np) {
+  const FusedPlan p = fused_plan_fold(c, np, true);
+  FusedWs w;
+  if (p.fold && !p.f32u && carve_fused_ws(p, nullptr, w) * 8 > kNoAllocScratchBytes)
+    return fused_plan_fold(c, np, false);
+  return p;
+}
+
 void ensure_workspace(rps_context& c, int np) {
   if (c.ws_np == np) return;
   c.clear_graphs();          // captured builds refer to the buffers about to change
@@ -1094,6 +1143,7 @@ void ensure_workspace(rps_context& c, int np) {
   c.rblocks_main = p.rblocks_main;
   c.blocks_main = p.blocks_main;
   c.blocks_l3 = p.blocks_l3;
+  c.fused_fold = p.fold;
   c.U.alloc(p.nU, cnt);
   c.Ug.alloc(p.nUg, cnt);
   c.Ugp.alloc(p.nUgp, cnt);
@@ -1116,6 +1166,8 @@ void ensure_workspace(rps_context& c, int np) {
 FusedWs context_ws(rps_context& c, int np) {
   FusedWs w;
   w.plan.f32u = uses_f32u(c, np);
+  w.plan.inner = w.plan.f32u || uses_f64u(c, np);
+  w.plan.fold = c.fused_fold;
   w.plan.m4 = (np == 16) && c.use_m4;
   w.plan.rtiles = c.rtiles;
   w.plan.gblocks = c.gblocks;
@@ -1556,18 +1608,18 @@ void enqueue_fused(rps_context& c, const FusedWs& w, int variant, int32_t nocc, 
   if (variant == RPS_VARIANT_PS) { s1 = 0; s2 = 1; s3 = 0; ce1 = 1; ce3 = 0; }
   if (variant == RPS_VARIANT_THC) { s1 = 0; s2 = 0; s3 = 1; ce1 = 0; ce3 = 1; }
   // U = Phi C (orbitals on the grid) and U_g = Phi_g C (at the points); the
-  // in-kernel-orbitals precision kernel needs U_g only
+  // in-kernel-orbitals kernels need U_g only
   const bool m4 = w.plan.m4;
-  const bool f32u = w.plan.f32u;
+  const bool inner = w.plan.inner;
   c.last_arith = (c.precision == RPS_PREC_FP64) ? RPS_PREC_FP64 : RPS_PREC_FP32;   // fused kernels: FP32 products
-  hip_check(orbitals(c.Phi.p, f32u ? 0 : c.ngp, c.Phig.p, c.nauxp, (int)c.Np, Csrc, (int)c.nbas, nocc, np, w.U,
+  hip_check(orbitals(c.Phi.p, inner ? 0 : c.ngp, c.Phig.p, c.nauxp, (int)c.Np, Csrc, (int)c.nbas, nocc, np, w.U,
                      w.Ug, m4 ? w.Ugp : nullptr, st),
             "orbitals");
   const bool need_main = (variant != RPS_VARIANT_THC);
   const bool need_l3 = (variant != RPS_VARIANT_PS);
-  // the in-kernel-orbitals kernel also forms the fit-fit line, as negated partials after
+  // the in-kernel-orbitals kernels also form the fit-fit line, as negated partials after
   // the M2 partials (their ordered sum is then M2 - Y; the rPS variant only)
-  const bool l3_in_main = f32u && variant == RPS_VARIANT_RPS;
+  const bool l3_in_main = w.plan.fold && variant == RPS_VARIANT_RPS;
   const int64_t nsub = c.nauxp / 16;
   if (need_main) {
     FusedArgs a{};
@@ -1579,7 +1631,7 @@ void enqueue_fused(rps_context& c, const FusedWs& w, int variant, int32_t nocc, 
     a.prec = c.precision;
     a.Vm32 = (c.precision != RPS_PREC_FP64) ? c.V32.p : nullptr;
     a.Ugp = m4 ? w.Ugp : nullptr; a.use_m4 = m4 ? c.use_m4 : 0;
-    if (f32u) { a.Phi32 = c.Phi32.p; a.Cm = Csrc; a.N = (int)c.nbas; a.n = nocc; }
+    if (inner) { a.Phi32 = c.Phi32.p; a.Cm = Csrc; a.N = (int)c.nbas; a.n = nocc; }
     if (l3_in_main) {
       a.Wl = c.W.p; a.ldw = c.nauxp;
       a.Yneg = w.M2p + w.plan.rblocks_main * c.nauxp * np; a.e3u = w.e3u;
@@ -2137,33 +2189,6 @@ void autotune(rps_context& c, int32_t nocc, const double* C, double* K, double* 
 }
 
 // ------------------------------------------------------------------ no-allocation build (continued)
-// Carve the workspace of plan p from base (256-byte aligned pieces); returns the
-// doubles used (the caller checks them against the scratch size before use).
-int64_t carve_fused_ws(const FusedPlan& p, double* base, FusedWs& w) {
-  int64_t off = 0;
-  auto take = [&](int64_t n) {
-    double* q = base ? base + off : nullptr;
-    off += (n + 31) / 32 * 32;
-    return q;
-  };
-  w.plan = p;
-  w.U = p.f32u ? nullptr : take(p.nU);      // the in-kernel-orbitals kernel forms U itself
-  w.Ug = take(p.nUg);
-  w.Ugp = p.m4 ? take(p.nUgp) : nullptr;
-  w.M2p = take(p.nM2p);
-  w.e3u = take(p.ne3u);
-  w.K1p = take(p.nK1p);
-  w.K3p = take(p.nK3p);
-  w.e1p = take(p.ne1p);
-  w.e3p = take(p.ne3p);
-  w.M2 = take(p.nM2);
-  w.K1 = take(p.nK1);
-  w.K3 = take(p.nK3);
-  w.epart = take(kEnergyBlocks);
-  w.ecount = reinterpret_cast<unsigned*>(take(32));
-  return off;
-}
-
 void build_noalloc_impl(rps_context& c, int32_t nocc, const double* C, double* K, double* ex, hipStream_t st) {
   if (c.ng == 0) fail(RPS_ERR_STATE, "context has no completed set-up");
   if (nocc < 1) fail(RPS_ERR_ARG, "nocc must be >= 1");

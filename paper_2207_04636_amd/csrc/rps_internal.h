@@ -242,8 +242,8 @@ struct FusedArgs {
   int want_m1;              // write M1^T = A^T Ug rows (when K1 is not fused)
   int want_e;               // accumulate sum A o P into e1p (else the caller forms it from M2)
   int prec;                 // rps_precision
-  // precision form with the orbitals of each R tile formed in the kernel (NULL Phi32: U from Ur)
-  const float* Phi32;       // [Rp x Np] FP32 basis values
+  // orbitals of each R tile formed in the kernel (n <= 16; NULL Cm: U from Ur)
+  const float* Phi32;       // [Rp x Np] FP32 basis values (precision form; FP64 reads Phir)
   const double* Cm;         // [N x n] occupied coefficients (row pitch n)
   int N, n;
   // fit-fit line folded into that kernel (Wl NULL: not computed).  Unit (g subtile ys,
@@ -260,8 +260,8 @@ struct FusedArgs {
   double* e1p;              // [gblocks*rblocks]
 };
 int fused_rblocks(const FusedArgs& a);
-// g subtiles per wave of the in-kernel-orbitals precision kernel (Phi32 set; at most 8)
-// and its LDS bytes (at most 160 KiB).
+// g subtiles per wave of the in-kernel-orbitals kernels (precision form at most 8, FP64 at
+// most 5) and the LDS bytes of the precision one (at most 160 KiB).
 int64_t fused_f32u_nmy(const FusedArgs& a);
 int64_t fused_f32u_lds(const FusedArgs& a);
 int64_t fused_lds_bytes(const FusedArgs& a);

@@ -243,3 +243,45 @@ def test_coulomb_small_basis(lib, nfunc, mesh):
     assert np.abs(J - Jref).max() < 1e-11 * np.abs(Jref).max()
     assert abs(E - Eref) < 1e-11 * abs(Eref)
     assert np.array_equal(J, J2) and E == E2
+
+
+# ---- FP64 exchange with n <= 16: orbitals formed in the V-streaming kernel, fit-fit line folded in
+@pytest.mark.parametrize("w,nocc,shape", [
+    (_s_cell(1, (4, 4, 4), 1), 1, None),                                  # one tile of everything
+    (dataclasses.replace(_s_cell(17, (5, 7, 9), 3), naux=40), 3, None),   # ragged last grid tile
+    (dataclasses.replace(_s_cell(64, (9, 8, 8), 16), naux=128), 16, None),
+    (dataclasses.replace(_s_cell(128, (16, 15, 12), 15), naux=160), 15, None),
+    (ri.diamond_supercell((1, 1, 1), (16, 17, 18), 2, naux=192), 16, None),      # 1.5 g subtiles per wave
+    (ri.diamond_supercell((1, 1, 1), (16, 17, 18), 2, naux=448), 9, "3,1"),      # 4, odd number of R tiles
+    (ri.diamond_supercell((1, 1, 1), (16, 17, 18), 2, naux=640), 16, "2,1"),     # 5
+    (ri.diamond_supercell((1, 1, 1), (16, 17, 18), 2, naux=704), 16, None),      # two uneven g blocks
+    (ri.diamond_supercell((1, 1, 1), (16, 17, 18), 2, naux=320), 13, "2,4"),     # the last g block empty
+    (ri.diamond_supercell((1, 1, 1), (28, 35, 32), 2, naux=704), 11, "1,2"),    # line 3 in its own kernel (scratch)
+])
+def test_fused_fp64_orbitals_in_kernel(lib, w, nocc, shape, monkeypatch):
+    """All three variants and the no-allocation build against the 4x4x4-instruction kernels,
+    which read U from memory and form the fit-fit line by themselves (same points, same V)."""
+    import torch
+    if shape:
+        monkeypatch.setenv("RPS_FUSED_SHAPE", shape)
+    w = dataclasses.replace(w, nocc=nocc)
+    C = _coefficients(w, seed=nocc)
+    variants = (lib.VARIANT_RPS, lib.VARIANT_PS, lib.VARIANT_THC)
+    with lib.Context.from_workload(w, seed=w.sketch_seed()) as ctx:
+        pts = ctx.points()
+        got = [ctx.build(C, variant=v) for v in variants]
+        again = ctx.build(C)
+        Cd = torch.from_numpy(C).cuda()
+        Kd = torch.empty_like(Cd)
+        ed = torch.zeros(1, dtype=torch.float64, device="cuda")
+        ctx.build_noalloc(Cd, Kd, ed)
+        torch.cuda.synchronize()
+        assert np.array_equal(Kd.cpu().numpy(), got[0][0]) and float(ed[0]) == got[0][1]
+    monkeypatch.setenv("RPS_FP64_MFMA", "m4")
+    with lib.Context.from_workload(w, points=pts) as ctx:
+        ref = [ctx.build(C, variant=v) for v in variants]
+    assert np.array_equal(again[0], got[0][0]) and again[1] == got[0][1]
+    for (K, E), (Kr, Er), v in zip(got, ref, variants):
+        dk = np.abs(K - Kr).max() / np.abs(Kr).max()
+        _say(f"case: FP64 fused N={w.nbas} n={nocc} N_aux={w.naux} variant {v} dE={E - Er:.2e} dK={dk:.2e}")
+        assert dk < 1e-11 and abs(E - Er) < 1e-11 * abs(Er)
