@@ -1376,9 +1376,20 @@ __global__ __launch_bounds__(256) void orbitals_kernel(const double* __restrict_
   const int64_t sfirst = (int64_t)blockIdx.x * 4 + w, sstep = (int64_t)gridDim.x * 4;
   // the first block of basis values is in flight while C is staged
   if (sfirst < nsub) fetch(sfirst);
-  for (int e = tid; e < NPK * NP; e += 256) {
-    const int r = e / NP, c = e % NP;
-    sC[e] = (r < N && c < n) ? C[(int64_t)r * n + c] : 0.0;
+  // (eight loads of C in flight per thread: one at a time they took most of the launch when
+  // only the points' rows are formed, 7.5 us against 5.5 for 640 rows of 104 functions)
+  for (int e0 = tid; e0 < NPK * NP; e0 += 8 * 256) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = e0 + u * 256, r = e / NP, c = e % NP;
+      v[u] = C[(r < N && c < n) ? r * n + c : 0];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = e0 + u * 256, r = e / NP, c = e % NP;
+      if (e < NPK * NP) sC[e] = (r < N && c < n) ? v[u] : 0.0;
+    }
   }
   __syncthreads();
   for (int64_t sidx = sfirst; sidx < nsub; sidx += sstep) {
@@ -1454,7 +1465,17 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceArgs ra) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; p < sg.nparts; p += 16) s += sg.in[p * sg.count + i];
+    if (sg.nparts - (p - q) > 48) {
+      // a long rest in one predicated round (1.3 us less with 216 partials); a short one
+      // (few partials, many outputs) would pay for the loads it does not need
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = sg.in[min(p + 16 * u, sg.nparts - 1) * sg.count + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += (p + 16 * u < sg.nparts) ? v[u] : 0.0;
+    } else {
+      for (; p < sg.nparts; p += 16) s += sg.in[p * sg.count + i];
+    }
   }
   red[q][x] = s;
   __syncthreads();
@@ -1470,8 +1491,12 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceArgs ra) {
 // K[16m.., 16j..]: it forms K2 = Phi_g^T M2 for the tile on the matrix cores
 // with the inner dimension split over the 8 waves (fixed-order reduction) and
 // writes K = dV (s1 K1 + s2 K2 + s3 K3) for mu < N, i < n.  The last workgroup
-// sums the energy partials with a fixed tree.
-__global__ __launch_bounds__(512) void finalize_kernel(const double* __restrict__ Phig, const double* __restrict__ M2,
+// sums the energy partials with a fixed tree.  Small cells see the latency of a few
+// rounds of loads, so every loop keeps its loads in flight together.  (16 waves per
+// tile: no faster there, and 5% on a batch of larger cells lost.)
+constexpr int FT = 512;       // threads of a finalize workgroup
+constexpr int FW = FT / 64;
+__global__ __launch_bounds__(FT, 8) void finalize_kernel(const double* __restrict__ Phig, const double* __restrict__ M2,
                                                       int64_t G, const double* __restrict__ K1,
                                                       const double* __restrict__ K3, int N, int n,
                                                       int np, int Np, double s1, double s2, double s3, double dV,
@@ -1479,7 +1504,7 @@ __global__ __launch_bounds__(512) void finalize_kernel(const double* __restrict_
                                                       int64_t ne1, const double* __restrict__ e3p, int64_t ne3,
                                                       double ce1, double ce3, double* __restrict__ ex,
                                                       EnergyDots dots) {
-  __shared__ double red[8][64][4];
+  __shared__ double red[FW][64][4];
   __shared__ int last_blk;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int l16 = lane & 15, lq = lane >> 4;
@@ -1496,20 +1521,31 @@ __global__ __launch_bounds__(512) void finalize_kernel(const double* __restrict_
     };
     double sa = 0.0, sb = 0.0;
     int64_t b0, b1;
-    slice(ne1, b0, b1);
-    for (int64_t p = b0 + tid; p < b1; p += 512) sa += e1p[p];
-    slice(ne3, b0, b1);
-    for (int64_t p = b0 + tid; p < b1; p += 512) sb += e3p[p];
-    slice(dots.n1, b0, b1);
-#pragma unroll 8
-    for (int64_t p = b0 + tid; p < b1; p += 512) sa += dots.x1[p] * dots.y1[p];
-    slice(dots.n3, b0, b1);
-#pragma unroll 4
-    for (int64_t p = b0 + tid; p < b1; p += 512) sb += dots.x3[p] * dots.y3[p];
+    // sum of x (o y) over the block's slice, eight terms per thread in flight
+    auto sum = [&](const double* x, const double* y, int64_t n, double acc) {
+      slice(n, b0, b1);
+      for (int64_t p = b0 + tid; p < b1; p += 8 * FT) {
+        double u[8], v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int64_t q = min(p + k * FT, b1 - 1);
+          u[k] = x[q];
+          v[k] = y ? y[q] : 1.0;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (p + k * FT < b1) acc += u[k] * v[k];
+      }
+      return acc;
+    };
+    sa = sum(e1p, nullptr, ne1, sa);
+    sb = sum(e3p, nullptr, ne3, sb);
+    sa = sum(dots.x1, dots.y1, dots.n1, sa);
+    sb = sum(dots.x3, dots.y3, dots.n3, sb);
     double* r1 = &red[0][0][0];
     r1[tid] = ce1 * sa + ce3 * sb;
     __syncthreads();
-    for (int off = 256; off > 0; off >>= 1) {
+    for (int off = FT / 2; off > 0; off >>= 1) {
       if (tid < off) r1[tid] += r1[tid + off];
       __syncthreads();
     }
@@ -1527,11 +1563,11 @@ __global__ __launch_bounds__(512) void finalize_kernel(const double* __restrict_
       if (last_blk) {
         __threadfence();
         double v = 0.0;
-        for (int i = tid; i < neb; i += 512)
+        for (int i = tid; i < neb; i += FT)
           v += __hip_atomic_load(dots.part + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         r1[tid] = v;
         __syncthreads();
-        for (int off = 256; off > 0; off >>= 1) {
+        for (int off = FT / 2; off > 0; off >>= 1) {
           if (tid < off) r1[tid] += r1[tid + off];
           __syncthreads();
         }
@@ -1545,22 +1581,31 @@ __global__ __launch_bounds__(512) void finalize_kernel(const double* __restrict_
   }
   const int m = blockIdx.x / (np / 16), j = blockIdx.x % (np / 16);
   d4_t acc = zero_d4();
+  double kadd[4] = {0.0, 0.0, 0.0, 0.0};       // s1 K1 + s3 K3, requested with the first operands
+  if (w == 0)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t q = (int64_t)(16 * m + 4 * r + lq) * np + 16 * j + l16;
+      if (K1) kadd[r] += s1 * K1[q];
+      if (K3) kadd[r] += s3 * K3[q];
+    }
   if (M2) {
     // wave w takes the k slices sl = w + 8 q (G is a multiple of 64), sixteen at a time
     // with all their loads in flight together (clamped, unconditional; slices past the
     // end contribute zero)
-    const int64_t per = G / 32;
-    for (int64_t q0 = 0; q0 < per; q0 += 16) {
-      double a[16], b[16];
+    constexpr int NQ = 16;
+    const int64_t per = G / (4 * FW);
+    for (int64_t q0 = 0; q0 < per; q0 += NQ) {
+      double a[NQ], b[NQ];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
+      for (int u = 0; u < NQ; ++u) {
         const int64_t q = (q0 + u < per) ? q0 + u : per - 1;
-        const int64_t g = 4 * (w + 8 * q) + lq;
+        const int64_t g = 4 * (w + FW * q) + lq;
         a[u] = Phig[g * Np + 16 * m + l16];
         b[u] = M2[g * np + 16 * j + l16];
       }
 #pragma unroll
-      for (int u = 0; u < 16; ++u) acc = mfma_f64(a[u], (q0 + u < per) ? b[u] : 0.0, acc);
+      for (int u = 0; u < NQ; ++u) acc = mfma_f64(a[u], (q0 + u < per) ? b[u] : 0.0, acc);
     }
   }
 #pragma unroll
@@ -1570,13 +1615,9 @@ __global__ __launch_bounds__(512) void finalize_kernel(const double* __restrict_
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       double s = 0.0;
-      for (int ww = 0; ww < 8; ++ww) s += red[ww][lane][r];
+      for (int ww = 0; ww < FW; ++ww) s += red[ww][lane][r];
       const int mu = 16 * m + 4 * r + lq, i = 16 * j + l16;
-      const int64_t q = (int64_t)mu * np + i;
-      double v = s2 * s;
-      if (K1) v += s1 * K1[q];
-      if (K3) v += s3 * K3[q];
-      if (mu < N && i < n) K[(int64_t)mu * n + i] = dV * v;
+      if (mu < N && i < n) K[(int64_t)mu * n + i] = dV * (s2 * s + kadd[r]);
     }
   }
 }
@@ -1864,7 +1905,7 @@ hipError_t finalize(const double* Phig, const double* M2, int64_t G, const doubl
   const int64_t nterms = dots.n1 + dots.n3 + ne1 + ne3;
   int neb = (nterms <= 16384) ? 1 : (int)std::min<int64_t>((nterms + 4095) / 4096, dots.part ? dots.nparts : 1);
   if (neb < 1) neb = 1;
-  hipLaunchKernelGGL(finalize_kernel, dim3(ntile + neb), dim3(512), 0, s, Phig, M2, G, K1, K3, N, n, np, Np, s1, s2,
+  hipLaunchKernelGGL(finalize_kernel, dim3(ntile + neb), dim3(FT), 0, s, Phig, M2, G, K1, K3, N, n, np, Np, s1, s2,
                      s3, dV, K, e1p, ne1, e3p, ne3, ce1, ce3, ex, dots);
   if (neb > 1 && ex && !dots.count)
     hipLaunchKernelGGL(energy_sum_kernel, dim3(1), dim3(256), 0, s, dots.part, neb, dV, ex);
