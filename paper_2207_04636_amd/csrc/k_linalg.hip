@@ -2,11 +2,11 @@
 //
 // * Cholesky factorisation of the fitting metric X_gg (Sec. 4.3 solves the
 //   least-squares fit of Sec. 3.1, Eq. 11, with a Cholesky factorisation):
-//   blocked right-looking, 64-column panels factored in LDS, the block column
+//   blocked right-looking, 64-column panels factored by one wave, the block column
 //   below by substitution, the trailing matrix by the FP64 MFMA product.
 // * Triangular solves with many right-hand sides (the N_g columns of X_gR, or
-//   the N_chi columns when forming W): 64-row diagonal blocks by substitution,
-//   one thread per right-hand side, the rest by matrix products.
+//   the N_chi columns when forming W): 64-row diagonal blocks by one wave per
+//   16 right-hand sides, the rest by matrix products.
 // * Pivoted Cholesky of an explicit Gram matrix.  QR with column pivoting of a
 //   matrix M (Sec. 3.1, 4.3) picks as pivot k the column whose norm, after
 //   projecting out the columns picked before, is largest.  That residual norm
@@ -17,6 +17,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "mfma.h"
 #include "rps_internal.h"
@@ -26,77 +27,118 @@ namespace {
 
 constexpr int NB = 64;
 
-__global__ __launch_bounds__(256) void chol_panel_kernel(double* A, int64_t lda, int64_t k0, int32_t* status) {
-  __shared__ double L[NB][NB + 1];
-  __shared__ double piv;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < NB * NB; e += 256) {
-    const int i = e / NB, j = e % NB;
-    L[i][j] = (j <= i) ? A[(k0 + i) * lda + k0 + j] : 0.0;
-  }
-  __syncthreads();
-  for (int j = 0; j < NB; ++j) {
-    if (tid == 0) {
-      double d = L[j][j];
+// One wave factors the 64 x 64 block with row i in lane i's registers.  The kernel is one
+// serial chain (a square root, a quotient and a rank-1 update per column); nothing but its
+// latency counts, so no barrier stands in it: column j goes round through LDS and every
+// lane updates its row with 64 - j independent products.  A workgroup of 256 with the block
+// in LDS and three barriers per column took 99 us.
+__global__ __launch_bounds__(64) void chol_panel_kernel(double* A, int64_t lda, int64_t k0, int32_t* status) {
+  __shared__ __align__(16) double col[NB];
+  const int lane = threadIdx.x;
+  double* row = A + (k0 + lane) * lda + k0;
+  double x[NB];               // entries past the diagonal are never stored
+#pragma unroll
+  for (int j = 0; j < NB; ++j) x[j] = row[j];
+  auto columns = [&](auto jb) {          // columns 16 jb .. 16 jb + 15
+    constexpr int J0 = 16 * decltype(jb)::value;
+#pragma unroll
+    for (int jj = 0; jj < 16; ++jj) {
+      const int j = J0 + jj;
+      double d = __shfl(x[j], j, 64);
       if (!(d > 0.0)) {
-        if (status[0] == 0) status[0] = (int32_t)(1 + k0 + j);
+        if (lane == 0 && status[0] == 0) status[0] = (int32_t)(1 + k0 + j);
         d = 1.0;
       }
-      piv = sqrt(d);
-      L[j][j] = piv;
+      const double piv = sqrt(d);
+      x[j] = (lane == j) ? piv : x[j] / piv;
+      col[lane] = x[j];
+      __builtin_amdgcn_wave_barrier();
+      double c[NB - J0];
+#pragma unroll
+      for (int u = 0; u < NB - J0; ++u) c[u] = col[J0 + u];
+#pragma unroll
+      for (int u = jj + 1; u < NB - J0; ++u) x[J0 + u] -= x[j] * c[u];
+      // (done here: put off to their uses the products would keep every c alive)
+#pragma unroll
+      for (int u = jj + 1; u < NB - J0; ++u) asm volatile("" : "+v"(x[J0 + u]));
+      __builtin_amdgcn_wave_barrier();
     }
-    __syncthreads();
-    for (int i = j + 1 + tid; i < NB; i += 256) L[i][j] /= piv;
-    __syncthreads();
-    for (int e = tid; e < NB * NB; e += 256) {
-      const int i = e / NB, k = e % NB;
-      if (i > j && k > j && k <= i) L[i][k] -= L[i][j] * L[k][j];
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < NB * NB; e += 256) {
-    const int i = e / NB, j = e % NB;
-    if (j <= i) A[(k0 + i) * lda + k0 + j] = L[i][j];
-  }
+  };
+  columns(std::integral_constant<int, 0>{});
+  columns(std::integral_constant<int, 1>{});
+  columns(std::integral_constant<int, 2>{});
+  columns(std::integral_constant<int, 3>{});
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+    if (j <= lane) row[j] = x[j];
 }
 
-// Solve a 64-vector v against the 64x64 lower triangle Ls (in LDS):
-// TRANS = false: L x = v (forward), TRANS = true: L^T x = v (backward).
-// Vector v number t has component j at base[t*sv + j*sj].
+// Solve 64-vectors v against the 64x64 lower triangle L: TRANS = false: L x = v
+// (forward), TRANS = true: L^T x = v (backward).  Vector v number t has component j at
+// base[t*sv + j*sj].  A wave takes 16 vectors, component 16 b + 4 r + lane / 16 of vector
+// lane % 16 in x[b][r]: this is at once the result and the operand layout of the FP64
+// matrix instruction, so the six 16 x 16 blocks off the diagonal are matrix products on
+// registers.  The four on it are substitutions: component i goes round by a lane
+// permutation, every lane divides, and subtracts it from the components it holds.  What is
+// left is the latency of 64 such steps; two waves per SIMD share it at 32768 vectors.
+// (One vector per thread, each component a chain of products over those before it, was
+// 2016 dependent operations at one wave per SIMD: 49 us there against 18 us now.)
+constexpr int TRI = 64;       // vectors of a workgroup (four waves)
 template <bool TRANS>
 __global__ __launch_bounds__(256) void tri64_kernel(const double* __restrict__ Lg, int64_t ldl, double* base,
                                                    int64_t sv, int64_t sj, int64_t nvec) {
-  __shared__ double Ls[NB][NB + 1];
-  for (int e = threadIdx.x; e < NB * NB; e += 256) {
-    const int i = e / NB, j = e % NB;
-    Ls[i][j] = (j <= i) ? Lg[i * ldl + j] : 0.0;
+  __shared__ double S[NB][NB + 2];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int64_t t = (int64_t)blockIdx.x * TRI + 16 * w + l16;
+  double* v = base + (t < nvec ? t : nvec - 1) * sv;
+  d4_t x[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[b][r] = v[(16 * b + 4 * r + lq) * sj];
+#pragma unroll
+  for (int u = 0; u < NB * NB / 256; ++u) {
+    const int e = tid + 256 * u, i = e / NB, j = e % NB;
+    S[i][j] = Lg[(int64_t)i * ldl + j];          // (nothing reads its upper triangle)
   }
   __syncthreads();
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= nvec) return;
-  double* v = base + t * sv;
-  double x[NB];
 #pragma unroll
-  for (int j = 0; j < NB; ++j) x[j] = v[j * sj];
-  if (!TRANS) {
+  for (int q = 0; q < 4; ++q) {
+    const int b = TRANS ? 3 - q : q;             // block solved in this round
+    const int o = 16 * b;
+    double f[16][4];                             // factor of component i in component 4 r + lq of the block
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      double s = x[i];
+    for (int i = 0; i < 16; ++i)
 #pragma unroll
-      for (int k = 0; k < i; ++k) s -= Ls[i][k] * x[k];
-      x[i] = s / Ls[i][i];
+      for (int r = 0; r < 4; ++r) f[i][r] = TRANS ? S[o + i][o + 4 * r + lq] : S[o + 4 * r + lq][o + i];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const int i = TRANS ? 15 - s : s;
+      const double xi = __shfl(x[b][i >> 2], (i & 3) * 16 + l16, 64) / S[o + i][o + i];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = 4 * r + lq;
+        if (c == i) x[b][r] = xi;
+        else if (TRANS ? c < i : c > i) x[b][r] -= f[i][r] * xi;
+      }
     }
-  } else {
+    // the blocks still to be solved minus this one's contribution
 #pragma unroll
-    for (int i = NB - 1; i >= 0; --i) {
-      double s = x[i];
+    for (int p = q + 1; p < 4; ++p) {
+      const int m = TRANS ? 3 - p : p;
 #pragma unroll
-      for (int k = i + 1; k < NB; ++k) s -= Ls[k][i] * x[k];
-      x[i] = s / Ls[i][i];
+      for (int k = 0; k < 4; ++k) {
+        const double a = TRANS ? S[o + 4 * k + lq][16 * m + l16] : S[16 * m + l16][o + 4 * k + lq];
+        x[m] = mfma_f64(-a, x[b][k], x[m]);
+      }
     }
   }
+  if (t >= nvec) return;
 #pragma unroll
-  for (int j = 0; j < NB; ++j) v[j * sj] = x[j];
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[(16 * b + 4 * r + lq) * sj] = x[b][r];
 }
 
 // ---------------- pivoted Cholesky
@@ -277,11 +319,11 @@ hipError_t cholesky_lower(double* A, int64_t n, int64_t lda, int32_t* status, hi
   hipError_t e = hipMemsetAsync(status, 0, sizeof(int32_t), s);
   if (e != hipSuccess) return e;
   for (int64_t k0 = 0; k0 < n; k0 += NB) {
-    hipLaunchKernelGGL(chol_panel_kernel, dim3(1), dim3(256), 0, s, A, lda, k0, status);
+    hipLaunchKernelGGL(chol_panel_kernel, dim3(1), dim3(64), 0, s, A, lda, k0, status);
     const int64_t rest = n - k0 - NB;
     if (rest <= 0) break;
     // A21 <- A21 L11^-T : each row x solves L11 x = a
-    hipLaunchKernelGGL(tri64_kernel<false>, dim3(nblk(rest, 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL(tri64_kernel<false>, dim3(nblk(rest, TRI)), dim3(256), 0, s,
                        A + k0 * lda + k0, lda, A + (k0 + NB) * lda + k0, lda, (int64_t)1, rest);
     Gemm g;
     g.M = rest; g.N = rest; g.K = NB;
@@ -296,7 +338,7 @@ hipError_t cholesky_lower(double* A, int64_t n, int64_t lda, int32_t* status, hi
 }
 
 // Two-level blocked solve.  Outer blocks of NB2 rows: the block is solved 64 rows
-// at a time (the 64 x 64 triangle in LDS, one thread per right-hand side, and
+// at a time (the 64 x 64 triangle in LDS, 16 right-hand sides per wave, and
 // rank-64 updates confined to the block's rows), then the rest of B takes one
 // rank-NB2 update.  The updates that sweep all of B are therefore NB2 deep, so B
 // streams through HBM n / NB2 times instead of n / 64 times.
@@ -324,10 +366,10 @@ hipError_t tri_solve_lower(const double* L, int64_t n, int64_t ldl, double* B, i
     for (int64_t q = 0; q < nin; ++q) {
       const int64_t k0 = o0 + (trans ? (nin - 1 - q) : q) * NB;
       if (!trans)
-        hipLaunchKernelGGL(tri64_kernel<false>, dim3(nblk(ncols, 256)), dim3(256), 0, s,
+        hipLaunchKernelGGL(tri64_kernel<false>, dim3(nblk(ncols, TRI)), dim3(256), 0, s,
                            L + k0 * ldl + k0, ldl, B + k0 * ldb, (int64_t)1, ldb, ncols);
       else
-        hipLaunchKernelGGL(tri64_kernel<true>, dim3(nblk(ncols, 256)), dim3(256), 0, s,
+        hipLaunchKernelGGL(tri64_kernel<true>, dim3(nblk(ncols, TRI)), dim3(256), 0, s,
                            L + k0 * ldl + k0, ldl, B + k0 * ldb, (int64_t)1, ldb, ncols);
       const hipError_t e = trans ? update(o0, k0, k0, NB) : update(k0 + NB, o1, k0, NB);
       if (e != hipSuccess) return e;

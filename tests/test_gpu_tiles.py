@@ -285,3 +285,19 @@ def test_fused_fp64_orbitals_in_kernel(lib, w, nocc, shape, monkeypatch):
         dk = np.abs(K - Kr).max() / np.abs(Kr).max()
         _say(f"case: FP64 fused N={w.nbas} n={nocc} N_aux={w.naux} variant {v} dE={E - Er:.2e} dK={dk:.2e}")
         assert dk < 1e-11 and abs(E - Er) < 1e-11 * abs(Er)
+
+
+# ---- set-up: Cholesky panels and triangular solves in 64-row blocks, 512-row outer blocks
+@pytest.mark.parametrize("naux", [1, 16, 63, 64, 65, 200, 520])
+def test_setup_solve_blocks(lib, naux):
+    """V and W against the oracle's LAPACK solve on a ragged grid, with the bar of the set-up's
+    parity tests: both solves carry the metric's condition number times eps, up to 1e-8."""
+    from oracle import isdf
+    w = ri.diamond_supercell((1, 1, 1), (11, 13, 14), 2, naux=naux)
+    with lib.Context.from_workload(w, seed=w.sketch_seed()) as ctx:
+        pts = ctx.points()
+        V, W = ctx.array(1), ctx.array(2)
+    st = isdf.setup(w, basis.eval_basis(w), points=pts)
+    _say(f"case: set-up solve N_aux={naux} dV={np.abs(V - st['V']).max() / np.abs(st['V']).max():.2e}")
+    assert np.abs(V - st["V"]).max() < 1e-8 * np.abs(st["V"]).max()
+    assert np.abs(W - st["W"]).max() < 1e-8 * np.abs(st["W"]).max()
