@@ -468,7 +468,11 @@ __host__ __device__ __forceinline__ int gemm32_parts(const Gemm32& g) { return g
 // Requires K (and every K split) a multiple of 16; whole 16-byte pieces past M or
 // the readable N are read from the matrix's edge instead (their products only
 // reach outputs that are not stored).
-template <int TM, int TN, bool TA, bool TB, bool OUT32>
+//
+// MG: a workgroup takes several splits, so the FP32 sums also start anew inside it.  A
+// variant of its own: with the test in the loop of every product, M2 of unmerged splits
+// ran 1.9% slower (2.14 against 2.18 ms for 6144 x 224 over 81280).
+template <int TM, int TN, bool TA, bool TB, bool OUT32, bool MG>
 __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
   constexpr int BK = 16;
   constexpr int BM = 32 * TM, BN = 32 * TN;
@@ -627,9 +631,9 @@ __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = mfma_f32(a[i][kk], b[j][kk], acc[i][j]);
     if constexpr (!OUT32) {
-      ++pos;
-      if (pos % FLUSH == 0 || pos == seg || t + 1 == nk) {
-        if (pos == seg) pos = 0;
+      if constexpr (MG) ++pos;
+      if (MG ? (pos % FLUSH == 0 || pos == seg || t + 1 == nk) : ((t + 1) % FLUSH == 0 || t + 1 == nk)) {
+        if (MG && pos == seg) pos = 0;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1324,12 +1328,21 @@ void launch32v_bk(const Gemm32& g, dim3 grid, hipStream_t s) {
 }
 // K steps of 16: at the 3x3x3 cell's chunk shapes they measured 102-110 TF/s against
 // 98-106 TF/s with steps of 32 (twice the LDS and prefetch registers per workgroup)
+template <int TN, bool OUT32, bool MG>
+void launch32d_mg(const Gemm32& g, dim3 grid, hipStream_t s) {
+  if (!g.transA && !g.transB) hipLaunchKernelGGL((gemm32d_kernel<4, TN, false, false, OUT32, MG>), grid, dim3(256), 0, s, g);
+  else if (g.transA && !g.transB) hipLaunchKernelGGL((gemm32d_kernel<4, TN, true, false, OUT32, MG>), grid, dim3(256), 0, s, g);
+  else if constexpr (TN != 3) {        // 96-wide tiles take an MN-major B only
+    if (!g.transA) hipLaunchKernelGGL((gemm32d_kernel<4, TN, false, true, OUT32, MG>), grid, dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((gemm32d_kernel<4, TN, true, true, OUT32, MG>), grid, dim3(256), 0, s, g);
+  }
+}
+
 template <int TN, bool OUT32>
 void launch32d(const Gemm32& g, dim3 grid, hipStream_t s) {
-  if (!g.transA && !g.transB) hipLaunchKernelGGL((gemm32d_kernel<4, TN, false, false, OUT32>), grid, dim3(256), 0, s, g);
-  else if (g.transA && !g.transB) hipLaunchKernelGGL((gemm32d_kernel<4, TN, true, false, OUT32>), grid, dim3(256), 0, s, g);
-  else if (!g.transA && g.transB) hipLaunchKernelGGL((gemm32d_kernel<4, TN, false, true, OUT32>), grid, dim3(256), 0, s, g);
-  else hipLaunchKernelGGL((gemm32d_kernel<4, TN, true, true, OUT32>), grid, dim3(256), 0, s, g);
+  if constexpr (!OUT32)
+    if (g.merge > 1) return launch32d_mg<TN, OUT32, true>(g, grid, s);
+  launch32d_mg<TN, OUT32, false>(g, grid, s);
 }
 
 template <int TN, bool OUT32>
@@ -1368,11 +1381,13 @@ int gemm32_tile_n(int64_t N) {
 // resident workgroups at 115 TF/s, partials written and read back at 4 TB/s).  Only the FP64
 // sums are grouped differently.  M1^T of a full chunk at n = 288 goes from three splits to
 // one workgroup per tile (2.52 -> 2.39 ms), M2 from 5 x 177 workgroups on 512 places (1.73
-// rounds) to 20 x 177 (6.9).
+// rounds) to 20 x 177 (6.9).  The plan is left for a predicted gain of 3% or more only: fewer,
+// longer rounds that save a little of the reduction lose more at their ends (M2 of 6144 x 224,
+// eight splits in two rounds joined to four in one: 2.12 -> 2.17 ms).
 static void gemm32_regroup(Gemm32& g, int bn) {
   const int64_t tiles = ((g.M + 127) / 128) * ((g.N + bn - 1) / bn), slots = (bn == 96) ? 512 : 768;
   const int64_t kper = ((g.K + g.splitk - 1) / g.splitk + 15) / 16 * 16;
-  double best = 1e300;
+  double best = 1e300, need = 1.0;
   auto consider = [&](int merge, int sub) {
     const int64_t parts = (int64_t)g.splitk / merge * sub;
     const int64_t len = (sub > 1) ? (kper + 64 * sub - 1) / (64 * sub) * 64 : merge * kper;
@@ -1380,13 +1395,16 @@ static void gemm32_regroup(Gemm32& g, int bn) {
     const double rounds = (double)((tiles * parts + slots - 1) / slots);
     const double t = rounds * (double)len * (2.0 * 128 * bn * slots / 115e12) +
                      (parts > 1 ? (double)(parts * g.M * g.N) * (16.0 / 4e12) + 5e-6 : 0.0);
-    if (t < best * (1.0 - 1e-9)) {
+    if (t < best * need) {
       best = t;
+      need = 1.0 - 1e-9;
       g.merge = merge;
       g.sub = sub;
     }
   };
-  for (int m = 1; m <= g.splitk; ++m)
+  consider(1, 1);
+  need = 0.97;
+  for (int m = 2; m <= g.splitk; ++m)
     if (g.splitk % m == 0) consider(m, 1);
   for (int u = 2; u <= 8 && kper / u >= 512; ++u) consider(1, u);
 }
@@ -1419,8 +1437,7 @@ hipError_t gemm_f32(const Gemm32& g0, hipStream_t s) {
   const dim3 grid1((unsigned)((ntile + 7) / 8 * 8));
   if (vec && ntile > (int64_t)UINT32_MAX - 8) return hipErrorInvalidValue;
   if (bn == 96) {
-    if (g.transA) hipLaunchKernelGGL((gemm32d_kernel<4, 3, true, false, false>), grid1, dim3(256), 0, s, g);
-    else hipLaunchKernelGGL((gemm32d_kernel<4, 3, false, false, false>), grid1, dim3(256), 0, s, g);
+    launch32d<3, false>(g, grid1, s);
   } else if (bn == 64) {
     if (direct) { if (out32) launch32d<2, true>(g, grid1, s); else launch32d<2, false>(g, grid1, s); }
     else if (vec) { if (out32) launch32v<2, true>(g, grid1, s); else launch32v<2, false>(g, grid1, s); }
