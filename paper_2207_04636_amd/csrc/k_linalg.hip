@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void tri64_kernel(const double* __restrict__ L
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int b = TRANS ? 3 - q : q;             // block solved in this round
+    const int b = TRANS ? 3 - q : q;             // block solved now
     const int o = 16 * b;
     double f[16][4];                             // factor of component i in component 4 r + lq of the block
 #pragma unroll
