@@ -440,6 +440,15 @@ __device__ __forceinline__ int kmajor_row(int q) {
   return ((t >> 2) << 3) + (t & 3) + ((q & 1) << 2);
 }
 
+// The wait before a step's barrier in the LDS-direct kernels, which hold three LDS stages:
+// the barrier of step t lets the loads of step t + 2 overwrite the stage that step t - 1
+// read.  So it waits not only for the step's own loads (vmcnt, the caller ORs in how many of
+// the next step's may stay in flight) but also for the wave's LDS reads of step t - 1
+// (lgkmcnt 0): nothing else makes them finish there, since the compiler moves the matrix
+// instructions that use them, and its own wait for them, past the barrier (up to seven
+// reads were in flight at it, and a wave ahead could overwrite what they had yet to read).
+constexpr int kStageWait = 0x070;      // expcnt 7 (no wait), lgkmcnt 0, vmcnt from the caller
+
 // Parts of K that run as workgroups of their own on the LDS-direct kernel.
 __host__ __device__ __forceinline__ int gemm32_parts(const Gemm32& g) { return g.splitk / g.merge * g.sub; }
 
@@ -591,8 +600,9 @@ __global__ __launch_bounds__(256, 2) void gemm32d_kernel(Gemm32 g) {
   // otherwise waits for every load in flight once per three steps.
   auto step = [&](int64_t t, const float* __restrict__ as, const float* __restrict__ bs,
                   float* __restrict__ an, float* __restrict__ bn) {
-    // this step's loads landed (the next step's NPER may still be in flight)
-    __builtin_amdgcn_s_waitcnt(0xF70 | NPER);
+    // this step's loads landed (the next step's NPER may still be in flight), and this
+    // wave's reads of the previous stage are done: see kStageWait
+    __builtin_amdgcn_s_waitcnt(kStageWait | NPER);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -1047,7 +1057,8 @@ __device__ __forceinline__ void gemm64d_body(const Gemm& g, int64_t m0, int64_t 
   auto step = [&](int64_t t, const double* __restrict__ as, const double* __restrict__ bs,
                   const double* __restrict__ ss, double* __restrict__ an, double* __restrict__ bn,
                   double* __restrict__ sn) {
-    __builtin_amdgcn_s_waitcnt(0xF70 | NPER);
+    // this step's loads landed, this wave's reads of the previous stage are done (kStageWait)
+    __builtin_amdgcn_s_waitcnt(kStageWait | NPER);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
