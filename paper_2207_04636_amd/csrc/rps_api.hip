@@ -40,6 +40,97 @@ void hip_check(hipError_t e, const char* what) {
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
+// Workspaces of the full exchange matrix that no call is using, for the next one: its
+// hundreds of MB allocated and freed by every call took 26 to 52 ms beside kernels of 2.5 ms.
+// One pool serves all contexts, so however many there are, at most kKeep bytes per device
+// stand idle.  A block belongs to one call from take to give and is given back with its work
+// done, so threads and streams cannot meet in one.  Idle blocks are freed with the last
+// context, and whenever the library would otherwise run out of device memory.
+class WorkspacePool {
+ public:
+  static constexpr int64_t kKeep = 1ll << 30;
+  struct Block {
+    int device = 0;
+    double* p = nullptr;
+    int64_t n = 0;
+  };
+  static WorkspacePool& get() {
+    static WorkspacePool* pool = new WorkspacePool;   // never destroyed: the runtime may be gone at exit
+    return *pool;
+  }
+  // The smallest idle block of at least n doubles on the current device, or p = NULL.
+  Block take(int64_t n) {
+    Block b;
+    if (hipGetDevice(&b.device) != hipSuccess) return b;
+    std::lock_guard<std::mutex> lock(mu_);
+    int best = -1;
+    for (int i = 0; i < (int)idle_.size(); ++i)
+      if (idle_[i].device == b.device && idle_[i].n >= n && (best < 0 || idle_[i].n < idle_[best].n)) best = i;
+    if (best >= 0) {
+      b = idle_[best];
+      idle_.erase(idle_.begin() + best);
+    }
+    return b;
+  }
+  // Keep b, at the cost of the blocks longest idle on its device (or of b, if larger than kKeep).
+  void give(const Block& b) noexcept {
+    std::lock_guard<std::mutex> lock(mu_);
+    try {
+      idle_.push_back(b);
+    } catch (...) {
+      (void)hipFree(b.p);
+      return;
+    }
+    int64_t held = 0;
+    for (int i = (int)idle_.size() - 1; i >= 0; --i) {
+      if (idle_[i].device != b.device) continue;
+      if (held + idle_[i].n * 8 <= kKeep) {
+        held += idle_[i].n * 8;
+      } else {
+        (void)hipFree(idle_[i].p);
+        idle_.erase(idle_.begin() + i);
+      }
+    }
+  }
+  // Free every idle block; whether there was one.
+  bool trim() {
+    std::lock_guard<std::mutex> lock(mu_);
+    const bool any = !idle_.empty();
+    for (const Block& b : idle_) (void)hipFree(b.p);
+    idle_.clear();
+    return any;
+  }
+  // Member of every context: the pool empties when the last one goes.
+  struct User {
+    User() { get().count(1); }
+    ~User() { get().count(-1); }
+    User(const User&) = delete;
+    User& operator=(const User&) = delete;
+  };
+
+ private:
+  void count(int change) {
+    std::unique_lock<std::mutex> lock(mu_);
+    contexts_ += change;
+    const bool none = (contexts_ == 0);
+    lock.unlock();
+    if (none) trim();
+  }
+  std::mutex mu_;
+  std::vector<Block> idle_;     // longest idle first
+  int contexts_ = 0;
+};
+
+// hipMalloc that gives the pool's idle blocks back before it fails for want of memory
+hipError_t device_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && WorkspacePool::get().trim()) {
+    (void)hipGetLastError();      // the launches after it report the last error
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
 // Device buffer owned by a context (or by a set-up step; freed on every exit path).
 template <typename Tp>
 struct DBuf {
@@ -52,7 +143,7 @@ struct DBuf {
   void alloc(int64_t count, int64_t* counter) {
     release(counter);
     if (count <= 0) return;
-    hip_check(hipMalloc((void**)&p, sizeof(Tp) * count), "hipMalloc");
+    hip_check(device_malloc((void**)&p, sizeof(Tp) * count), "hipMalloc");
     n = count;
     if (counter) *counter += (int64_t)sizeof(Tp) * count;
   }
@@ -69,6 +160,7 @@ struct DBuf {
 }  // namespace
 
 struct rps_context {
+  WorkspacePool::User pool_user;
   // geometry and sizes
   double lat[9], ainv[9];
   int mesh[3];
@@ -127,9 +219,6 @@ struct rps_context {
   bool jws_small = false;
   int64_t jchunk = 0;
   DBuf<double> jCp, jCin, jU, jrho, jwork, jpart, jJ;
-  // full exchange matrix: workspace, kept between calls while it is small (build_full_impl)
-  DBuf<double> fC, fCp, fU, fUg, fA, fO, fT, fK3, fK, fwork;
-  int64_t fbytes = 0;
   // Madelung term: S = dV Phi^T Phi (kept once formed) and workspace
   DBuf<double> Sdev, mCp, mSC, mpart;
   // autotuned launch parameters (0: built-in default)
@@ -181,8 +270,6 @@ struct rps_context {
     gM1T32.release(nullptr);
     gA32.release(nullptr);
     ecount.release(nullptr);
-    DBuf<double>* fb[] = {&fC, &fCp, &fU, &fUg, &fA, &fO, &fT, &fK3, &fK, &fwork};
-    for (auto* b : fb) b->release(nullptr);
     DBuf<double>* jb[] = {&kern, &jCp, &jCin, &jU, &jrho, &jwork, &jpart, &jJ, &Sdev, &mCp, &mSC, &mpart};
     for (auto* b : jb) b->release(nullptr);
     V32.release(nullptr);
@@ -225,7 +312,6 @@ constexpr int64_t kSplitWork = 64ll << 20;   // doubles of split-K partials (512
 constexpr int kEnergyBlocks = 256;            // most blocks the energy dot products are split over
 constexpr int kStreamMaxNp = 128;             // largest padded n of the streaming form
 constexpr int64_t kFullChunk = 32ll << 20;    // doubles of A per chunk of the full exchange matrix (256 MB)
-constexpr int64_t kFullKeep = 1ll << 30;      // its workspace stays with the context up to 1 GB (see build_full_impl)
 constexpr int64_t kChiPanel = 32768;          // grid columns per fitting-function panel (set-up)
 constexpr int64_t kWPanel = 1024;             // rows per panel of the V and W stage (set-up)
 constexpr int kStreamBlocks = 512;            // workgroups aimed at per streaming launch (default)
@@ -737,6 +823,7 @@ void setup_impl(rps_context& c, const rps_cell* cell, const rps_basis* b, int64_
     const double need = persist + (given ? 0.0 : std::max(xgg + xblk, selb)) + 64.0 * 1024 * 1024;
     size_t fr = 0, tot = 0;
     hip_check(hipMemGetInfo(&fr, &tot), "hipMemGetInfo");
+    if (need > (double)fr && WorkspacePool::get().trim()) hip_check(hipMemGetInfo(&fr, &tot), "hipMemGetInfo");
     if (need > (double)fr)
       fail(RPS_ERR_NOMEM, "set-up needs about " + std::to_string((int64_t)(need / 1e9)) + " GB, " +
                               std::to_string((int64_t)(fr / 1000000000ull)) + " GB free");
@@ -748,7 +835,7 @@ void setup_impl(rps_context& c, const rps_cell* cell, const rps_basis* b, int64_
   hip_check(fill(c.Phi.p, c.ngp * c.Np, 0.0, st), "fill");
   {
     DBuf<ShellDev> dsh;
-    hip_check(hipMalloc((void**)&dsh.p, sizeof(ShellDev) * shells.size()), "hipMalloc");
+    hip_check(device_malloc((void**)&dsh.p, sizeof(ShellDev) * shells.size()), "hipMalloc");
     dsh.n = (int64_t)shells.size();
     hip_check(hipMemcpyAsync(dsh.p, shells.data(), sizeof(ShellDev) * shells.size(), hipMemcpyHostToDevice, st),
               "copy shells");
@@ -1816,7 +1903,7 @@ void build_impl(rps_context& c, int variant, int32_t nocc, const double* C, doub
 // Eq. 13): K = dV [Phi_g^T (A Phi) + (Phi_g^T (A Phi))^T - Phi_g^T (B Phi_g)],
 // A = V o (U_g U^T), B = W o (U_g U_g^T).  Needed once at the end of an SCF
 // run (Sec. 3.3), so it takes the simple route: A in g chunks by the GEMM with
-// the Hadamard epilogue, then plain GEMMs; temporaries live for the call.
+// the Hadamard epilogue, then plain GEMMs, in one workspace from the pool.
 void build_full_impl(rps_context& c, int32_t nocc, const double* C, double* K, int32_t flags, hipStream_t st) {
   if (c.ng == 0) fail(RPS_ERR_STATE, "context has no completed set-up");
   if (nocc < 1) fail(RPS_ERR_ARG, "nocc must be >= 1");
@@ -1827,72 +1914,86 @@ void build_full_impl(rps_context& c, int32_t nocc, const double* C, double* K, i
   // A in chunks of g rows, 256 MB each (the size of the last-level cache, which then serves
   // much of the second product's reads), but whole 128-row output tiles
   const int64_t gc = std::min<int64_t>(G, std::max<int64_t>(128, kFullChunk / R / 128 * 128));
-  struct Release {     // a workspace above kFullKeep goes back at the end of the call
-    rps_context& c;
-    ~Release() {
-      if (c.fbytes <= kFullKeep) return;
-      DBuf<double>* all[] = {&c.fC, &c.fCp, &c.fU, &c.fUg, &c.fA, &c.fO, &c.fT, &c.fK3, &c.fK, &c.fwork};
-      for (auto* b : all) b->release(&c.bytes);
-      c.fbytes = 0;
+  // The workspace and the products that may split K, laid out from base (any aligned address
+  // serves to learn the size: it decides nothing but alignment); the doubles it takes.
+  double *fCp, *fU, *fUg, *fA, *fO, *fT, *fK3, *fC = nullptr, *fK = nullptr;
+  std::vector<Gemm> split;
+  size_t nchunk = 0;
+  auto layout = [&](double* base) {
+    int64_t off = 0;
+    auto take = [&](int64_t n) {
+      double* q = base + off;
+      off += round_up(n, 32);       // 256-byte aligned pieces
+      return q;
+    };
+    fCp = take(Np * np);
+    fU = take(R * np);
+    fUg = take(G * np);
+    fA = take(std::max(gc * R, G * G));
+    fO = take(G * Np);
+    fT = take(Np * Np);
+    fK3 = take(Np * Np);
+    if (!dev) {
+      fC = take(N * nocc);
+      fK = take(N * N);
     }
-  } release{c};
-  auto need = [&](DBuf<double>& b, int64_t n) {
-    if (b.n >= n) return;
-    const int64_t before = c.bytes;
-    b.alloc(n, &c.bytes);
-    c.fbytes += c.bytes - before;
+    split.clear();
+    auto plan = [&](int64_t M, int64_t K, const double* A, int64_t lda, bool tA, const double* B, double* D) {
+      Gemm g;                       // (B and the result have the basis's width and pitch)
+      g.M = M; g.N = Np; g.K = K;
+      g.A = A; g.lda = lda; g.transA = tA; g.B = B; g.ldb = Np; g.C = D; g.ldc = Np;
+      gemm_plan(g, kSplitWork);
+      split.push_back(g);
+    };
+    for (int64_t g0 = 0; g0 < G; g0 += gc)      // O[c] = A_c Phi
+      plan(std::min(gc, G - g0), R, fA, R, false, c.Phi.p, fO + g0 * Np);
+    nchunk = split.size();
+    plan(Np, G, c.Phig.p, Np, true, fO, fT);    // T = Phi_g^T O
+    plan(G, G, fA, G, false, c.Phig.p, fO);     // B Phi_g (in O's place)
+    plan(Np, G, c.Phig.p, Np, true, fO, fK3);   // K3 = Phi_g^T (B Phi_g)
+    int64_t wk = 0;
+    for (const Gemm& g : split)
+      if (g.splitk > 1) wk = std::max(wk, g.splitk * g.M * g.N);
+    double* work = take(wk);
+    for (Gemm& g : split) g.work = work;
+    return off;
   };
-  std::vector<Gemm> split;      // the products that may split K, planned before anything runs
-  auto plan = [&](int64_t M, int64_t Nn, int64_t K, const double* A, int64_t lda, bool tA, const double* B, int64_t ldb,
-                  double* C_, int64_t ldc) {
-    Gemm g;
-    g.M = M; g.N = Nn; g.K = K;
-    g.A = A; g.lda = lda; g.transA = tA; g.B = B; g.ldb = ldb; g.C = C_; g.ldc = ldc;
-    gemm_plan(g, kSplitWork);
-    return g;
-  };
-  need(c.fCp, Np * np);
-  need(c.fU, R * np);
-  need(c.fUg, G * np);
-  need(c.fA, std::max(gc * R, G * G));
-  need(c.fO, G * Np);
-  need(c.fT, Np * Np);
-  need(c.fK3, Np * Np);
-  if (!dev) {
-    need(c.fC, N * nocc);
-    need(c.fK, N * N);
+  // back to the pool once the call's work is done, freed (which waits for the device) after a failure
+  struct Lease {
+    WorkspacePool::Block b;
+    bool done = false;
+    ~Lease() {
+      if (done) WorkspacePool::get().give(b);
+      else if (b.p) (void)hipFree(b.p);
+    }
+  } lease;
+  const int64_t need = layout(c.Phi.p);
+  lease.b = WorkspacePool::get().take(need);
+  if (!lease.b.p) {
+    hip_check(device_malloc((void**)&lease.b.p, (size_t)need * 8), "hipMalloc");
+    lease.b.n = need;
   }
-  for (int64_t g0 = 0; g0 < G; g0 += gc)      // O[c] = A_c Phi
-    split.push_back(plan(std::min(gc, G - g0), Np, R, c.fA.p, R, false, c.Phi.p, Np, c.fO.p + g0 * Np, Np));
-  const size_t nchunk = split.size();
-  split.push_back(plan(Np, Np, G, c.Phig.p, Np, true, c.fO.p, Np, c.fT.p, Np));    // T = Phi_g^T O
-  split.push_back(plan(G, Np, G, c.fA.p, G, false, c.Phig.p, Np, c.fO.p, Np));     // B Phi_g (in O's place)
-  split.push_back(plan(Np, Np, G, c.Phig.p, Np, true, c.fO.p, Np, c.fK3.p, Np));   // K3 = Phi_g^T (B Phi_g)
-  int64_t wk = 1;
-  for (const Gemm& g : split)
-    if (g.splitk > 1) wk = std::max(wk, g.splitk * g.M * g.N);
-  need(c.fwork, wk);
-  for (Gemm& g : split) g.work = c.fwork.p;
+  layout(lease.b.p);
 
   const double* Csrc = C;
   if (!dev) {
-    hip_check(hipMemcpyAsync(c.fC.p, C, (size_t)N * nocc * 8, hipMemcpyHostToDevice, st), "copy C");
-    Csrc = c.fC.p;
+    hip_check(hipMemcpyAsync(fC, C, (size_t)N * nocc * 8, hipMemcpyHostToDevice, st), "copy C");
+    Csrc = fC;
   }
-  hip_check(pack_matrix(Csrc, N, nocc, nocc, c.fCp.p, Np, np, st), "pack C");
+  hip_check(pack_matrix(Csrc, N, nocc, nocc, fCp, Np, np, st), "pack C");
   {
     Gemm g;   // U = Phi C
     g.M = R; g.N = np; g.K = Np;
-    g.A = c.Phi.p; g.lda = Np; g.B = c.fCp.p; g.ldb = np; g.C = c.fU.p; g.ldc = np;
+    g.A = c.Phi.p; g.lda = Np; g.B = fCp; g.ldb = np; g.C = fU; g.ldc = np;
     hip_check(gemm_f64(g, st), "U");
   }
-  hip_check(gather_rows(c.fU.p, np, c.dpoints.p, c.naux, G, np, c.fUg.p, np, st), "U_g");
+  hip_check(gather_rows(fU, np, c.dpoints.p, c.naux, G, np, fUg, np, st), "U_g");
   for (size_t q = 0; q < nchunk; ++q) {
     const int64_t g0 = (int64_t)q * gc;
     Gemm a;   // A_c = V_c o (U_g[c] U^T)
     a.M = split[q].M; a.N = R; a.K = np;
-    a.A = c.fUg.p + g0 * np; a.lda = np; a.B = c.fU.p; a.ldb = np; a.transB = true;
-    a.C = c.fA.p; a.ldc = R; a.epi = EPI_HADAMARD_SRC; a.ldd = R;
+    a.A = fUg + g0 * np; a.lda = np; a.B = fU; a.ldb = np; a.transB = true;
+    a.C = fA; a.ldc = R; a.epi = EPI_HADAMARD_SRC; a.ldd = R;
     if (c.V.p) a.D = c.V.p + g0 * R;
     else a.D32 = c.V32.p + g0 * R;
     hip_check(gemm_f64(a, st), "A chunk");
@@ -1902,16 +2003,17 @@ void build_full_impl(rps_context& c, int32_t nocc, const double* C, double* K, i
   {
     Gemm b;   // B = W o (U_g U_g^T)
     b.M = G; b.N = G; b.K = np;
-    b.A = c.fUg.p; b.lda = np; b.B = c.fUg.p; b.ldb = np; b.transB = true;
-    b.C = c.fA.p; b.ldc = G; b.epi = EPI_HADAMARD_SRC; b.D = c.W.p; b.ldd = G;
+    b.A = fUg; b.lda = np; b.B = fUg; b.ldb = np; b.transB = true;
+    b.C = fA; b.ldc = G; b.epi = EPI_HADAMARD_SRC; b.D = c.W.p; b.ldd = G;
     hip_check(gemm_f64(b, st), "B");
   }
   hip_check(gemm_f64(split[nchunk + 1], st), "B Phi_g");
   hip_check(gemm_f64(split[nchunk + 2], st), "Phi_g^T (B Phi_g)");
-  double* Kout = dev ? K : c.fK.p;
-  hip_check(full_combine(c.fT.p, c.fK3.p, Np, N, c.dV, Kout, st), "combine");
-  if (!dev) hip_check(hipMemcpyAsync(K, c.fK.p, (size_t)N * N * 8, hipMemcpyDeviceToHost, st), "copy K");
-  hip_check(hipStreamSynchronize(st), "sync");   // as documented; the workspace may be released now
+  double* Kout = dev ? K : fK;
+  hip_check(full_combine(fT, fK3, Np, N, c.dV, Kout, st), "combine");
+  if (!dev) hip_check(hipMemcpyAsync(K, fK, (size_t)N * N * 8, hipMemcpyDeviceToHost, st), "copy K");
+  hip_check(hipStreamSynchronize(st), "sync");   // as documented; the workspace is free again
+  lease.done = true;
 }
 
 // ------------------------------------------------------------------ Coulomb matrix

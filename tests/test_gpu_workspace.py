@@ -1,0 +1,69 @@
+"""Device memory that outlives a call of the full exchange matrix: one pool for all contexts,
+at most 1 GB per device, given back with the last context."""
+import sys
+import threading
+
+import numpy as np
+import pytest
+
+import rps_inputs as ri
+
+pytestmark = pytest.mark.gpu
+
+MB = 1 << 20
+
+
+def _say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2207_04636_amd as P
+    P.load()
+    return P
+
+
+def test_full_exchange_memory_is_shared_and_bounded(lib):
+    """Five contexts with about 300 MB of workspace each, in turn and then in threads of their
+    own: equal results, and never more than 1 GB (and the runtime's own few MB) held between
+    calls; nothing once the contexts are gone."""
+    import torch
+    w = ri.diamond_cell(4.0)
+    C = np.linalg.qr(np.random.default_rng(3).standard_normal((w.nbas, 16)))[0].copy()
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    with lib.Context.from_workload(w, seed=w.sketch_seed()) as ctx:
+        pts = ctx.points()
+        ctx.build_full(C)
+    start = free()      # the library's code and constants are loaded
+    ctxs = [lib.Context.from_workload(w, points=pts) for _ in range(5)]
+    try:
+        before = free()
+        K = [c.build_full(C) for c in ctxs]
+        _say(f"case: five contexts in turn, {(before - free()) / MB:.0f} MB held")
+        assert before - free() <= 1100 * MB
+        assert all(np.array_equal(K[0], k) for k in K[1:])
+        out = [None] * 5
+
+        def work(i):
+            torch.cuda.set_device(0)
+            out[i] = [ctxs[i].build_full(C) for _ in range(3)]
+
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(5)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert all(np.array_equal(K[0], k) for o in out for k in o)
+        _say(f"  in threads, {(before - free()) / MB:.0f} MB held")
+        assert before - free() <= 1100 * MB
+    finally:
+        for c in ctxs:
+            c.close()
+    _say(f"  contexts gone, {(start - free()) / MB:.0f} MB held")
+    assert start - free() <= 100 * MB
