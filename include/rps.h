@@ -237,10 +237,11 @@ rps_status rps_build_exchange_variant(rps_context *ctx, int32_t variant, int32_t
  * at the end of an SCF run (Sec. 3.3).  nocc, C as for
  * rps_build_exchange_occRI; K: [N][N] FP64 output (host or device per flags).
  * Works on any context (FP64 products; the precision form reads its FP32 V).
- * Its temporaries (256 MB, 1 KB per grid point or 8 N_aux^2 bytes, whichever is most,
- * with 8 N_aux N and 8 N_g n bytes and up to 512 MB of split partials) come from a pool
- * that all contexts share: between calls it keeps at most 1 GB per device, until the last
- * context is destroyed or another allocation of the library needs the memory.
+ * Its temporaries come from a pool that all contexts share: 256 MB, 1 KB per grid point
+ * (512 bytes above 1.9 million points) or 8 N_aux^2 bytes, whichever is most, with
+ * 8 N_aux N and 8 N_g n bytes and up to 512 MB of split partials.  Between calls the pool
+ * keeps at most 1 GB per device, until the last context is destroyed or another
+ * allocation of the library needs the memory.
  * Synchronises hip_stream before returning.
  * Errors: RPS_ERR_ARG, RPS_ERR_STATE, RPS_ERR_NOMEM, RPS_ERR_DEVICE.
  */

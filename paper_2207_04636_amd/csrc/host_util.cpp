@@ -4,6 +4,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <cmath>
 
 namespace rps {
@@ -152,6 +153,15 @@ void orthonormalize_columns(std::vector<double>& A, int64_t nrow, int64_t ncol) 
     if (nrm > 0.0)
       for (int64_t r = 0; r < nrow; ++r) A[r * ncol + j] /= nrm;
   }
+}
+
+// 256 MB (the size of the last-level cache, which then serves much of the second product's
+// reads) in whole 128-row output tiles, at least one; 64 rows where 128 would take more than
+// 2 GB, so that the largest grids need no more than that.
+int64_t full_chunk_rows(int64_t R) {
+  constexpr int64_t chunk = 32ll << 20, most = 2000000000ll / 8;      // doubles
+  if (128 * R > most) return 64;
+  return std::max<int64_t>(128, chunk / R / 128 * 128);
 }
 
 }  // namespace rps

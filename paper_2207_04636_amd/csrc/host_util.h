@@ -34,4 +34,7 @@ std::vector<double> sketch_normal(int64_t nrow, int64_t ncol, uint64_t seed, uin
 // (modified Gram-Schmidt, applied twice).
 void orthonormalize_columns(std::vector<double>& A, int64_t nrow, int64_t ncol);
 
+// Rows of A per chunk of the full exchange matrix, for R padded grid points.
+int64_t full_chunk_rows(int64_t R);
+
 }  // namespace rps

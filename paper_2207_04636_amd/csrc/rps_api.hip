@@ -311,7 +311,6 @@ struct StageLog {
 constexpr int64_t kSplitWork = 64ll << 20;   // doubles of split-K partials (512 MB)
 constexpr int kEnergyBlocks = 256;            // most blocks the energy dot products are split over
 constexpr int kStreamMaxNp = 128;             // largest padded n of the streaming form
-constexpr int64_t kFullChunk = 32ll << 20;    // doubles of A per chunk of the full exchange matrix (256 MB)
 constexpr int64_t kChiPanel = 32768;          // grid columns per fitting-function panel (set-up)
 constexpr int64_t kWPanel = 1024;             // rows per panel of the V and W stage (set-up)
 constexpr int kStreamBlocks = 512;            // workgroups aimed at per streaming launch (default)
@@ -1911,9 +1910,7 @@ void build_full_impl(rps_context& c, int32_t nocc, const double* C, double* K, i
   if (flags != RPS_PTRS_HOST && flags != RPS_PTRS_DEVICE) fail(RPS_ERR_ARG, "flags must be RPS_PTRS_HOST or RPS_PTRS_DEVICE");
   const bool dev = (flags == RPS_PTRS_DEVICE);
   const int64_t np = round_up(nocc, 16), Np = c.Np, G = c.nauxp, R = c.ngp, N = c.nbas;
-  // A in chunks of g rows, 256 MB each (the size of the last-level cache, which then serves
-  // much of the second product's reads), but whole 128-row output tiles
-  const int64_t gc = std::min<int64_t>(G, std::max<int64_t>(128, kFullChunk / R / 128 * 128));
+  const int64_t gc = std::min<int64_t>(G, full_chunk_rows(R));
   // The workspace and the products that may split K, laid out from base (any aligned address
   // serves to learn the size: it decides nothing but alignment); the doubles it takes.
   double *fCp, *fU, *fUg, *fA, *fO, *fT, *fK3, *fC = nullptr, *fK = nullptr;

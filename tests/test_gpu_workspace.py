@@ -67,3 +67,22 @@ def test_full_exchange_memory_is_shared_and_bounded(lib):
             c.close()
     _say(f"  contexts gone, {(start - free()) / MB:.0f} MB held")
     assert start - free() <= 100 * MB
+
+
+def test_full_exchange_of_a_large_grid(lib):
+    """More than 1.9 million points: A in chunks of 64 rows (a half-empty output tile), three
+    of them.  K_full C = K_occ within the rounding of FP64 sums over grid and points."""
+    import dataclasses
+    w = ri.tiny_s_cell(nfunc=9, mesh=8, L=4.0, nocc=3, naux=130, cid=92, lmax=1)
+    w = dataclasses.replace(w, mesh=np.array([125, 125, 126]))
+    rng = np.random.default_rng(7)
+    C = np.linalg.qr(rng.standard_normal((w.nbas, 3)))[0].copy()
+    pts = np.sort(rng.choice(w.ngrid, w.naux, replace=False)).astype(np.int64)
+    q = 1.0 + rng.random((w.naux, 1))
+    V = (q * np.cos(1e-5 * np.arange(w.ngrid))[None, :]).copy()
+    W = 1.0 + rng.random((w.naux, w.naux))
+    W = 0.5 * (W + W.T)
+    with lib.Context.from_potentials(w, pts, V, W) as ctx:
+        Kf, (K, _) = ctx.build_full(C), ctx.build(C)
+    _say(f"case: full exchange, {w.ngrid} points, |K_full C - K| {np.abs(Kf @ C - K).max() / np.abs(K).max():.1e}")
+    assert np.abs(Kf @ C - K).max() < 1e-10 * np.abs(K).max()
