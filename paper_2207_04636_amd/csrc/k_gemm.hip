@@ -1581,6 +1581,19 @@ double direct64_time(int64_t tiles, int64_t K, int64_t z, int64_t outputs) {
          (z > 1 ? (double)z * (double)outputs * (16.0 / 4e12) + 5e-6 : 0.0);
 }
 
+// (The atom blocks of a screened basis: 32 atoms of 8000 points with 416 functions, 320 tiles
+// of K = 8000, took 3.5 ms for J; in 4 pieces each on the LDS-direct kernel, 0.8 ms.)
+int64_t sparse_pieces(int64_t K, int64_t tiles, int64_t outputs, int64_t work_cap) {
+  int64_t best = 1;
+  double best_t = 1e300;
+  for (int64_t z = 1; z <= 64; ++z) {
+    if (z > 1 && (K / z < 256 || z * outputs > work_cap)) break;
+    const double t = direct64_time(tiles, K, z, outputs);
+    if (t < best_t) { best_t = t; best = z; }
+  }
+  return best;
+}
+
 void gemm_plan(Gemm& g, int64_t work_cap_doubles) {
   g.tile_n = 0;
   g.splitk = 1;

@@ -525,20 +525,6 @@ void compute_owners(rps_context& c, const double* atoms, hipStream_t st) {
   datoms.release(nullptr);
 }
 
-// Pieces along the grid of the atoms' products over their Voronoi sets (J and K1): the count
-// of least estimated time that keeps >= 256 rows per piece, given the largest set, the
-// output tiles of one piece of every atom and their outputs.  (32 atoms of 8000 points with
-// 416 functions: 320 tiles of K = 8000 took 3.5 ms for J; in 4 pieces each on the LDS-direct kernel, 0.8 ms.)
-int sparse_pieces(int64_t rows, int64_t tiles, int64_t outputs) {
-  int best = 1;
-  double best_t = 1e300;
-  for (int z = 1; z <= 64; ++z) {
-    if (z > 1 && rows / z < 256) break;
-    const double t = direct64_time(tiles, rows, z, outputs);
-    if (t < best_t) { best_t = t; best = z; }
-  }
-  return best;
-}
 // First row and row count (a multiple of 8, possibly 0) of piece z of nr rows
 void sparse_piece(int64_t nr, int pieces, int z, int64_t& r0, int64_t& k) {
   const int64_t seg = round_up((nr + pieces - 1) / pieces, 8);
@@ -603,7 +589,7 @@ void build_screened_blocks(rps_context& c, const double* atoms, hipStream_t st) 
     for (int64_t i = 0; i < (nc + 127) / 128; ++i) jtiles += std::min((nc + 63) / 64, 2 * i + 2);
     jout += nc * nc;
   }
-  c.sjns = sparse_pieces(c.smaxr, jtiles, jout);
+  c.sjns = (int)sparse_pieces(c.smaxr, jtiles, jout, kSplitWork);
   for (int I = 0; I < natom; ++I) {
     const int64_t nc = c.fofs[I + 1] - c.fofs[I];
     c.qofs[I + 1] = c.qofs[I] + c.sjns * nc * nc;
@@ -1290,7 +1276,7 @@ void ensure_sparse_ws(rps_context& c, int np) {
   const int64_t F = std::max<int64_t>(c.fofs[c.natom], 1);
   int64_t tiles = 0;
   for (int I = 0; I < c.natom; ++I) tiles += (c.fofs[I + 1] - c.fofs[I] + 127) / 128 * ((np + 63) / 64);
-  c.skns = sparse_pieces(c.smaxr, tiles, c.fofs[c.natom] * np);
+  c.skns = (int)sparse_pieces(c.smaxr, tiles, c.fofs[c.natom] * np, kSplitWork);
   c.sCg.alloc(F * np, &c.bytes);
   c.sK1p.alloc(c.skns * F * np, &c.bytes);
   c.sUv.alloc(std::max<int64_t>(c.vofs[c.natom], 1) * np, &c.bytes);

@@ -42,6 +42,10 @@ void gemm_plan(Gemm& g, int64_t work_cap_doubles);
 // workgroups (tiles of 128 x 64 times z splits of K, three workgroups per compute unit) at
 // 65 TF/s, and the z x outputs partials written and read back at 4 TB/s.
 double direct64_time(int64_t tiles, int64_t K, int64_t z, int64_t outputs);
+// Pieces along K of a group of such products: the count of least estimated time that keeps
+// >= 256 of K per piece, given the longest K, the output tiles of one piece of every product
+// and their outputs (doubles); more than one only while the pieces' outputs fit work_cap.
+int64_t sparse_pieces(int64_t K, int64_t tiles, int64_t outputs, int64_t work_cap);
 // One launch of many independent products on the LDS-direct kernel: item i computes
 // C_i = alpha op(A_i) B_i + beta C_i with A_i = base.A + aofs etc. (its own sizes and
 // pitches), and with base.kscale + kofs as the row scale when base.kscale is set (transA

@@ -20,3 +20,20 @@ def test_full_exchange_chunk(R):
     assert rows >= 64 and rows % 64 == 0
     assert rows * R * 8 <= max(2_000_000_000, 64 * R * 8)
     assert rows <= 128 or (rows % 128 == 0 and rows * R * 8 <= 256 << 20)
+
+
+@pytest.mark.parametrize("K,tiles,outputs", [
+    (8000, 320, 32 * 416 ** 2),         # 32 atoms: several pieces
+    (700, 20, 8 * 104 ** 2), (200, 3, 100), (0, 0, 0), (6500, 3520, 64 * 832 ** 2),
+    (100_000, 768 * 5 + 40, 59_000_000),     # without a cap: several pieces of 472 MB each
+])
+def test_atom_block_pieces_fit_the_workspace(K, tiles, outputs):
+    """Partials of the atom blocks' products: one copy, or as many as fit the 512 MB that the
+    other split products keep to."""
+    cap = 64 << 20
+    z = _fn("_ZN3rps13sparse_piecesEllll", K, tiles, outputs, cap)
+    assert z >= 1 and (z == 1 or (z * outputs <= cap and K // z >= 256))
+    if (K, tiles) == (8000, 320):
+        assert z > 1
+    if K == 100_000:
+        assert z == 1 and _fn("_ZN3rps13sparse_piecesEllll", K, tiles, outputs, 1 << 40) > 1
