@@ -1174,7 +1174,9 @@ int64_t carve_fused_ws(const FusedPlan& p, double* base, FusedWs& w) {
     return q;
   };
   w.plan = p;
-  w.U = p.f32u ? nullptr : take(p.nU);      // (FP64: the scratch limit stays where it was before U moved into the kernel)
+  // FP64: counted though nothing reads it where the kernel forms U.  The sizes that the scratch
+  // holds are part of the entry point's contract, and they were set with U in it.
+  w.U = p.f32u ? nullptr : take(p.nU);
   w.Ug = take(p.nUg);
   w.Ugp = p.m4 ? take(p.nUgp) : nullptr;
   w.M2p = take(p.nM2p);
@@ -1216,7 +1218,7 @@ void ensure_workspace(rps_context& c, int np) {
   c.blocks_main = p.blocks_main;
   c.blocks_l3 = p.blocks_l3;
   c.fused_fold = p.fold;
-  c.U.alloc(p.nU, cnt);
+  c.U.alloc(p.inner ? 0 : p.nU, cnt);      // (orbitals formed in the kernel never go to memory)
   c.Ug.alloc(p.nUg, cnt);
   c.Ugp.alloc(p.nUgp, cnt);
   c.M2p.alloc(p.nM2p, cnt);

@@ -86,3 +86,23 @@ def test_full_exchange_of_a_large_grid(lib):
         Kf, (K, _) = ctx.build_full(C), ctx.build(C)
     _say(f"case: full exchange, {w.ngrid} points, |K_full C - K| {np.abs(Kf @ C - K).max() / np.abs(K).max():.1e}")
     assert np.abs(Kf @ C - K).max() < 1e-10 * np.abs(K).max()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_no_orbitals_held_where_the_kernel_forms_them(lib, prec):
+    """n <= 16, N <= 128: U stays in the kernel, so a build's workspace on a large grid with few
+    points is below the size that U alone would have."""
+    import dataclasses
+    w = ri.tiny_s_cell(nfunc=9, mesh=8, L=4.0, nocc=3, naux=4, cid=93, lmax=1)
+    w = dataclasses.replace(w, mesh=np.array([64, 64, 64]))
+    C = np.linalg.qr(np.random.default_rng(8).standard_normal((w.nbas, 3)))[0].copy()
+    pts = np.array([5, 70001, 140003, 210007])
+    with lib.Context.from_workload(w, points=pts, precision=lib.PREC_FP64 if prec == "fp64" else lib.PREC_FP32) as ctx:
+        before = ctx.info()["device_bytes"]
+        K, E = ctx.build(C)
+        for v in (lib.VARIANT_PS, lib.VARIANT_THC):
+            ctx.build(C, variant=v)
+        grown = ctx.info()["device_bytes"] - before
+    _say(f"case: workspace of a build, {prec}: {grown / MB:.1f} MB, U would be {w.ngrid * 16 * 8 / MB:.1f} MB")
+    assert grown < w.ngrid * 16 * 8
+    assert np.isfinite(K).all() and np.isfinite(E)
