@@ -121,13 +121,16 @@ class WorkspacePool {
   int contexts_ = 0;
 };
 
-// hipMalloc that gives the pool's idle blocks back before it fails for want of memory
+// hipMalloc that gives the pool's idle blocks back before it fails for want of memory.  Its
+// error is cleared: it is returned here, and the next launch would report it as its own.
 hipError_t device_malloc(void** p, size_t bytes) {
-  hipError_t e = hipMalloc(p, bytes);
-  if (e == hipErrorOutOfMemory && WorkspacePool::get().trim()) {
-    (void)hipGetLastError();      // the launches after it report the last error
-    e = hipMalloc(p, bytes);
-  }
+  auto attempt = [&] {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+  };
+  hipError_t e = attempt();
+  if (e == hipErrorOutOfMemory && WorkspacePool::get().trim()) e = attempt();
   return e;
 }
 
@@ -1106,7 +1109,7 @@ void choose_shape(rps_context& c, int np, FusedArgs& a) {
 
 // Partials and the zeroed counter of the finalize kernel's split energy sum.
 void ensure_energy_parts(rps_context& c) {
-  if (c.epart.p) return;
+  if (c.ecount.p) return;
   c.epart.alloc(kEnergyBlocks, &c.bytes);
   c.ecount.alloc(1, &c.bytes);
   hip_check(hipMemset(c.ecount.p, 0, sizeof(unsigned)), "hipMemset");
@@ -1206,6 +1209,7 @@ FusedPlan fused_plan(rps_context& c, int np) {
 
 void ensure_workspace(rps_context& c, int np) {
   if (c.ws_np == np) return;
+  c.ws_np = -1;              // no workspace until every buffer below is there
   c.clear_graphs();          // captured builds refer to the buffers about to change
   int64_t* cnt = &c.bytes;
   if (const char* m = getenv("RPS_FP64_MFMA"))
@@ -1274,6 +1278,7 @@ FusedWs context_ws(rps_context& c, int np) {
 // workspace of the products with the screened basis's atom blocks
 void ensure_sparse_ws(rps_context& c, int np) {
   if (c.sws_np == np) return;
+  c.sws_np = -1;
   c.clear_graphs();
   const int64_t F = std::max<int64_t>(c.fofs[c.natom], 1);
   int64_t tiles = 0;
@@ -1311,6 +1316,7 @@ StreamArgs pass_m1(const rps_context& c, int np);
 void ensure_general(rps_context& c, int np) {
   if (c.sparse) ensure_sparse_ws(c, np);
   if (c.gws_np == np) return;
+  c.gws_np = -1;
   c.clear_graphs();
   int64_t* cnt = &c.bytes;
   const bool f32 = c.precision != RPS_PREC_FP64;
@@ -2033,6 +2039,7 @@ bool coulomb_small_path(const rps_context& c, int np) {
 void ensure_coulomb(rps_context& c, int np) {
   const bool small = coulomb_small_path(c, np);
   if (c.jws_np == np && c.jws_small == small) return;
+  c.jws_np = -1;
   int64_t* cnt = &c.bytes;
   c.jchunk = std::min<int64_t>(c.ngp, std::max<int64_t>(64, kCoulombChunk / np / 64 * 64));
   c.jCp.alloc(c.Np * np, cnt);
@@ -2050,10 +2057,8 @@ void ensure_coulomb(rps_context& c, int np) {
 // ej = dV sum_R rho V_H.  All steps run on st in FP64.
 // Lower triangles of the atom J blocks Phi_I^T diag(v) Phi_I, then J = dV sum over atoms
 void sparse_j(rps_context& c, const double* vh, double* J, hipStream_t st) {
-  if (!c.sQ.p) {
-    c.sQ.alloc(std::max<int64_t>(c.qofs[c.natom], 1), &c.bytes);
-    c.svv.alloc(std::max<int64_t>(c.vofs[c.natom], 1), &c.bytes);
-  }
+  if (!c.sQ.p) c.sQ.alloc(std::max<int64_t>(c.qofs[c.natom], 1), &c.bytes);
+  if (!c.svv.p) c.svv.alloc(std::max<int64_t>(c.vofs[c.natom], 1), &c.bytes);
   hip_check(gather_rows(vh, 1, c.sperm.p, c.vofs[c.natom], c.vofs[c.natom], 1, c.svv.p, 1, st), "V_H rows");
   Gemm g;
   g.A = c.sPhi.p; g.transA = true; g.B = c.sPhi.p; g.C = c.sQ.p;
@@ -2157,25 +2162,23 @@ void madelung_impl(rps_context& c, int32_t nocc, const double* C, double* K, dou
   const int64_t N = c.nbas, Np = c.Np, np = round_up(nocc, 16);
   int64_t* cnt = &c.bytes;
   if (!c.Sdev.p) {
-    c.Sdev.alloc(Np * Np, cnt);
     const int z = coulomb_splits(c);
     int64_t tmp = 0;
     DBuf<double> work;
+    if (z > 1) work.alloc(z * Np * Np, &tmp);
+    c.Sdev.alloc(Np * Np, cnt);
     Gemm g;
     g.M = Np; g.N = Np; g.K = c.ngp;
     g.A = c.Phi.p; g.lda = Np; g.transA = true; g.B = c.Phi.p; g.ldb = Np;
     g.C = c.Sdev.p; g.ldc = Np; g.alpha = c.dV;
     if (z > 1) {
-      work.alloc(z * Np * Np, &tmp);
       g.splitk = z; g.work = work.p;
     }
     hip_check(gemm_f64(g, st), "overlap");
     hip_check(hipStreamSynchronize(st), "sync");
   }
-  if (c.mCp.n < Np * np) {
-    c.mCp.alloc(Np * np, cnt);
-    c.mSC.alloc(Np * np, cnt);
-  }
+  if (c.mCp.n < Np * np) c.mCp.alloc(Np * np, cnt);
+  if (c.mSC.n < Np * np) c.mSC.alloc(Np * np, cnt);
   if (!c.mpart.p) c.mpart.alloc(256, cnt);
   int64_t tmp = 0;
   DBuf<double> hC, hK, hE;

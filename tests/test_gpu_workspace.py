@@ -106,3 +106,53 @@ def test_no_orbitals_held_where_the_kernel_forms_them(lib, prec):
     _say(f"case: workspace of a build, {prec}: {grown / MB:.1f} MB, U would be {w.ngrid * 16 * 8 / MB:.1f} MB")
     assert grown < w.ngrid * 16 * 8
     assert np.isfinite(K).all() and np.isfinite(E)
+
+
+def test_build_after_a_failed_allocation(lib, monkeypatch):
+    """A build whose workspace does not fit returns an error and leaves no half of it behind: the
+    builds after it, of the size that was there before and of the refused one once there is
+    room, are those of a context of their own.  Idle workspace of the full exchange matrix is
+    given back before the library reports that there is no memory."""
+    import torch
+    monkeypatch.setenv("RPS_BUILD_PATH", "general")
+    w = ri.diamond_cell(4.0)
+    rng = np.random.default_rng(9)
+
+    def take_all_but_64_mb():
+        hold = []
+        for _ in range(10):        # (memory freed before may come back a moment later)
+            torch.cuda.empty_cache()
+            free = torch.cuda.mem_get_info()[0]
+            if free <= 80 * MB:
+                break
+            hold.append(torch.empty(free - 64 * MB, dtype=torch.uint8, device="cuda"))
+        _say(f"  {torch.cuda.mem_get_info()[0] / MB:.0f} MB free")
+        assert torch.cuda.mem_get_info()[0] <= 80 * MB
+        return hold
+
+    C16, C48 = (np.linalg.qr(rng.standard_normal((w.nbas, n)))[0].copy() for n in (16, 48))
+    with lib.Context.from_workload(w, seed=w.sketch_seed()) as ctx:
+        pts = ctx.points()
+        want = [ctx.build(C16), ctx.build(C48), ctx.build_coulomb(C16), ctx.build_coulomb(C48)]
+        full = ctx.build_full(C16)
+    with lib.Context.from_workload(w, points=pts) as ctx:
+        ctx.build(C16)
+        ctx.build_coulomb(C16)
+        _say("case: build without room for its workspace")
+        hold = take_all_but_64_mb()        # a part of what n = 48 adds (about 140 MB)
+        with pytest.raises(lib.RpsError):
+            ctx.build(C48)
+        got = [ctx.build(C16)]
+        del hold
+        torch.cuda.empty_cache()
+        got += [ctx.build(C48), ctx.build_coulomb(C16), ctx.build_coulomb(C48)]
+        for (K, E), (Kw, Ew) in zip(got, [want[0], want[1], want[2], want[3]]):
+            assert np.array_equal(K, Kw) and E == Ew
+        # the pool's idle block makes room for a build
+        assert np.array_equal(ctx.build_full(C16), full)
+        ctx.build(C16)
+        hold = take_all_but_64_mb()
+        K, E = ctx.build(C48)
+        assert np.array_equal(K, want[1][0]) and E == want[1][1]
+        del hold
+        torch.cuda.empty_cache()
