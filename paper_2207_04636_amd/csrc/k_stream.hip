@@ -253,30 +253,6 @@ __global__ __launch_bounds__(NW * 64) void stream_kernel(StreamArgs a) {
   stream_body<TM, NC, TRANS, NW>(a, bx, by, smem_raw);
 }
 
-// Persistent form for the batching form: the work items of one pass class
-// (precision, n, orientation) over many cells, taken from a device queue in
-// list order (longest first) until it runs dry; every workgroup ends when the
-// counter passes the last item.  items[i] = (cell, x block, y split) and
-// args[cell] the cell's pass; *counter is zero at launch.
-template <typename TM, int NC, int TRANS, int NW>
-__global__ __launch_bounds__(NW * 64) void stream_queue_kernel(const StreamArgs* __restrict__ args,
-                                                              const StreamItem* __restrict__ items, int nitems,
-                                                              unsigned* __restrict__ counter) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ int s_item;
-  while (true) {
-    if (threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
-    __syncthreads();
-    const int i = s_item;
-    __syncthreads();
-    if (i >= nitems) break;
-    const StreamItem it = items[i];
-    const StreamArgs a = args[it.cell];
-    stream_body<TM, NC, TRANS, NW>(a, it.bx, it.by, smem_raw);
-    __syncthreads();
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Split-BF16 form (precision RPS_PREC_BF16X3) on v_mfma_f32_16x16x32_bf16
 // with FP32 accumulation inside a tile and FP64 across tiles.  Every operand
@@ -550,26 +526,6 @@ __global__ __launch_bounds__(NW * 64) void stream_bf16x3_kernel(StreamArgs a) {
   bf16x3_body<NC, TRANS, NW>(a, bx, by, smem_raw);
 }
 
-// Persistent split-BF16 form (see stream_queue_kernel).
-template <int NC, int TRANS, int NW>
-__global__ __launch_bounds__(NW * 64) void bf16x3_queue_kernel(const StreamArgs* __restrict__ args,
-                                                              const StreamItem* __restrict__ items, int nitems,
-                                                              unsigned* __restrict__ counter) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ int s_item;
-  while (true) {
-    if (threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
-    __syncthreads();
-    const int i = s_item;
-    __syncthreads();
-    if (i >= nitems) break;
-    const StreamItem it = items[i];
-    const StreamArgs a = args[it.cell];
-    bf16x3_body<NC, TRANS, NW>(a, it.bx, it.by, smem_raw);
-    __syncthreads();
-  }
-}
-
 template <typename K>
 int resident_blocks(K kern, size_t lds) {
   int per_cu = 0, dev = 0, cus = 0;
@@ -653,6 +609,9 @@ int stream_splits(int64_t nx, int64_t ny, int target_blocks) {
   return (int)sp;
 }
 
+namespace {
+int64_t stream_xblocks(int64_t nx) { return (nx + 127) / 128; }
+
 hipError_t stream_prepare(const StreamArgs& a, int prec, int nsplit, StreamArgs& b) {
   if (a.np < 16 || a.np > 128 || a.np % 16 || a.nx % 16 || a.ny % BY || a.ldy != a.np) return hipErrorInvalidValue;
   if (nsplit < 1 || prec < 0 || prec > 2) return hipErrorInvalidValue;
@@ -671,6 +630,7 @@ hipError_t stream_prepare(const StreamArgs& a, int prec, int nsplit, StreamArgs&
   b.nxo = a.nx;
   return hipSuccess;
 }
+}  // namespace
 
 // Workgroups of a pass that are resident at once on the current device.
 int stream_resident(int prec, const StreamArgs& a) {
@@ -695,71 +655,6 @@ int stream_plan_tail(int prec, const StreamArgs& a, int64_t part_rows, int64_t* 
   if (sp <= 1) return 1;
   *xfull = xb - rem;
   return (int)sp;
-}
-
-int64_t stream_xblocks(int64_t nx) { return (nx + 127) / 128; }
-
-namespace {
-template <typename TM, int NC, int TRANS>
-hipError_t queue_stream(const StreamArgs* args, const StreamItem* items, int nitems, unsigned* counter, int nblocks,
-                        hipStream_t s, int* resident) {
-  constexpr int NW = 8;
-  const size_t lds = (size_t)2 * BY * stream_ldy<TM, NC>() * sizeof(TM);
-  auto kern = stream_queue_kernel<TM, NC, TRANS, NW>;
-  if (resident) { *resident = resident_blocks(kern, lds); return hipSuccess; }
-  if (lds > 65536) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(NW * 64), lds, s, args, items, nitems, counter);
-  return hipGetLastError();
-}
-
-template <int NC, int TRANS>
-hipError_t queue_bf16x3(const StreamArgs* args, const StreamItem* items, int nitems, unsigned* counter, int nblocks,
-                        hipStream_t s, int* resident) {
-  constexpr int NW = 8;
-  const size_t lds = Bf16Layout<NC>::LDS_BYTES;
-  auto kern = bf16x3_queue_kernel<NC, TRANS, NW>;
-  if (resident) { *resident = resident_blocks(kern, lds); return hipSuccess; }
-  if (lds > 65536) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(NW * 64), lds, s, args, items, nitems, counter);
-  return hipGetLastError();
-}
-
-template <int TRANS>
-hipError_t queue_dispatch(int prec, int np, const StreamArgs* args, const StreamItem* items, int nitems,
-                          unsigned* counter, int nblocks, hipStream_t s, int* resident) {
-#define RPS_QCASE(NC_)                                                                                    \
-  case NC_:                                                                                               \
-    return prec == 0 ? queue_stream<double, NC_, TRANS>(args, items, nitems, counter, nblocks, s, resident) \
-         : prec == 1 ? queue_stream<float, NC_, TRANS>(args, items, nitems, counter, nblocks, s, resident)  \
-                     : queue_bf16x3<NC_, TRANS>(args, items, nitems, counter, nblocks, s, resident);
-  switch (np / 16) {
-    RPS_QCASE(1) RPS_QCASE(2) RPS_QCASE(3) RPS_QCASE(4) RPS_QCASE(5) RPS_QCASE(6) RPS_QCASE(7) RPS_QCASE(8)
-    default: return hipErrorInvalidValue;
-  }
-#undef RPS_QCASE
-}
-}  // namespace
-
-int stream_queue_blocks(int prec, int np, int trans) {
-  int r = 0;
-  if (prec < 0 || prec > 2 || np < 16 || np > 128 || np % 16) return 0;
-  if (trans) (void)queue_dispatch<1>(prec, np, nullptr, nullptr, 0, nullptr, 0, nullptr, &r);
-  else (void)queue_dispatch<0>(prec, np, nullptr, nullptr, 0, nullptr, 0, nullptr, &r);
-  return r;
-}
-
-hipError_t stream_product_queue(const StreamArgs* args, const StreamItem* items, int nitems, int prec, int np,
-                                int trans, unsigned* counter, int nblocks, hipStream_t s) {
-  if (nitems <= 0) return hipSuccess;
-  if (!args || !items || !counter || nblocks < 1 || prec < 0 || prec > 2) return hipErrorInvalidValue;
-  return trans ? queue_dispatch<1>(prec, np, args, items, nitems, counter, nblocks, s, nullptr)
-               : queue_dispatch<0>(prec, np, args, items, nitems, counter, nblocks, s, nullptr);
 }
 
 hipError_t stream_product(const StreamArgs& a, int prec, int nsplit, hipStream_t s) {
