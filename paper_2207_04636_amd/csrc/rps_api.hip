@@ -299,7 +299,8 @@ struct rps_context {
 namespace {
 
 // ------------------------------------------------------------------ set-up helpers
-// Stage timing on stderr when RPS_VERBOSE is set (large set-ups run for minutes).
+// Stage timing on stderr when RPS_VERBOSE is set (large set-ups run for minutes).  (It also
+// prints the plan of the M1 pass when a build's workspace is made.)
 struct StageLog {
   bool on = getenv("RPS_VERBOSE") != nullptr;
   std::chrono::steady_clock::time_point t0 = std::chrono::steady_clock::now();
@@ -1371,7 +1372,14 @@ void ensure_general(rps_context& c, int np) {
   c.gK1.alloc(c.Np * np, cnt);
   c.gK3.alloc(c.Np * np, cnt);
   c.gY.alloc(c.nauxp * np, cnt);
-  if (c.gSp.p) c.gm1_split = stream_plan_tail(c.precision, pass_m1(c, np), kStreamPartRows, &c.gm1_full);
+  if (c.gSp.p) {
+    c.gm1_split = stream_plan_tail(c.precision, pass_m1(c, np), kStreamPartRows, &c.gm1_full);
+    if (getenv("RPS_VERBOSE")) {
+      fprintf(stderr, "[rps build] M1 pass: %lld of %lld row blocks whole, the others in %d pieces\n",
+              (long long)c.gm1_full, (long long)((c.ngp + 127) / 128), c.gm1_split);
+      fflush(stderr);
+    }
+  }
   c.gwork.alloc(kSplitWork, cnt);
   ensure_energy_parts(c);
   c.Cdev.alloc(c.nbas * np, cnt);
