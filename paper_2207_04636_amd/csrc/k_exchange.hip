@@ -1096,8 +1096,8 @@ __global__ __launch_bounds__(512) void fused_f64u_kernel(FusedArgs a) {
   double vb[2][4][4];
   typedef double pair_t __attribute__((ext_vector_type(2)));
   // Addresses are a uniform base in scalar registers and a 32-bit lane offset (three rows of
-  // V: ldv < 2^27, checked on the host).  The offset is made opaque at each use: folded into
-  // 64-bit lane addresses kept over the loop it spills.
+  // V; axes are at most 256 points, so ldv is far below the 2^27 that fit).  The offset is
+  // made opaque at each use: folded into 64-bit lane addresses kept over the loop it spills.
   const uint32_t voff = (uint32_t)((lq * a.ldv + 2 * l16) * 8);
   auto opaque = [](uint32_t x) {
     asm volatile("" : "+v"(x));

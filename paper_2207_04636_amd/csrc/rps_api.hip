@@ -1059,14 +1059,13 @@ void prof_mark(rps_context& c, int slot, hipStream_t st) {
 bool uses_f32u(const rps_context& c, int np) { return c.Phi32.p && np == 16; }
 
 // FP64 with n <= 16 (N <= 128 on the fused path) forms them in its kernel too, unless
-// the 4x4x4 instruction is asked for (grids of 2^27 points and more, beyond its 32-bit
-// lane offsets, keep the kernel that reads U from memory).
+// the 4x4x4 instruction is asked for.
 bool uses_f64u(const rps_context& c, int np) {
-  return c.precision == RPS_PREC_FP64 && np == 16 && !c.use_m4 && c.Np <= 128 && c.ngp < (1ll << 27);
+  return c.precision == RPS_PREC_FP64 && np == 16 && !c.use_m4;
 }
 
 void choose_shape(rps_context& c, int np, FusedArgs& a) {
-  a.nwaves = (np == 16 && (c.precision != RPS_PREC_FP64 || c.use_m4 || uses_f64u(c, np))) ? 8 : 4;
+  a.nwaves = (np == 16) ? 8 : 4;
   a.np = np;
   a.G = c.nauxp;
   a.want_m2 = 1;
