@@ -1258,8 +1258,8 @@ __global__ __launch_bounds__(256, (TN == 2 && !KS) ? 3 : 2) void gemm_big_kernel
 
 // C = sum_z work[z] + beta * C (fixed order over z).  ZL lanes share an output: lane q
 // sums z = q, q + ZL, ... with four loads in flight, then the lanes are added in order.
-// One lane per output left a product of few outputs and many splits (209 x 48 of K =
-// 135040, 256 splits) with 40 blocks of long serial sums: 34 us; 16 lanes: 9 us.
+// One lane per output leaves a product of few outputs and many splits (209 x 48 of K =
+// 135040, 256 splits) with 40 blocks of long serial sums: 34 us in that build; 16 lanes: 7 us.
 template <int ZL>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const double* __restrict__ work, int splitk, int64_t M,
                                                            int64_t N, double* __restrict__ C, int64_t ldc,
@@ -1295,12 +1295,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const double* __rest
   if (Cf) Cf[m * ldcf + n] = (float)*c;
 }
 
-// Several lanes per output where that is needed to fill the device (fewer outputs than
-// 256 blocks of 256 threads) and the splits are enough to share.
+// Several lanes per output where that is needed to fill the device (no more outputs than
+// 256 blocks of 256 threads) and the splits are enough to share.  Sums of 16, 64 and 256
+// splits by one lane and by 16, alone on the device: 10032 outputs 2.4, 4.0, 14.4 and 2.3,
+// 3.6, 3.6 us; 65536 outputs 3.8, 4.7, 23 and 3.2, 4.2, 20 us; 131072 outputs 2.8, 10.5, 37
+// and 4.3, 12.1, 42 us; 262144 outputs 4.4, 20.5, 85 and 8.1, 20.7, 113 us.
 void launch_splitk_reduce(const double* work, int splitk, int64_t M, int64_t N, double* C, int64_t ldc, double beta,
                           float* Cf, int64_t ldcf, hipStream_t s) {
   const int64_t cnt = M * N;
-  if (splitk >= 16 && cnt < 16 * 65536)
+  if (splitk >= 16 && cnt <= 65536)
     hipLaunchKernelGGL(splitk_reduce_kernel<16>, dim3((unsigned)((cnt + 15) / 16)), dim3(256), 0, s, work, splitk, M, N,
                        C, ldc, beta, Cf, ldcf);
   else
@@ -1308,6 +1311,8 @@ void launch_splitk_reduce(const double* work, int splitk, int64_t M, int64_t N, 
                        C, ldc, beta, Cf, ldcf);
 }
 
+// (the row scale comes here only with RPS_GEMM64_DIRECT=0: the Coulomb matrix's operands always
+// meet the LDS-direct kernel's requirements)
 template <int TM, int TN>
 void launch_big(const Gemm& g, dim3 grid, hipStream_t s) {
   if (g.kscale) hipLaunchKernelGGL((gemm_big_kernel<TM, TN, true, false, true>), grid, dim3(256), 0, s, g);
